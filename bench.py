@@ -337,15 +337,18 @@ def time_evaluation(args, torch, E, ctx, s, far_prec, kinds, f, sig, out, u=None
         # whose class events overwrite the first pass's: the self stage time
         # holds both, the class rows would not
         kernels = []
-    far_flops = far_interactions(s) * FAR_FLOPS_PER_INTERACTION
+    # the direct sums' interactions: in FP64 well separated drops go through
+    # expansions, whose kernels are part of the far stage but not of this row
+    direct, expanded = ctx.far_plan() if far_prec == E.FAR_FP64 else (far_interactions(s), 0)
+    far_flops = direct * FAR_FLOPS_PER_INTERACTION
     # the far field runs alone in the timed region unless a share of it is
     # forked beside the self-interaction
     far_alone = not overlap
     name = "k_far32" if far_prec == E.FAR_FP32C else "k_far64"
-    far_ms = avg[2] if far_alone else None
+    far_ms = avg[2] if far_alone and not expanded else None
     far_src = timing_pass
     if far_ms is None and far_flops > 0:
-        # time the far kernel alone with HIP events (ehd_time_far), same tile
+        # time the direct kernel alone with HIP events (ehd_time_far), same tile
         far_ms = ctx.time_far(far_prec, tpt_, nch_, reps=3, kinds=kinds)
         far_src = "launched alone (ehd_time_far, 3 launches)"
     if far_flops > 0:
@@ -382,6 +385,7 @@ def time_evaluation(args, torch, E, ctx, s, far_prec, kinds, f, sig, out, u=None
     ctx.sync()
     return {"dt": dt, "ms_per_step": dt / K * 1e3, "value": T * K / dt, "stage_ms": dict(zip(E.STAGES, avg)),
             "kernels": kernels, "roofline": roof, "far_tile": tile, "far": fo.cpu().numpy(),
+            "far_plan": {"direct_interactions": direct, "expanded_pairs": expanded},
             "kernel_times": timing_pass,
             "overlap_plan": {"classes_beside_far": [p for c, p in enumerate(E.DEGREE_CLASSES) if beside >> c & 1],
                              "far_items_forked": forked}}
@@ -469,7 +473,7 @@ def bench_eval(args, torch, E, W, dev):
                    "grid": "paper (2p+2 longitudes)" if s.grid_mode == 0 else "2p longitudes",
                    "kinds": "S,D,S_L,L", "double_layer_density": "separate u" if args.separate_u else "f",
                    "far_prec": "fp64" if main_prec == E.FAR_FP64 else "fp32c",
-                   "far_interactions": far_interactions(s), "far_tile": r["far_tile"],
+                   "far_interactions": far_interactions(s), "far_plan": r["far_plan"], "far_tile": r["far_tile"],
                    "overlap_plan": r["overlap_plan"], "self_tile": self_tile, "graph": bool(args.graph)},
         "stage_ms": r["stage_ms"],
         "roofline": r["roofline"],

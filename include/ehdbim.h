@@ -18,7 +18,8 @@
  * (Sec. 2.1, eq. mod_weights: the expansion is rotated so that the target is
  * the north pole of an upsampled Gaussian grid of degree q_self), every other
  * drop by the regular rule (eq. reg_quadrature) on its upsampled degree-q_far
- * grid (direct summation).
+ * grid, by direct summation or, in FP64 between well separated drops, by
+ * expansions of the same sums truncated below their rounding (ehd_far_plan).
  *
  * Data layout (all FP64 unless stated):
  *   SH coefficients: orthonormal complex spherical harmonics with the
@@ -76,7 +77,8 @@ enum {
 };
 
 enum {
-    EHD_FAR_FP64 = 0,      /* far-field sums in FP64                         */
+    EHD_FAR_FP64 = 0,      /* far-field sums in FP64, by expansions where that
+                              is faster (ehd_far_plan)                       */
     EHD_FAR_FP32C = 1      /* FP32 arithmetic on drop-centred coordinates,
                               FP32 accumulation per source tile, compensated
                               (Kahan) accumulation of the tile sums          */
@@ -268,13 +270,24 @@ int ehd_overlap_plan(ehd_ctx* ctx, unsigned kinds, int far_prec, int with_u, uns
 
 /* Far-field tile shape: targets per thread (1 or 2) and number of source
  * chunks (1..16, at most the number of source tiles) the targets' sums are
- * split into.  ehd_set_drops sets a default; the autotuner (ehd_time_far over
- * candidates, paper_1811_10270_amd/autotune.py) picks the fastest. */
+ * split into.  ehd_set_drops sets a default (with it the FP64 sums take as many
+ * chunks as there can be; and of few targets each FP64 chunk is cut further);
+ * the autotuner (ehd_time_far over candidates,
+ * paper_1811_10270_amd/autotune.py) picks the fastest. */
 int ehd_set_far_config(ehd_ctx* ctx, int targets_per_thread, int nchunk);
 int ehd_get_far_config(const ehd_ctx* ctx, int* targets_per_thread, int* nchunk);
 
+/* How the FP64 far field of the current shapes is summed: *direct receives
+ * the target-source interactions of the direct sums, *expanded the (target
+ * drop, source drop) pairs that go through solid-harmonic expansions instead.
+ * A pair is expanded if its drops are so far apart that an order of at most 40
+ * truncates below the direct sums' rounding, and if all of them together are
+ * expected to save time; the FP32 far field sums every pair directly.  Renewed
+ * by ehd_set_drops and ehd_update_shape.  Host query only. */
+int ehd_far_plan(const ehd_ctx* ctx, long long* direct, long long* expanded);
+
 /* Autotuner support: mean milliseconds of `reps` launches (after one
- * warm-up launch) of the far-field kernel of precision far_prec for the
+ * warm-up launch) of the far-field kernel (the direct sums) of precision far_prec for the
  * kinds mask `kinds` (as for ehd_layer_potentials) with the given tile
  * shape, on the current source records, timed with HIP events.  Overwrites
  * the far field's partial sums (not the caller's outputs).  Synchronous. */

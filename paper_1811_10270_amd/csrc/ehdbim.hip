@@ -6,7 +6,8 @@
 // Pipeline of one evaluation (all on the context's stream):
 //   k_synth (densities on the far grids) -> k_src_dens (weighted source
 //   records, FP64 and FP32) -> k_self (rotation + rotated-grid synthesis +
-//   singular reduction, FP64) -> k_far64 / k_far32 (direct sums over the
+//   singular reduction, FP64) -> expansions between well separated drops
+//   (expand.hip, FP64 far field) -> k_far64 / k_far32 (direct sums over the
 //   other drops) -> k_combine (scaling, component selection).
 #include <hip/hip_runtime.h>
 
@@ -25,6 +26,7 @@
 #include <vector>
 
 #include "ehdbim.h"
+#include "expand.h"
 #include "tables.h"
 #include "ctx_access.h"
 
@@ -43,6 +45,9 @@ constexpr int kNearMaxM = 12;     // nearly singular targets: most check points 
 constexpr int kNearSplit = 16;    // source chunks per pair in the check-point sums
 constexpr int kRec32 = 13;        // x-c(3) n(3) wf(3) wu(3) wsig(1)
 constexpr int kMaxChunks = 16;    // far field: largest number of source chunks
+constexpr int kMaxCut = 4;        // far field: most parts a chunk is cut into where targets are few
+constexpr int kCutTargets = 32768;     // and the most targets that are few
+constexpr int kMaxListDrops = 1024;    // far field: most drops for tile lists without expansions
 
 // ---------------------------------------------------------------------------
 // Device-side descriptors
@@ -425,25 +430,39 @@ __global__ void k_geom_sources(const DropInfo* __restrict__ drops, const LegTab*
 }
 
 // (2 rho_d)^2 of each drop, rho_d the largest distance of its far-grid
-// nodes from its centre, into centre[4 d + 3]; one block per drop.
+// nodes from its centre, into centre[4 d + 3], and the squares of rho_d and of
+// its target nodes' largest distance into rad[2 d], rad[2 d + 1]; one block
+// per drop.
 __global__ __launch_bounds__(kThreads) void k_drop_radius(const DropInfo* __restrict__ drops,
                                                           const double* __restrict__ src64, long long Spad,
-                                                          double* __restrict__ centre)
+                                                          const double* __restrict__ tx, long long T,
+                                                          double* __restrict__ centre, double* __restrict__ rad)
 {
     const DropInfo D = drops[blockIdx.x];
-    double m = 0.0;
+    double m = 0.0, mt = 0.0;
     for (long long s = D.soff + threadIdx.x; s < D.soff + D.ns; s += blockDim.x) {
         const double dx = src64[s] - D.c[0], dy = src64[Spad + s] - D.c[1], dz = src64[2 * Spad + s] - D.c[2];
         m = fmax(m, dx * dx + dy * dy + dz * dz);
     }
-    __shared__ double red[kThreads];
-    red[threadIdx.x] = m;
+    const long long nt = (long long)(D.p + 1) * D.nlon_p;
+    for (long long t = D.toff + threadIdx.x; t < D.toff + nt; t += blockDim.x) {
+        const double dx = tx[t] - D.c[0], dy = tx[T + t] - D.c[1], dz = tx[2 * T + t] - D.c[2];
+        mt = fmax(mt, dx * dx + dy * dy + dz * dz);
+    }
+    __shared__ double red[2][kThreads];
+    red[0][threadIdx.x] = m;
+    red[1][threadIdx.x] = mt;
     __syncthreads();
     for (int o = kThreads / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
+        if (threadIdx.x < o)
+            for (int k = 0; k < 2; ++k) red[k][threadIdx.x] = fmax(red[k][threadIdx.x], red[k][threadIdx.x + o]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) centre[4 * blockIdx.x + 3] = 4.0 * red[0];
+    if (threadIdx.x == 0) {
+        centre[4 * blockIdx.x + 3] = 4.0 * red[0][0];
+        rad[2 * blockIdx.x] = red[0][0];
+        rad[2 * blockIdx.x + 1] = red[1][0];
+    }
 }
 
 // Weighted densities of the far-field sources (both precisions).
@@ -1156,13 +1175,27 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
 // double layer's -6, multiply the tile sums, and the Stokes single layer
 // keeps its f/r and r^-3 parts in separate tile sums (2 and 8 times the
 // terms).
+//
+// A block of targets sums only the tiles of other drops, and where well
+// separated drops go through expansions (expand.hip) those of the drops near
+// one of its own: the runs of tiles runs[runoff[bx]..] (first tile, position
+// in the block's list; the last entry holds the list's length), and a target
+// skips a tile whose drop is its own or (near given) not near it,
+// near[own drop][drop].  The list's tiles are split evenly over the chunks.
+// runoff NULL: every tile.
+struct FarRuns {
+    const int* runoff;
+    const int2* runs;
+    const unsigned char* near;
+    int nd;
+};
 template <int TPT, unsigned KM>
 __device__ __forceinline__ void far64_block(const double* __restrict__ tx,
                                                     const double* __restrict__ tnrm,
                                                     const int* __restrict__ tdrop, long long T,
                                                     const double* __restrict__ src, long long Spad,
                                                     const int2* __restrict__ tile_info, int ntiles,
-                                                    int tiles_per_chunk, double* __restrict__ partial, int bx, int by)
+                                                    int nchunk, FarRuns fr, double* __restrict__ partial, int bx, int by)
 {
     constexpr bool wS = KM & EHD_STOKES_SL, wD = KM & EHD_STOKES_DL;
     constexpr bool wSL = KM & EHD_LAP_SL, wL = KM & EHD_LAP_DL, wK = KM & EHD_LAP_DLADJ;
@@ -1185,8 +1218,14 @@ __device__ __forceinline__ void far64_block(const double* __restrict__ tx,
     // lie on one drop skips that drop's tiles whole
     const long long tb0 = (long long)bx * blockDim.x * TPT, tb1 = min(T - 1, tb0 + (long long)blockDim.x * TPT - 1);
     const int bdrop = tdrop[tb0] == tdrop[tb1] ? tdrop[tb0] : -1;
-    const int t0 = by * tiles_per_chunk, t1 = min(ntiles, t0 + tiles_per_chunk);
-    for (int tile = t0; tile < t1; ++tile) {
+    const int r0 = fr.runoff ? fr.runoff[bx] : 0, r1 = fr.runoff ? fr.runoff[bx + 1] - 1 : 1;
+    const int total = fr.runoff ? fr.runs[r1].y : ntiles;
+    const int per = (total + nchunk - 1) / nchunk, t0 = by * per, t1 = min(total, t0 + per);
+    for (int r = r0; r < r1; ++r) {
+    const int base = fr.runoff ? fr.runs[r].y : 0, first = fr.runoff ? fr.runs[r].x : 0;
+    const int end = min(t1, fr.runoff ? fr.runs[r + 1].y : ntiles);
+    for (int lt = max(t0, base); lt < end; ++lt) {
+        const int tile = first + lt - base;
         const int2 ti = tile_info[tile];          // (drop, sources in the tile)
         if (ti.x == bdrop) continue;              // uniform over the block
         const long long s = (long long)tile * kTile + threadIdx.x;
@@ -1194,8 +1233,12 @@ __device__ __forceinline__ void far64_block(const double* __restrict__ tx,
             for (int r = 0; r < kRec64; ++r) smd[r * kTile + threadIdx.x] = src[r * Spad + s];
         __syncthreads();
         const int sd = ti.x;
-        bool other = false;   // some target of this thread is not on the tile's drop
-        for (int k = 0; k < TPT; ++k) other = other || (sd != myd[k]);
+        bool other = false, mine[TPT];   // this thread's targets that the tile counts for
+        for (int k = 0; k < TPT; ++k) {
+            mine[k] = sd != myd[k];
+            if (fr.near) mine[k] = mine[k] && myd[k] >= 0 && fr.near[(long long)myd[k] * fr.nd + sd];
+            other = other || mine[k];
+        }
         double a[TPT][9], b[TPT][3];
         for (int k = 0; k < TPT; ++k) {
             for (int c = 0; c < 9; ++c) a[k][c] = 0.0;
@@ -1250,7 +1293,7 @@ __device__ __forceinline__ void far64_block(const double* __restrict__ tx,
             }
         }
         for (int k = 0; k < TPT; ++k) {
-            if (sd == myd[k]) continue;      // own drop: tile not counted
+            if (!mine[k]) continue;          // own drop, or one expanded
             // powers of two of 2/r: S 2 and 8, D 32 (with its -6), S_L 2, L and K* 8
             for (int c = 0; c < 3; ++c) acc[k][c] += fma(0.125, b[k][c], 0.5 * a[k][c]);
             for (int c = 3; c < 6; ++c) acc[k][c] += -0.1875 * a[k][c];
@@ -1259,6 +1302,7 @@ __device__ __forceinline__ void far64_block(const double* __restrict__ tx,
             acc[k][8] += 0.125 * a[k][8];
         }
         __syncthreads();
+    }
     }
     for (int k = 0; k < TPT; ++k)
         if (tt[k] < T)
@@ -1273,11 +1317,11 @@ __global__ __launch_bounds__(kThreads) void k_far64(const double* __restrict__ t
                                                     const int* __restrict__ tdrop, long long T,
                                                     const double* __restrict__ src, long long Spad,
                                                     const int2* __restrict__ tile_info, int ntiles,
-                                                    int tiles_per_chunk, double* __restrict__ partial, int nbx,
+                                                    int nchunk, FarRuns fr, double* __restrict__ partial, int nbx,
                                                     int vb0, int vb1)
 {
     for (int vb = vb0 + (int)blockIdx.x; vb < vb1; vb += (int)gridDim.x)
-        far64_block<TPT, KM>(tx, tnrm, tdrop, T, src, Spad, tile_info, ntiles, tiles_per_chunk, partial, vb % nbx,
+        far64_block<TPT, KM>(tx, tnrm, tdrop, T, src, Spad, tile_info, ntiles, nchunk, fr, partial, vb % nbx,
                              vb / nbx);
 }
 
@@ -1427,24 +1471,28 @@ struct RowMap {
     int comp[9];
 };
 
+// One thread per (target, row): the parts' loads are independent, so a small
+// evaluation waits for them once (two p = 32 drops, 64 parts: 36 -> 6 us).
 __global__ void k_combine(const double* __restrict__ raw_self, const double* __restrict__ partial,
-                          int nchunk, long long T, RowMap rows, double* __restrict__ self_out,
-                          double* __restrict__ far_out)
+                          int nparts, const double* __restrict__ expanded, long long T, RowMap rows,
+                          double* __restrict__ self_out, double* __restrict__ far_out)
 {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int r = blockIdx.y;
     if (t >= T) return;
-    for (int r = 0; r < rows.n; ++r) {
-        const int c = rows.comp[r];
-        double f = 0.0;
-        for (int ch = 0; ch < nchunk; ++ch) f += partial[((long long)ch * 9 + c) * T + t];
-        f *= kInv4Pi;
-        const double s = raw_self[(long long)c * T + t];
-        if (far_out) {
-            self_out[(long long)r * T + t] = s;
-            far_out[(long long)r * T + t] = f;
-        } else {
-            self_out[(long long)r * T + t] = s + f;
-        }
+    const int c = rows.comp[r];
+    const double* const p = partial + (long long)c * T + t;
+    double f = 0.0;
+#pragma unroll 16
+    for (int k = 0; k < nparts; ++k) f += p[(long long)k * 9 * T];
+    if (expanded) f += expanded[(long long)c * T + t];
+    f *= kInv4Pi;
+    const double s = raw_self[(long long)c * T + t];
+    if (far_out) {
+        self_out[(long long)r * T + t] = s;
+        far_out[(long long)r * T + t] = f;
+    } else {
+        self_out[(long long)r * T + t] = s + f;
     }
 }
 
@@ -1824,7 +1872,16 @@ struct ehd_ctx {
     double* d_syn = nullptr;         // synthesis scratch [9][max(T,Spad)]
     long long syn_stride = 0;
     double* d_raw = nullptr;         // [9][T]
-    double* d_partial = nullptr;     // [kMaxChunks][9][T]
+    double* d_partial = nullptr;     // [parts][9][T]: parts of the direct sums (far_parts)
+    double* d_expanded = nullptr;    // [9][T]: sums over the expanded pairs
+    double* d_rad = nullptr;         // [nd][2] squared radii: far-grid nodes, target nodes
+    // FP64 far field of separated drops by expansions, and the tiles the
+    // direct sums keep per target block (tile shapes of one and two targets
+    // per thread)
+    ehd::Expand ex;
+    ehd::Expand::Buf nearb, runoff[2], runs[2];
+    bool far_lists = false;
+    bool far_set = false;            // tile shape chosen by the caller
     int nchunk = 1;                  // far field: source chunks (grid y)
     int far_tpt = 1;                 // far field: targets per thread
     int self_pf[4] = {0, 0, 0, 0};   // self-interaction: Legendre prefetch batch per degree class (0: default)
@@ -1953,6 +2010,11 @@ struct ehd_ctx {
         near.release();
         near.release_tables();
         near.on = false;
+        ex.release();
+        for (ehd::Expand::Buf* b : {&nearb, &runoff[0], &runoff[1], &runs[0], &runs[1]}) {
+            if (b->p) (void)hipFree(b->p);
+            *b = {};
+        }
         for (void* a : allocs) (void)hipFree(a);
         allocs.clear();
         d_info = nullptr;
@@ -2112,14 +2174,14 @@ static const void* self_kernel_of_class(int cls, bool HF, bool HU, bool HS, int 
 
 // FP64 far-field launchers, one per (targets per thread, kinds mask).
 using Far64Launch = void (*)(dim3, hipStream_t, const double*, const double*, const int*, long long, const double*,
-                             long long, const int2*, int, int, double*, int, int, int);
+                             long long, const int2*, int, int, FarRuns, double*, int, int, int);
 template <int TPT, unsigned KM>
 static void launch_far64_km(dim3 grid, hipStream_t st, const double* tx, const double* tn, const int* tdrop,
-                            long long T, const double* src, long long S, const int2* tile_info, int ntiles, int tpc,
-                            double* partial, int nbx, int vb0, int vb1)
+                            long long T, const double* src, long long S, const int2* tile_info, int ntiles,
+                            int nchunk, FarRuns fr, double* partial, int nbx, int vb0, int vb1)
 {
     hipLaunchKernelGGL((k_far64<TPT, KM>), grid, dim3(kThreads), 0, st, tx, tn, tdrop, T, src, S, tile_info, ntiles,
-                       tpc, partial, nbx, vb0, vb1);
+                       nchunk, fr, partial, nbx, vb0, vb1);
 }
 template <int TPT, std::size_t... I>
 static const std::array<Far64Launch, 32>& far64_table_impl(std::index_sequence<I...>)
@@ -2656,6 +2718,76 @@ static int read_centres(ehd_ctx* ctx)
     return EHD_OK;
 }
 
+// Which pairs of drops the FP64 far field expands (expand.hip), and the tiles
+// that the direct sums keep: per block of targets the runs of tiles of the
+// other drops that are not expanded for all of the block's own.
+static int plan_far(ehd_ctx* ctx, const std::vector<double>& rad)
+{
+    const int nd = ctx->nd;
+    std::vector<ehd::ExpandDrop> drops(nd);
+    for (int d = 0; d < nd; ++d) {
+        const DropInfo& D = ctx->info[d];
+        drops[d] = {D.soff, D.ns, D.toff, (long long)(D.p + 1) * D.nlon_p, {D.c[0], D.c[1], D.c[2]},
+                    std::sqrt(rad[2 * d]), std::sqrt(rad[2 * d + 1])};
+    }
+    EHD_HIP(ctx, ehd::expand_plan(ctx->ex, drops, ctx->stream));
+    const bool on = ctx->ex.on;
+    ctx->far_lists = on || nd <= kMaxListDrops;
+    if (!ctx->far_lists) return EHD_OK;
+    const std::vector<unsigned char>& near = ctx->ex.near;
+    std::vector<int> off[2];
+    std::vector<int2> runs[2];
+    std::vector<unsigned char> any(nd);
+    for (int s = 0; s < 2; ++s) {
+        const long long step = (long long)kThreads * (s + 1);
+        int lo = 0;                                    // first drop of the block
+        for (long long t = 0; t < ctx->T; t += step) {
+            const size_t first = runs[s].size();
+            off[s].push_back((int)first);
+            while (t >= drops[lo].toff + drops[lo].nt) ++lo;
+            std::fill(any.begin(), any.end(), 0);
+            for (int i = lo; i < nd && drops[i].toff < std::min(ctx->T, t + step); ++i)
+                for (int j = 0; j < nd; ++j) any[j] |= (unsigned char)(i != j && (!on || near[(size_t)i * nd + j]));
+            int at = 0;
+            for (int j = 0; j < nd; ++j) {
+                if (!any[j]) continue;
+                const int tile = (int)(drops[j].soff / kTile);
+                // drops follow one another in the tiles: adjacent ones make one run
+                if (runs[s].size() == first || runs[s].back().x + at - runs[s].back().y != tile)
+                    runs[s].push_back(make_int2(tile, at));
+                at += (int)((drops[j].ns + kTile - 1) / kTile);
+            }
+            runs[s].push_back(make_int2(0, at));
+        }
+        off[s].push_back((int)runs[s].size());
+    }
+    auto put = [&](ehd::Expand::Buf& b, const void* v, size_t bytes) {
+        if (bytes > b.cap) {
+            if (b.p) (void)hipFree(b.p);
+            b = {};
+            const hipError_t e = hipMalloc(&b.p, bytes);
+            if (e != hipSuccess) return e;
+            b.cap = bytes;
+        }
+        return hipMemcpyAsync(b.p, v, bytes, hipMemcpyHostToDevice, ctx->stream);
+    };
+    hipError_t e = on ? put(ctx->nearb, near.data(), near.size()) : hipSuccess;
+    for (int s = 0; s < 2; ++s) {
+        if (e == hipSuccess) e = put(ctx->runoff[s], off[s].data(), sizeof(int) * off[s].size());
+        if (e == hipSuccess) e = put(ctx->runs[s], runs[s].data(), sizeof(int2) * runs[s].size());
+    }
+    const hipError_t es = hipStreamSynchronize(ctx->stream);   // the host lists go out of scope
+    if (e == hipErrorOutOfMemory) {                            // no room: direct sums over every tile
+        (void)hipGetLastError();
+        ctx->ex.release();
+        ctx->far_lists = false;
+        e = hipSuccess;
+    }
+    EHD_HIP(ctx, e);
+    EHD_HIP(ctx, es);
+    return EHD_OK;
+}
+
 // Target geometry on the own grids and far-source geometry on the far grids
 // from the context's copy of x.  Synchronous.
 static int build_geometry(ehd_ctx* ctx)
@@ -2670,10 +2802,12 @@ static int build_geometry(ehd_ctx* ctx)
     hipLaunchKernelGGL(k_geom_sources, dim3((S + 255) / 256), dim3(256), 0, ctx->stream, ctx->d_info,
                        ctx->d_legs, ctx->d_slot_drop, ctx->d_syn, vs, S, ctx->d_src64, ctx->d_src32);
     hipLaunchKernelGGL(k_drop_radius, dim3(ctx->nd), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_src64, S,
-                       ctx->d_centre);
+                       ctx->d_tx, T, ctx->d_centre, ctx->d_rad);
     EHD_HIP(ctx, hipGetLastError());
+    std::vector<double> rad(2 * ctx->nd);
+    EHD_HIP(ctx, hipMemcpyAsync(rad.data(), ctx->d_rad, sizeof(double) * rad.size(), hipMemcpyDeviceToHost, ctx->stream));
     EHD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    return EHD_OK;
+    return plan_far(ctx, rad);
 }
 
 int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h, const int* q_far_h,
@@ -2938,12 +3072,17 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
     if ((rc = dev_alloc(ctx, &ctx->d_src64, (size_t)kRec64 * S))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_src32, (size_t)kRec32 * S))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_raw, 9 * T))) return rc;
+    // default tile shape (the FP64 far field: far_chunks)
     const long long tblocks = (T + kThreads - 1) / kThreads;
     ctx->far_tpt = 1;
     ctx->nchunk = (int)std::min<long long>(std::min<long long>(std::max<long long>(1, (2048 + tblocks - 1) / tblocks),
                                                                ctx->ntiles), kMaxChunks);
-    if ((rc = dev_alloc(ctx, &ctx->d_partial, (size_t)kMaxChunks * 9 * T))) return rc;
+    ctx->far_set = false;
+    const size_t parts = kMaxChunks * (T > kCutTargets ? 1 : kMaxCut);
+    if ((rc = dev_alloc(ctx, &ctx->d_partial, parts * 9 * T))) return rc;
+    if ((rc = dev_alloc(ctx, &ctx->d_expanded, (size_t)9 * T))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_info_tmp, ndrops))) return rc;
+    if ((rc = dev_alloc(ctx, &ctx->d_rad, 2 * (size_t)ndrops))) return rc;
 
     // --- target geometry (own grids) and far-source geometry
     return build_geometry(ctx);
@@ -3024,10 +3163,37 @@ int ehd_num_coefs(const ehd_ctx* ctx, long long* ncoef)
 
 // Far-field launch with the context's tile shape (targets per thread, source
 // chunks) on the context's launch stream.
-// Number of far-field work items (target block, chunk) of a tile shape.
-static long long far_items(const ehd_ctx* ctx, int tpt, int nchunk)
+// Blocks of targets of a tile shape.
+static long long far_blocks(const ehd_ctx* ctx, int tpt)
 {
-    return (ctx->T + (long long)kThreads * tpt - 1) / ((long long)kThreads * tpt) * nchunk;
+    return (ctx->T + (long long)kThreads * tpt - 1) / ((long long)kThreads * tpt);
+}
+
+// Source chunks of an evaluation: those the caller chose, or the default.
+// With the default the FP64 direct sums take as many as there can be, since
+// the drops near a target are few tiles (256 drops of p = 32: 1 chunk 34.3 ms,
+// 4 27.1, 16 23.5; 64 drops of mixed degree, 4 chunks 9.5 ms, 16 7.4); the
+// FP32 sums depend on the split at their rounding and keep theirs.
+static int far_chunks(const ehd_ctx* ctx, int far_prec)
+{
+    return ctx->far_set || far_prec != EHD_FAR_FP64 ? ctx->nchunk : std::min(ctx->ntiles, kMaxChunks);
+}
+
+// Source parts (partial sums per target) of a tile shape: its chunks; in FP64
+// each is cut into up to four where there are so few blocks of targets that
+// the chunks would leave compute units with less than four blocks (two p = 32
+// drops, q_far = 96, 18 blocks x 16 chunks: 271 -> 190 us).
+static int far_parts(const ehd_ctx* ctx, int far_prec, int tpt, int nchunk)
+{
+    if (far_prec != EHD_FAR_FP64 || ctx->T > kCutTargets) return nchunk;
+    const long long items = far_blocks(ctx, tpt) * nchunk;
+    return nchunk * (int)std::min<long long>(kMaxCut, std::max<long long>(1, (4LL * ctx->ncu + items - 1) / items));
+}
+
+// Number of far-field work items (target block, part) of a tile shape.
+static long long far_items(const ehd_ctx* ctx, int far_prec, int tpt, int nchunk)
+{
+    return far_blocks(ctx, tpt) * far_parts(ctx, far_prec, tpt, nchunk);
 }
 
 // Far-field items [vb0, vb1) (vb1 < 0: all), on `blocks` looping blocks
@@ -3037,16 +3203,21 @@ static int launch_far(ehd_ctx* ctx, int far_prec, unsigned kinds, int tpt, int n
 {
     const long long T = ctx->T, S = ctx->Spad;
     const long long tblocks = (T + (long long)kThreads * tpt - 1) / ((long long)kThreads * tpt);
-    const long long nvb = tblocks * nchunk;
+    const int slots = far_parts(ctx, far_prec, tpt, nchunk);
+    const long long nvb = tblocks * slots;
     if (vb1 < 0) vb1 = nvb;
     if (nvb > INT_MAX) EHD_FAIL(ctx, EHD_E_SHAPE, "too many far-field work items (%lld)", nvb);
     if (vb1 <= vb0) return EHD_OK;
-    const int tpc = (ctx->ntiles + nchunk - 1) / nchunk;
+    const int tpc = (ctx->ntiles + slots - 1) / slots;
     const dim3 grid((unsigned)(blocks > 0 ? std::min(blocks, vb1 - vb0) : vb1 - vb0));
     if (far_prec == EHD_FAR_FP64) {
         const Far64Launch fn = (tpt == 2 ? far64_table<2>() : far64_table<1>())[kinds & EHD_ALL_KINDS];
-        fn(grid, ctx->ls, ctx->d_tx, ctx->d_tn, ctx->d_tdrop, T, ctx->d_src64, S, ctx->d_tile_info, ctx->ntiles, tpc,
-           ctx->d_partial, (int)tblocks, (int)vb0, (int)vb1);
+        FarRuns fr{nullptr, nullptr, nullptr, ctx->nd};
+        if (ctx->far_lists)
+            fr = {(const int*)ctx->runoff[tpt - 1].p, (const int2*)ctx->runs[tpt - 1].p,
+                  ctx->ex.on ? (const unsigned char*)ctx->nearb.p : nullptr, ctx->nd};
+        fn(grid, ctx->ls, ctx->d_tx, ctx->d_tn, ctx->d_tdrop, T, ctx->d_src64, S, ctx->d_tile_info, ctx->ntiles, slots,
+           fr, ctx->d_partial, (int)tblocks, (int)vb0, (int)vb1);
     } else {
         const Far32Launch fn = (tpt == 2 ? far32_table<2>() : far32_table<1>())[kinds & EHD_ALL_KINDS];
         fn(grid, ctx->ls, ctx->d_tx, ctx->d_tn, ctx->d_tdrop, T, ctx->d_src32, S, ctx->d_tile_info, ctx->d_centre,
@@ -3163,9 +3334,10 @@ struct OverlapPlan {
 static OverlapPlan overlap_plan(ehd_ctx* ctx, int far_prec, unsigned kinds, bool needF, bool needU, bool needLap)
 {
     OverlapPlan pl;
-    pl.nvb = far_items(ctx, ctx->far_tpt, ctx->nchunk);
+    const int nchunk = far_chunks(ctx, far_prec);
+    pl.nvb = far_items(ctx, far_prec, ctx->far_tpt, nchunk);
     if (!ctx->overlap || ctx->nd < 2) return pl;   // one drop: no far interactions, nothing to overlap
-    pl.whole = pl.nvb <= 2LL * ctx->ncu;
+    pl.whole = far_blocks(ctx, ctx->far_tpt) * nchunk <= 2LL * ctx->ncu;
     if (pl.whole) {
         for (int c = 0; c < 4; ++c)
             if (!ctx->cls_drops[c].empty()) pl.beside |= 1u << c;
@@ -3241,36 +3413,48 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
         return rc;
     };
     const OverlapPlan pl = overlap_plan(ctx, far_prec, kinds, needF, needU, needLap);
+    const int nchunk = far_chunks(ctx, far_prec);
     const long long nvb = pl.nvb, split = pl.split;
     const bool whole = pl.whole;
     const unsigned beside = whole ? 0xFu : pl.beside;
+    const bool expanded = far_prec == EHD_FAR_FP64 && ctx->ex.on;
+    // 3a. far field: the expanded pairs of drops
+    auto expansions = [&]() -> int {
+        if (!expanded) return EHD_OK;
+        EHD_HIP(ctx, ehd::expand_enqueue(ctx->ex, ctx->ls, kinds, ctx->d_src64, S, ctx->d_tx, ctx->d_tn, T,
+                                         ctx->d_expanded));
+        return EHD_OK;
+    };
     int rc;
     if (split == 0) {
         if ((rc = self_classes(0xFu))) return rc;
         ctx->mark(2);
-        // 3. far field
-        if ((rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, ctx->nchunk))) return rc;
+        if ((rc = expansions())) return rc;
+        // 3b. far field: direct sums
+        if ((rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, nchunk))) return rc;
     } else {
         if (!whole && (rc = self_classes(0xFu & ~beside))) return rc;
         EHD_HIP(ctx, hipEventRecord(ctx->ev_fork, ctx->ls));
         EHD_HIP(ctx, hipStreamWaitEvent(ctx->far_stream, ctx->ev_fork, 0));
         hipStream_t main = ctx->ls;
         ctx->ls = ctx->far_stream;
-        rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, ctx->nchunk, 0, split, whole ? 0 : ctx->ncu);
+        rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, nchunk, 0, split, whole ? 0 : ctx->ncu);
         ctx->ls = main;
         if (rc) return rc;
         EHD_HIP(ctx, hipEventRecord(ctx->ev_join, ctx->far_stream));
         if ((rc = self_classes(beside))) return rc;
         ctx->mark(2);
-        // 3. far field: the rest, then the forked part
-        if ((rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, ctx->nchunk, split, nvb))) return rc;
+        if ((rc = expansions())) return rc;
+        // 3b. far field: the rest, then the forked part
+        if ((rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, nchunk, split, nvb))) return rc;
         EHD_HIP(ctx, hipStreamWaitEvent(ctx->ls, ctx->ev_join, 0));
     }
 
     ctx->mark(3);
     // 4. outputs
-    hipLaunchKernelGGL(k_combine, dim3((T + 255) / 256), dim3(256), 0, ctx->ls, ctx->d_raw, ctx->d_partial,
-                       ctx->nchunk, T, rows, self_out_d, far_out_d);
+    hipLaunchKernelGGL(k_combine, dim3((T + 255) / 256, rows.n), dim3(256), 0, ctx->ls, ctx->d_raw, ctx->d_partial,
+                       far_parts(ctx, far_prec, ctx->far_tpt, nchunk), expanded ? ctx->d_expanded : nullptr, T, rows,
+                       self_out_d, far_out_d);
     EHD_HIP(ctx, hipGetLastError());
     // 5. nearly singular targets: replace the affected drops' far sums
     if (ctx->near.npairs) {
@@ -3308,7 +3492,7 @@ int ehd_layer_potentials(ehd_ctx* ctx, const double* fcoef_d, const double* ucoe
         rc = enqueue_evaluation(ctx, fcoef_d, ucoef_d, sigcoef_d, kinds, far_prec, self_out_d, far_out_d);
     } else {
         const ehd_ctx::GraphKey key{fcoef_d, ucoef_d, sigcoef_d, self_out_d, far_out_d, kinds, far_prec,
-                                    ctx->far_tpt, ctx->nchunk};
+                                    ctx->far_tpt, far_chunks(ctx, far_prec)};
         if (!ctx->gexec || !(key == ctx->gkey)) {
             ctx->drop_graph();
             // record the sequence on the private stream, then instantiate
@@ -3402,6 +3586,7 @@ int ehd_set_far_config(ehd_ctx* ctx, int targets_per_thread, int nchunk)
                  kMaxChunks, ctx->ntiles);
     ctx->far_tpt = targets_per_thread;
     ctx->nchunk = nchunk;
+    ctx->far_set = true;
     return EHD_OK;
 }
 
@@ -3411,6 +3596,21 @@ int ehd_get_far_config(const ehd_ctx* ctx, int* targets_per_thread, int* nchunk)
     *targets_per_thread = ctx->far_tpt;
     *nchunk = ctx->nchunk;
     return ctx->nd ? EHD_OK : EHD_E_STATE;
+}
+
+int ehd_far_plan(const ehd_ctx* ctx, long long* direct, long long* expanded)
+{
+    if (!ctx || !direct || !expanded) return EHD_E_ARG;
+    if (!ctx->nd) return EHD_E_STATE;
+    *direct = *expanded = 0;
+    for (int i = 0; i < ctx->nd; ++i)
+        for (int j = 0; j < ctx->nd; ++j) {
+            if (i == j) continue;
+            const DropInfo& D = ctx->info[i];
+            if (ctx->ex.on && !ctx->ex.near[(size_t)i * ctx->nd + j]) ++*expanded;
+            else *direct += (long long)(D.p + 1) * D.nlon_p * ctx->info[j].ns;
+        }
+    return EHD_OK;
 }
 
 int ehd_time_far(ehd_ctx* ctx, int far_prec, unsigned kinds, int targets_per_thread, int nchunk, int reps,

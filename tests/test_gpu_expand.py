@@ -1,0 +1,114 @@
+"""FP64 far field by expansions between well separated drops, against the
+oracle's direct sums (Sec. 2.1, eq. reg_quadrature).
+
+Tolerance: an expanded pair is truncated at 4e-15 of its potentials, and the
+sums of some 1e5 terms of either side round at 1e-13 of the largest value;
+1e-12 normwise per output leaves a decade."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1811_10270_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_1811_10270_amd import ehdbim
+    ehdbim.load()
+    return ehdbim
+
+
+def scaled(s, radii):
+    """The suspension with each drop's shape scaled about its centre."""
+    off = W.drop_offsets(s.p.astype(np.int64))
+    x = s.xcoef.copy()
+    for d, r in enumerate(radii):
+        blk = x[3 * off[d]:3 * off[d + 1]].reshape(3, -1)
+        blk[:, 2:] *= r
+    s.xcoef = x
+    return s
+
+
+def far(E, s, kinds, ntest=400):
+    """(far rows, oracle's far rows at the same sampled targets, expanded pairs)."""
+    import torch
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    ctx.set_drops(s.p, s.q_self, s.q_far, s.grid_mode, torch.from_numpy(s.xcoef).to(dev))
+    f, sg = torch.from_numpy(s.fcoef).to(dev), torch.from_numpy(s.sigcoef).to(dev)
+    u = torch.from_numpy(s.ucoef).to(dev) if s.ucoef is not None else None
+    rows = E.rows_for_kinds(kinds)
+    so = torch.zeros(len(rows), ctx.ntargets, dtype=torch.float64, device=dev)
+    fo = torch.full_like(so, 7.0)
+    ctx.layer_potentials(f, u, sg, kinds, E.FAR_FP64, so, fo)
+    ctx.sync()
+    direct, expanded = ctx.far_plan()
+    td, tn = oracle.all_targets(s)
+    sel = np.unique(np.linspace(0, len(td) - 1, ntest).astype(int))
+    ref = oracle.far(s, td[sel], tn[sel])[rows]
+    got = fo.cpu().numpy()[:, sel]
+    ctx.close()
+    return got, ref, expanded
+
+
+def suspension(case):
+    if case == "uneven_degrees":          # every translation class, drops of few and of many nodes
+        s = W.with_separate_u(W.suspension(48, [6, 15, 29, 32], 15.0, 11))
+    elif case == "uneven_sizes":          # radii from 0.2 to 1.1 about one length unit, 2p longitudes
+        s = W.suspension(40, [25], 14.0, 12, grid_mode=1)
+        scaled(s, np.random.default_rng(1).uniform(0.2, 1.1, 40))
+    else:                                 # lowest orders only: sparse, far apart
+        s = W.suspension(40, [24], 60.0, 13)
+    return s
+
+
+@pytest.mark.parametrize("case", ["uneven_degrees", "uneven_sizes", "sparse"])
+def test_expanded_far_field_matches_the_direct_sums(E, case):
+    s = suspension(case)
+    got, ref, expanded = far(E, s, E.ALL_KINDS)
+    err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    print(case, "expanded pairs", expanded, "err", err, flush=True)
+    assert expanded > 0
+    assert np.all(err < TOL), err
+
+
+@pytest.mark.parametrize("kinds", [1, 2, 4, 8, 16, 3, 5, 12, 18, 20, 28, 15])
+def test_every_kind_set_takes_its_own_columns(E, kinds):
+    got, ref, expanded = far(E, suspension("uneven_degrees"), kinds, 60)
+    err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    assert expanded > 0 and np.all(err < TOL), (kinds, err)
+
+
+def test_plan_follows_the_shape_and_replays(E):
+    """The plan is renewed by ehd_update_shape (drops moved together: nothing
+    to expand; back: the same bits), and a recorded evaluation gives them too."""
+    import torch
+    s = suspension("sparse")
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    x = torch.from_numpy(s.xcoef).to(dev)
+    ctx.set_drops(s.p, s.q_self, s.q_far, s.grid_mode, x)
+    f, sg = torch.from_numpy(s.fcoef).to(dev), torch.from_numpy(s.sigcoef).to(dev)
+    out = [torch.zeros(9, ctx.ntargets, dtype=torch.float64, device=dev) for _ in range(2)]
+    ctx.layer_potentials(f, None, sg, E.ALL_KINDS, E.FAR_FP64, out[0])
+    ctx.sync()
+    pairs = ctx.far_plan()
+    assert pairs[1] > 0
+    close = s.xcoef.copy().reshape(s.ndrops, 3, -1)
+    close[:, :, 0] *= 0.01                # centres within a radius of each other
+    ctx.update_shape(torch.from_numpy(close.ravel().copy()).to(dev))
+    assert ctx.far_plan()[1] == 0
+    ctx.update_shape(x)
+    assert ctx.far_plan() == pairs
+    for graph, overlap in ((False, False), (True, False), (True, True)):
+        ctx.set_overlap(overlap)
+        ctx.set_graph(graph)
+        for _ in range(3):
+            out[1].fill_(7.0)
+            ctx.layer_potentials(f, None, sg, E.ALL_KINDS, E.FAR_FP64, out[1])
+            ctx.sync()
+            assert torch.equal(out[0], out[1]), (graph, overlap)
+            _ = (out[1] * 2.0).sum().item()       # eager work between replays
+    ctx.set_graph(False)
+    ctx.close()

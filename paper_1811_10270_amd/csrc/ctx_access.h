@@ -12,6 +12,13 @@ int ehd_ctx_device(const ehd_ctx* ctx);
 int ehd_ctx_ndrops(const ehd_ctx* ctx);
 int ehd_ctx_drop_p(const ehd_ctx* ctx, int d);
 int ehd_ctx_graph_on(const ehd_ctx* ctx);
+// Operator matrices of the singular rule of one kind (EHD_LAP_DLADJ or
+// EHD_STOKES_DL) for a solve's mat-vecs: built for the current shapes (*ready
+// false: not to be had, evaluate with ehd_layer_potentials), the kind's layer
+// potential by them, and their end (all: give the memory back in any case).
+int ehd_ctx_matrices(ehd_ctx* ctx, unsigned kind, bool* ready);
+int ehd_ctx_matrix_potential(ehd_ctx* ctx, const double* in, int far_prec, double* out);
+void ehd_ctx_matrices_done(ehd_ctx* ctx, bool all);
 // Record `msg` as the context's last error and return `code`.
 int ehd_ctx_fail(ehd_ctx* ctx, int code, const char* msg);
 

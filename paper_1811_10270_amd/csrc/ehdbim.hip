@@ -48,6 +48,9 @@ constexpr int kMaxChunks = 16;    // far field: largest number of source chunks
 constexpr int kMaxCut = 4;        // far field: most parts a chunk is cut into where targets are few
 constexpr int kCutTargets = 32768;     // and the most targets that are few
 constexpr int kMaxListDrops = 1024;    // far field: most drops for tile lists without expansions
+constexpr long long kOpGrid = 1LL << 30;           // operator matrices: bytes of rotated-grid weights at a time
+constexpr int kOpGroup = 8;                        // targets per group of one weight field
+constexpr size_t kOpKeep = (size_t)2 << 30;        // and the most memory kept from solve to solve
 
 // ---------------------------------------------------------------------------
 // Device-side descriptors
@@ -82,6 +85,7 @@ struct DropInfo {
     long long soff;            // first far-field source slot (tile aligned)
     long long ns;              // real far-field source nodes
     double c[3];               // reference centre (mean position)
+    long long moff;            // operator matrices: doubles per field of the earlier drops
 };
 
 // Column-major index of the (n, m) triangle, n = m..p: column m starts at
@@ -617,15 +621,21 @@ static inline bool self_row0(int p)
     return p <= 16 ? SelfClass<16>::ROW0 : p <= 24 ? SelfClass<24>::ROW0 : p <= 32 ? SelfClass<32>::ROW0 : SelfClass<48>::ROW0;
 }
 
-template <int PMAX, bool HF, bool HU, bool HS, int PFT = 0>
+// MODE 0: layer potentials.  MODE 1 and 2 take no density: instead of summing
+// they store the rule's weights on the rotated grid, w (h.n0) / (4 pi r^3)
+// (K*) or -6 w (h.n) h_i h_j / (4 pi r^5) (D, ij = xx xy xz yy yz zz), at
+// raw[slot * gstride + (ij * (Q + 1) + latitude) * nlon + longitude], slot the
+// target's place in `order` (for the solvers' operator matrices).
+template <int PMAX, bool HF, bool HU, bool HS, int PFT = 0, int MODE = 0>
 __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     const DropInfo* __restrict__ drops, const LegTab* __restrict__ legs,
     const WigTab* __restrict__ wigs, const int* __restrict__ order, const int* __restrict__ tdrop,
     const double* __restrict__ xcoef, const double* __restrict__ fcoef,
     const double* __restrict__ ucoef, const double* __restrict__ scoef,
     const double* __restrict__ tx, const double* __restrict__ tnrm, long long T, unsigned kinds,
-    double* __restrict__ raw)
+    double* __restrict__ raw, long long gstride)
 {
+    static_assert(MODE == 0 || (!HF && !HU && !HS), "weights only");
     constexpr int NF = 3 + (HF ? 3 : 0) + (HU ? 3 : 0) + (HS ? 1 : 0);
     constexpr int FOFF = 3, UOFF = 3 + (HF ? 3 : 0), SOFF = 3 + (HF ? 3 : 0) + (HU ? 3 : 0);
     constexpr int NV = NF + 6;           // + x_theta(3), x_phi/sin(3)
@@ -640,7 +650,8 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     // Workgroups go to the 8 XCDs round-robin; give each XCD a contiguous
     // range of the cost-ordered target list, so that the blocks sharing an
     // L2 work on neighbouring targets (same rotation tables).
-    const long long tg = order[xcd_slot(blockIdx.x, gridDim.x)];
+    const unsigned slot = xcd_slot(blockIdx.x, gridDim.x);
+    const long long tg = order[slot];
     const int d = tdrop[tg];
     const DropInfo D = drops[d];
     const int p = D.p;
@@ -905,6 +916,32 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
         }
     };
 
+    // MODE 1, 2: the weights of the node (latitude i, longitude lon)
+    double* const gout = MODE ? raw + slot * gstride : nullptr;
+    auto emit_node = [&](const double* val, double wi, int i, int lon) {
+        const double cx = val[4] * val[8] - val[5] * val[7];
+        const double cy = val[5] * val[6] - val[3] * val[8];
+        const double cz = val[3] * val[7] - val[4] * val[6];
+        const double J2 = cx * cx + cy * cy + cz * cz;
+        const double hx = x0[0] - val[0], hy = x0[1] - val[1], hz = x0[2] - val[2];
+        const double ir = rsqrt_nr(hx * hx + hy * hy + hz * hz), ir3 = ir * ir * ir * kInv4Pi;
+        double* const o = gout + (long long)i * Lq.nlon + lon;
+        if constexpr (MODE == 1) {
+            o[0] = wi * J2 * rsqrt_nr(J2) * (hx * n0v[0] + hy * n0v[1] + hz * n0v[2]) * ir3;
+        } else {
+            // w (h.n) = wi (h.(x_theta x x_phi)): the area factor cancels
+            const double t = -6.0 * wi * (hx * cx + hy * cy + hz * cz) * ir3 * ir * ir;
+            const long long gs = (long long)(Lq.Q + 1) * Lq.nlon;
+            const double tx_ = t * hx, ty_ = t * hy;
+            o[0] = tx_ * hx;
+            o[gs] = tx_ * hy;
+            o[2 * gs] = tx_ * hz;
+            o[3 * gs] = ty_ * hy;
+            o[4 * gs] = ty_ * hz;
+            o[5 * gs] = t * hz * hz;
+        }
+    };
+
     // Row 0 of the longitude sums (when taken apart): each wave stores the two
     // nodes (phi = 0, pi) of its latitude in the block's row-0 records, and
     // after the block's last barrier one wave evaluates all sixteen in
@@ -913,7 +950,10 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     double* const RZ = R + LB * gsz + NW * NBW;
     auto row0_eval = [&](int bb) {
         const int i = bb * LB + (lane >> 1);
-        if (lane < 2 * LB && i <= Lq.Q) eval_node(RZ + lane * NVP, wsing[i], true);
+        if (lane < 2 * LB && i <= Lq.Q) {
+            if constexpr (MODE) emit_node(RZ + lane * NVP, wsing[i], i, (lane & 1) ? qg.H : 0);
+            else eval_node(RZ + lane * NVP, wsing[i], true);
+        }
     };
 
     // first prefetch batch of the next latitude block: block 0's here, each
@@ -998,6 +1038,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
             const bool node_ok = 2 * l <= qg.H &&
                                  (c4 == 0 || (c4 == 1 && 2 * l < qg.H) || (c4 == 2 && l > 0) ||
                                   (c4 == 3 && l > 0 && 2 * l < qg.H));
+            const int lon = c4 == 0 ? l : c4 == 1 ? qg.H - l : c4 == 2 ? qg.H + l : 2 * qg.H - l;
             dbl4 ec, es, oc, os;
             // longitude sums of latitude ll of the block, this wave's row tile:
             // k-steps up to the class maximum without guards (past a group's
@@ -1070,10 +1111,18 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
                 publish(na);
                 __builtin_amdgcn_sched_barrier(0);
                 chain(ll0 + dll);
-                eval_node(na, node_ok ? wa : 0.0, false);
+                if constexpr (MODE) {
+                    if (node_ok) emit_node(na, wa, b * LB + ll0, lon);
+                } else {
+                    eval_node(na, node_ok ? wa : 0.0, false);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 publish(nb);
-                eval_node(nb, node_ok ? wb : 0.0, false);
+                if constexpr (MODE) {
+                    if (node_ok) emit_node(nb, wb, b * LB + ll0 + dll, lon);
+                } else {
+                    eval_node(nb, node_ok ? wb : 0.0, false);
+                }
             } else {
                 for (int ll = ll0; ll < ll1; ll += dll) {
                     const int i = b * LB + ll;
@@ -1115,7 +1164,10 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    if (node_ok) eval_node(NB + lane * NVP, wsing[i], true);
+                    if (node_ok) {
+                        if constexpr (MODE) emit_node(NB + lane * NVP, wsing[i], i, lon);
+                        else eval_node(NB + lane * NVP, wsing[i], true);
+                    }
                     // the buffer is rewritten for the next latitude
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
@@ -1143,6 +1195,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
         __syncthreads();  // Fourier blocks consumed before the next block's Legendre sums
     }
     if (SC::ROW0 && qg.l0 == 1 && nblk > 0 && wv == ((nblk - 1) & (NW - 1))) row0_eval(nblk - 1);
+    if constexpr (MODE != 0) return;
     for (int c = 0; c < 9; ++c) {
         const double sv = wave_sum_dpp(acc[c]);
         if (lane == 0) red[wv][c] = sv;
@@ -1535,6 +1588,360 @@ __global__ void k_analyze(const DropInfo* __restrict__ drops, const LegTab* __re
 }
 
 // ---------------------------------------------------------------------------
+// Operator matrices of the singular rule for the Galerkin solves: on fixed
+// shapes K* and D are linear in the density's coefficients, so a solve builds
+// each target's row once, at about the cost of one evaluation, and its
+// mat-vecs read it (two p = 32 drops: 1350 us for k_self, 12 us for a K*
+// product and 40 for a D product).  A row is the transpose of k_self's steps: the weights on the
+// rotated grid (k_self, MODE 1 and 2), their longitude and Legendre sums
+// (k_adj_grid), the transposed rotation (k_adj_rot).
+// ---------------------------------------------------------------------------
+
+// Operand tables of k_adj_grid for one singular grid (p, Q), filled by
+// k_adj_tables: the quarter-period cos/sin of the term groups EC ES OC OS
+// (QuarterGrid) in column tiles of 16 terms, per k-step the lane's
+// l = 4 k + lane / 16, with the factors 1, 2 and -2 of the expansion; and
+// Pbar per latitude tile of 16, (order m, sixteen degrees from m on) and
+// k-step of four latitudes.
+struct AdjTab {
+    double *trig, *P;
+    int nk, ntrig, nleg, nrow;     // k-steps; column tiles; (m, degree tile) pairs; latitude tiles
+};
+__host__ __device__ inline int adj_terms(int p, int q) { return q == 0 ? p / 2 + 1 : q == 1 ? p / 2 : (p + 1) / 2; }
+__host__ __device__ inline AdjTab adj_sizes(int p, int nlon)
+{
+    AdjTab a{};
+    a.nk = (nlon / 4 + 1 + 7) / 8 * 2;                       // in chunks of eight l
+    for (int q = 0; q < 4; ++q) a.ntrig += (adj_terms(p, q) + 15) / 16;
+    for (int m = 0; m <= p; ++m) a.nleg += (p + 1 - m + 15) / 16;
+    return a;
+}
+// Order and group of term `term` of column tile ct (m = -1: none).
+__device__ __forceinline__ void adj_term(int p, int ct, int term, int* grp, int* m)
+{
+    int q = 0;
+    while (q < 4 && ct >= (adj_terms(p, q) + 15) / 16) ct -= (adj_terms(p, q++) + 15) / 16;
+    *grp = q;
+    const int k = 16 * ct + term;
+    *m = (q < 4 && k < adj_terms(p, q)) ? (q == 0 ? 2 * k : q == 1 ? 2 * k + 2 : 2 * k + 1) : -1;
+}
+// Order and first degree of pair `q` of the (m, degree tile) pairs.
+__device__ __forceinline__ void adj_pair(int p, int q, int* m, int* n0)
+{
+    int k = 0;
+    for (; k <= p; ++k) {
+        const int nt = (p + 1 - k + 15) / 16;
+        if (q < nt) break;
+        q -= nt;
+    }
+    *m = k;
+    *n0 = k + 16 * q;
+}
+
+__global__ void k_adj_tables(const LegTab* __restrict__ legs, const AdjTab* __restrict__ tabs)
+{
+    const AdjTab A = tabs[blockIdx.y];
+    if (!A.P) return;                                        // not a singular grid
+    const LegTab L = legs[blockIdx.y];
+    const int p = L.p, nl = L.nlon / 4 + 1, Q1 = L.Q + 1, nrow = (Q1 + 15) / 16;
+    const long nc = ncoef(p);
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, lane = e & 63;
+    if (e < A.ntrig * A.nk * 64) {
+        const int k = (e >> 6) % A.nk, ct = (e >> 6) / A.nk, l = 4 * k + (lane >> 4);
+        int g, m;
+        adj_term(p, ct, lane & 15, &g, &m);
+        double v = 0.0;
+        if (m >= 0 && l < nl)
+            v = L.trig[((long long)l * (p + 1) + m) * 2 + (g & 1)] * ((g & 1) ? -2.0 : m ? 2.0 : 1.0);
+        A.trig[e] = v;
+    }
+    if (e < nrow * A.nleg * 4 * 64) {
+        const int k = (e >> 6) & 3, q = ((e >> 6) >> 2) % A.nleg, i = 16 * (((e >> 6) >> 2) / A.nleg) + 4 * k + (lane >> 4);
+        int m, n0;
+        adj_pair(p, q, &m, &n0);
+        const int n = n0 + (lane & 15);
+        A.P[e] = (i < Q1 && n <= p) ? L.P[(long long)i * nc + tri(n, m)] : 0.0;
+    }
+}
+
+// The coefficients' sums over the rotated grid of up to eight weight fields of
+// one grid, a wave each (the targets of a group, or the six fields of one),
+//   C(n, m) = sum_i Pbar_n^m(t_i) sum_l g(i, l) (1 or 2) (cos m phi_l, -sin m phi_l),
+// c[slot][field][tri(n, m)] (re, im).  Latitudes in tiles of 16: each wave
+// folds the four images l, N - l, H - l, H + l of its nodes into the four term
+// groups in registers and takes their longitude sums on FP64 MFMA (rows
+// latitudes, columns terms) into LDS; then the Legendre sums of all fields run
+// on MFMA together (rows degrees, columns (field, re/im)), so that the table
+// of Pbar is read once for eight fields.  One block fits a compute unit, so
+// latency bounds it: operands are loaded a chunk or two pairs ahead (without
+// that 6.9, with it 3.3 ms for the four solves of a step of two p = 32 drops).
+// LEG: (m, degree tile) pairs per wave, 7 up to p = 32 (51 pairs), 13 at 48 (100).
+template <int LEG>
+__global__ __launch_bounds__(512) void k_adj_grid(const DropInfo* __restrict__ drops, const LegTab* __restrict__ legs,
+                                                  const AdjTab* __restrict__ tabs, const int* __restrict__ order,
+                                                  const int* __restrict__ tdrop, const int2* __restrict__ groups,
+                                                  int slot0, int nf, long long gstride, long long cstride,
+                                                  const double* __restrict__ g, double* __restrict__ c)
+{
+    extern __shared__ double fs[];                           // [16 latitudes][p + 1][16 = (field, re/im)]
+    __shared__ double fold[8][4][16][9];                     // per wave: term group, latitude, eight l
+    const int2 gr = groups[blockIdx.x];                      // first slot, targets
+    const DropInfo D = drops[tdrop[order[gr.x]]];
+    const LegTab L = legs[D.leg_ps];
+    const AdjTab A = tabs[D.leg_ps];
+    const int p = L.p, N = L.nlon, H = N / 2, nl = H / 2 + 1, Q1 = L.Q + 1;
+    const long nc = ncoef(p);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slot = gr.x - slot0 + (nf == 1 ? wv : 0), f = nf == 1 ? 0 : wv;
+    const bool active = nf == 1 ? wv < gr.y : wv < nf;
+    const double* const gs = g + (active ? slot * gstride + (long long)f * Q1 * N : 0);
+    const int fr = lane >> 3, fl = lane & 7;                 // this lane's latitudes (fr, fr + 8) and l of a chunk
+    double (*const fw)[16][9] = fold[wv];
+    const int ld = 16 * (p + 1);
+    for (int z = threadIdx.x; z < 16 * ld; z += 512) fs[z] = 0.0;   // (sin 0 and absent fields stay zero)
+    int pm[LEG];
+    dbl4 acc[LEG];
+#pragma unroll
+    for (int k = 0; k < LEG; ++k) {
+        int n0;
+        adj_pair(p, min(wv + 8 * k, A.nleg - 1), &pm[k], &n0);
+        acc[k] = dbl4{0, 0, 0, 0};
+    }
+    // column tiles of the groups: one or two each
+    int first[4], two[4];
+#pragma unroll
+    for (int q = 0, at = 0; q < 4; ++q) {
+        first[q] = at;
+        const int nt = (adj_terms(p, q) + 15) / 16;
+        two[q] = nt > 1;
+        at += nt;
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < Q1; i0 += 16) {
+        if (active) {
+            dbl4 a[4][2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[q][0] = a[q][1] = dbl4{0, 0, 0, 0};
+            double v[2][4];                                  // the four images of the next chunk's nodes
+            auto load = [&](int ch) __attribute__((always_inline)) {
+                const int l = min(8 * ch + fl, nl - 1);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double* const row = gs + (long long)min(i0 + fr + 8 * h, Q1 - 1) * N;
+                    v[h][0] = row[l];
+                    v[h][1] = row[l ? N - l : 0];
+                    v[h][2] = row[H - l];
+                    v[h][3] = row[H + l];
+                }
+            };
+            load(0);
+            for (int ch = 0; ch < A.nk / 2; ++ch) {
+                const int l = 8 * ch + fl;
+                double t[2][4][2];                           // this chunk's trig operands
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const double* const tp = A.trig + ((long long)first[q] * A.nk + 2 * ch + u) * 64 + lane;
+                        t[u][q][0] = tp[0];
+                        if (two[q]) t[u][q][1] = tp[A.nk * 64];
+                    }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    // images that coincide, and rows past the last latitude or
+                    // longitude, count nothing
+                    const int r = fr + 8 * h;
+                    const bool on = i0 + r < Q1 && l < nl, in1 = on && l > 0, in2 = on && 2 * l < H;
+                    const double a0 = on ? v[h][0] : 0.0, a1 = in1 ? v[h][1] : 0.0, a2 = in2 ? v[h][2] : 0.0;
+                    const double a3 = in1 && in2 ? v[h][3] : 0.0;
+                    const double s0 = a0 + a1, d0 = a0 - a1, s1 = a2 + a3, d1 = a2 - a3;
+                    fw[0][r][fl] = s0 + s1;                  // EC
+                    fw[1][r][fl] = d0 - d1;                  // ES
+                    fw[2][r][fl] = s0 - s1;                  // OC
+                    fw[3][r][fl] = d0 + d1;                  // OS
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                if (ch + 1 < A.nk / 2) load(ch + 1);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const double e = fw[q][lane & 15][4 * u + (lane >> 4)];
+                        a[q][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e, t[u][q][0], a[q][0], 0, 0, 0);
+                        if (two[q]) a[q][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e, t[u][q][1], a[q][1], 0, 0, 0);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const int term = 16 * w + (lane & 15);
+                    if (term >= adj_terms(p, q)) continue;
+                    const int m = q == 0 ? 2 * term : q == 1 ? 2 * term + 2 : 2 * term + 1;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) fs[((lane >> 4) + 4 * r) * ld + 16 * m + 2 * wv + (q & 1)] = a[q][w][r];
+                }
+        }
+        // Pbar operands two pairs ahead (clamped, unguarded loads): the first
+        // ones before the barrier
+        const double* const P = A.P + ((long long)(i0 / 16) * A.nleg * 4) * 64 + lane;
+        const double* const b = fs + (lane >> 4) * ld + (lane & 15);
+        double av[3][4];
+        auto pair = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) av[k % 3][u] = P[(long long)(4 * min(wv + 8 * k, A.nleg - 1) + u) * 64];
+        };
+        pair(0);
+        pair(1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < LEG; ++k) {
+            if (k + 2 < LEG) pair(k + 2);
+            if (wv + 8 * k < A.nleg)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[k % 3][u], b[4 * u * ld + 16 * pm[k]], acc[k], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // column (field, re/im) of every pair -> that field's coefficients
+    const int v = (lane & 15) >> 1, ri = lane & 1;
+    const bool mine = nf == 1 ? v < gr.y : v < nf;
+    double* const o = c + (mine ? (gr.x - slot0 + (nf == 1 ? v : 0)) * cstride + (nf == 1 ? 0 : v) * 2 * nc : 0);
+#pragma unroll
+    for (int k = 0; k < LEG; ++k) {
+        const int q = wv + 8 * k;
+        if (q >= A.nleg || !mine) continue;
+        int m, n0;
+        adj_pair(p, q, &m, &n0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = n0 + (lane >> 4) + 4 * r;
+            if (n <= p) o[2 * tri(n, m) + ri] = acc[k][r];
+        }
+    }
+}
+
+// Rows of the operator matrix: the transposed rotation of the coefficients
+// c[slot][field], one block per target slot and NB fields.  With z = c_nm e^{im phi_t}
+// and Re c' = A z_re, Im c' = B z_im (k_self step 1), the row's entries are
+//   (cos m phi R + sin m phi I, cos m phi I - sin m phi R),
+//   R_m = sum_m' A_mm' C_re(m'),  I_m = sum_m' B_mm' C_im(m').
+// A wave takes a degree, a lane an order m; the tables' rows run over the
+// second order, so the sums read them transposed:
+//   A_mm' = (-1)^(m+m') A_m'm, B alike (m, m' >= 1), A_m0 = 2 (-1)^m A_0m.
+// mat[drop's matrices][field][node][packed coefficients].
+template <int NB>
+__global__ __launch_bounds__(kThreads) void k_adj_rot(const DropInfo* __restrict__ drops,
+                                                      const LegTab* __restrict__ legs, const WigTab* __restrict__ wigs,
+                                                      const int* __restrict__ order, const int* __restrict__ tdrop,
+                                                      int nf, long long cstride, const double* __restrict__ c,
+                                                      double* __restrict__ mat)
+{
+    __shared__ double2 cs[NB][(EHD_MAX_P + 1) * (EHD_MAX_P + 2) / 2];
+    const int slot = blockIdx.x, f = NB * blockIdx.y;
+    const long long t = order[slot];
+    const DropInfo D = drops[tdrop[t]];
+    const int p = D.p, node = (int)(t - D.toff), j = node / D.nlon_p, k = node % D.nlon_p;
+    const long nc = ncoef(p);
+    const double2* const src = reinterpret_cast<const double2*>(c + slot * cstride + (long long)f * 2 * nc);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        for (int e = threadIdx.x; e < nc; e += kThreads) cs[b][e] = src[b * nc + e];
+    __syncthreads();
+    const long wb = ehd::wig_block(p);
+    const auto A = gmem(wigs[D.wig].A + (long long)j * wb), B = gmem(wigs[D.wig].B + (long long)j * wb);
+    const auto ph = gmem(legs[D.leg_pp].trig + (long long)k * (p + 1) * 2);
+    const long long nt = (long long)(p + 1) * D.nlon_p;
+    // the drop's matrices follow those of the earlier drops: nf T_e 2 ncoef(p_e) doubles each
+    double2* const o = reinterpret_cast<double2*>(mat + D.moff * nf + (f * nt + node) * 2 * nc);
+    const int m = threadIdx.x & 63;
+    const double cm = m <= p ? ph[2 * m] : 0.0, sm = m <= p ? ph[2 * m + 1] : 0.0, sgm = (m & 1) ? -1.0 : 1.0;
+    for (int n = p - (int)(threadIdx.x >> 6); n >= 0; n -= kThreads / 64) {
+        if (m > n) continue;
+        const auto An = A + ehd::wig_off(n) + m, Bn = B + ehd::wig_off(n) + m;
+        const double2* const cn = &cs[0][n * (n + 1) / 2];
+        constexpr int CN = (EHD_MAX_P + 1) * (EHD_MAX_P + 2) / 2;
+        double R[NB], I[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) R[b] = I[b] = 0.0;
+        double sg = -1.0;
+#pragma unroll 4
+        for (int mp = 1; mp <= n; ++mp) {
+            const double a = sg * An[mp * (n + 1)], e = sg * Bn[mp * (n + 1)];
+            sg = -sg;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                R[b] = fma(a, cn[b * CN + mp].x, R[b]);
+                I[b] = fma(e, cn[b * CN + mp].y, I[b]);
+            }
+        }
+        const double a0 = m ? 2.0 * An[0] : An[0];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const double r = m ? sgm * fma(a0, cn[b * CN].x, R[b]) : fma(a0, cn[b * CN].x, 0.5 * R[b]);
+            const double i = m ? sgm * I[b] : 0.0;
+            o[b * nt * nc + n * (n + 1) / 2 + m] = make_double2(cm * r + sm * i, m ? cm * i - sm * r : 0.0);
+        }
+    }
+}
+
+// Products with the operator matrices: a wave per target streams its rows
+// (HBM bound: 19.5 MB per p = 32 drop and field).  NM = 1: raw[8] = M in;
+// NM = 6 (symmetric): raw[3 + i] = sum_j M_ij in_j.
+template <int NM>
+__global__ __launch_bounds__(kThreads) void k_mat_apply(const DropInfo* __restrict__ drops,
+                                                        const int* __restrict__ tdrop, const double* __restrict__ mat,
+                                                        const double* __restrict__ in, long long T,
+                                                        double* __restrict__ raw)
+{
+    const long long t = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+    if (t >= T) return;
+    const DropInfo D = drops[tdrop[t]];
+    const int nc = (int)ncoef(D.p), lane = threadIdx.x & 63;
+    const long long nt = (long long)(D.p + 1) * D.nlon_p;
+    const double2* const M = reinterpret_cast<const double2*>(mat + D.moff * NM + (t - D.toff) * 2 * nc);
+    constexpr int K = NM == 1 ? 1 : 3;
+    const double* const x = in + K * D.coff;                 // (a caller's: aligned to doubles only)
+    double s[K];
+    for (int k = 0; k < K; ++k) s[k] = 0.0;
+    for (int e = lane; e < nc; e += 64) {
+        double2 v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = make_double2(x[2 * (k * nc + e)], x[2 * (k * nc + e) + 1]);
+        auto dot = [&](int row, int k) {
+            const double2 a = M[row * nt * nc + e];
+            return fma(a.x, v[k].x, a.y * v[k].y);
+        };
+        if constexpr (NM == 1) {
+            s[0] += dot(0, 0);
+        } else {
+            auto both = [&](int row, int i, int j) {
+                const double2 a = M[row * nt * nc + e];
+                s[i] = fma(a.x, v[j].x, fma(a.y, v[j].y, s[i]));
+                s[j] = fma(a.x, v[i].x, fma(a.y, v[i].y, s[j]));
+            };
+            s[0] += dot(0, 0);
+            both(1, 0, 1);
+            both(2, 0, 2);
+            s[1] += dot(3, 1);
+            both(4, 1, 2);
+            s[2] += dot(5, 2);
+        }
+    }
+    for (int k = 0; k < K; ++k) {
+        const double v = wave_sum_dpp(s[k]);
+        if (lane == 0) raw[(NM == 1 ? 8 : 3 + k) * T + t] = v;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Nearly singular targets (Sec. 2.1, the interpolation approach): for a
 // target x0 closer than delta to the surface of another drop j, drop j's
 // contribution is replaced by the value at x0 of the polynomial through
@@ -1881,6 +2288,13 @@ struct ehd_ctx {
     ehd::Expand ex;
     ehd::Expand::Buf nearb, runoff[2], runs[2];
     bool far_lists = false;
+    // operator matrices of the solvers and the workspaces of their rows
+    ehd::Expand::Buf opmat, opgrid, opcoef, optab, opgroups;
+    std::vector<int2> opgroup_h[2];  // per weight fields 1, 6: (first slot, targets) of one drop each
+    int opgroup_off[2][5] = {};      // first group of each degree class
+    std::vector<AdjTab> adjtab_h;
+    bool opready = false;            // the tables and groups of the current drops are on the device
+    unsigned opkind = 0;             // the kind the matrices are of, 0: none
     bool far_set = false;            // tile shape chosen by the caller
     int nchunk = 1;                  // far field: source chunks (grid y)
     int far_tpt = 1;                 // far field: targets per thread
@@ -1944,7 +2358,7 @@ struct ehd_ctx {
     }
     void mark(int stage)
     {
-        if (!nslots || capturing) return;
+        if (!nslots || capturing || opkind) return;   // (a solve's matrix evaluations take no slot)
         const long long slot = ncalls % nslots;
         if (stage == 0)
             for (int c = 0; c < 4; ++c) class_used[slot * 4 + c] = 0;
@@ -2011,7 +2425,9 @@ struct ehd_ctx {
         near.release_tables();
         near.on = false;
         ex.release();
-        for (ehd::Expand::Buf* b : {&nearb, &runoff[0], &runoff[1], &runs[0], &runs[1]}) {
+        opkind = 0;
+        opready = false;
+        for (ehd::Expand::Buf* b : {&optab, &opgroups, &nearb, &runoff[0], &runoff[1], &runs[0], &runs[1], &opmat, &opgrid, &opcoef}) {
             if (b->p) (void)hipFree(b->p);
             *b = {};
         }
@@ -2137,8 +2553,9 @@ static int launch_self_class(ehd_ctx* ctx, int cls, const double* f, const doubl
     const double *a9 = ctx->d_tx, *a10 = ctx->d_tn;
     long long a11 = ctx->T;
     double* a13 = ctx->d_raw;
+    long long a14 = 0;
     void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4, (void*)&a5, (void*)&f, (void*)&u,
-                    (void*)&s, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13};
+                    (void*)&s, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&a14};
     EHD_HIP(ctx, hipLaunchKernel(fn, dim3((unsigned)count), dim3(SelfClass<PMAX>::NT), args, lds, ctx->ls));
     ctx->mark_class(cls, 1);
     return EHD_OK;
@@ -2762,13 +3179,8 @@ static int plan_far(ehd_ctx* ctx, const std::vector<double>& rad)
         off[s].push_back((int)runs[s].size());
     }
     auto put = [&](ehd::Expand::Buf& b, const void* v, size_t bytes) {
-        if (bytes > b.cap) {
-            if (b.p) (void)hipFree(b.p);
-            b = {};
-            const hipError_t e = hipMalloc(&b.p, bytes);
-            if (e != hipSuccess) return e;
-            b.cap = bytes;
-        }
+        const hipError_t e = ehd::ensure(b, bytes);
+        if (e != hipSuccess) return e;
         return hipMemcpyAsync(b.p, v, bytes, hipMemcpyHostToDevice, ctx->stream);
     };
     hipError_t e = on ? put(ctx->nearb, near.data(), near.size()) : hipSuccess;
@@ -2970,7 +3382,7 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
 
     // --- per-drop layout
     ctx->info.assign(ndrops, DropInfo{});
-    long long coff = 0, toff = 0, soff = 0;
+    long long coff = 0, toff = 0, soff = 0, moff = 0;
     for (int d = 0; d < ndrops; ++d) {
         DropInfo& D = ctx->info[d];
         D.p = p_h[d];
@@ -2987,7 +3399,9 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
         D.coff = coff;
         D.toff = toff;
         D.soff = soff;
+        D.moff = moff;
         D.ns = (long long)(D.qf + 1) * D.nlon_f;
+        moff += (long long)(D.p + 1) * D.nlon_p * (D.p + 1) * (D.p + 2);
         coff += (long long)(D.p + 1) * (D.p + 2);
         toff += (long long)(D.p + 1) * D.nlon_p;
         soff += (D.ns + kTile - 1) / kTile * kTile;
@@ -2996,6 +3410,12 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
     ctx->T = toff;
     ctx->Spad = soff;
     ctx->ntiles = (int)(soff / kTile);
+    ctx->adjtab_h.assign(legs.size(), AdjTab{});
+    for (const DropInfo& D : ctx->info) {
+        AdjTab& A = ctx->adjtab_h[D.leg_ps];
+        A = adj_sizes(D.p, D.nlon_s);
+        A.nrow = (D.qs + 1 + 15) / 16;
+    }
     if ((rc = upload(ctx, &ctx->d_legs, legs))) return rc;
     if ((rc = upload(ctx, &ctx->d_wigs, wigs))) return rc;
 
@@ -3351,9 +3771,11 @@ static OverlapPlan overlap_plan(ehd_ctx* ctx, int far_prec, unsigned kinds, bool
 }
 
 // The launch sequence of one evaluation, on ctx->ls.
+// matrices: the singular rule by the operator matrices of `kinds`
+// (ehd_ctx_matrices), in the serial order.
 static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double* ucoef_d,
                               const double* sigcoef_d, unsigned kinds, int far_prec, double* self_out_d,
-                              double* far_out_d)
+                              double* far_out_d, bool matrices = false)
 {
     const bool needS = kinds & EHD_STOKES_SL, needD = kinds & EHD_STOKES_DL;
     const bool needLap = kinds & (EHD_LAP_SL | EHD_LAP_DL | EHD_LAP_DLADJ);
@@ -3368,20 +3790,23 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
 
     const long long T = ctx->T, S = ctx->Spad, vs = ctx->syn_stride;
     ctx->mark(0);
-    // 1. densities on the far grids -> weighted source records
+    // 1. densities on the far grids -> weighted source records (one drop: no
+    //    other drop reads them)
+    const bool single = ctx->nd == 1;
     double* synf = needF ? ctx->d_syn : nullptr;
     double* synu = needU ? ctx->d_syn + 3 * vs : nullptr;
     double* syns = needLap ? ctx->d_syn + 6 * vs : nullptr;
-    if (needF)
+    if (needF && !single)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
                            ctx->d_legs, 1, ctx->d_rows_f, fcoef_d, synf, vs);
-    if (needU)
+    if (needU && !single)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
                            ctx->d_legs, 1, ctx->d_rows_f, ucoef_d, synu, vs);
-    if (needLap)
+    if (needLap && !single)
         hipLaunchKernelGGL((k_synth<1, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
                            ctx->d_legs, 1, ctx->d_rows_f, sigcoef_d, syns, vs);
-    hipLaunchKernelGGL(k_src_dens, dim3((S + 255) / 256), dim3(256), 0, ctx->ls, synf, synu, syns, vs, S,
+    if (!single)
+        hipLaunchKernelGGL(k_src_dens, dim3((S + 255) / 256), dim3(256), 0, ctx->ls, synf, synu, syns, vs, S,
                        ctx->d_src64, ctx->d_src32);
     EHD_HIP(ctx, hipGetLastError());
 
@@ -3394,7 +3819,16 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
     const unsigned kself = (ctx->near.npairs && (kinds & EHD_LAP_DLADJ)) ? (kinds | EHD_LAP_SL) : kinds;
     auto self_classes = [&](unsigned cm) {
         int rc = EHD_OK;
-        if (needU && (needF || needLap)) {
+        if (matrices) {
+            const dim3 grid((unsigned)((T + kThreads / 64 - 1) / (kThreads / 64)));
+            const double* const m = (const double*)ctx->opmat.p;
+            if (kinds == EHD_LAP_DLADJ)
+                hipLaunchKernelGGL(k_mat_apply<1>, grid, dim3(kThreads), 0, ctx->ls, ctx->d_info, ctx->d_tdrop, m, sigcoef_d,
+                                   T, ctx->d_raw);
+            else
+                hipLaunchKernelGGL(k_mat_apply<6>, grid, dim3(kThreads), 0, ctx->ls, ctx->d_info, ctx->d_tdrop, m, ucoef_d,
+                                   T, ctx->d_raw);
+        } else if (needU && (needF || needLap)) {
             const unsigned k1 = kself & ~(unsigned)EHD_STOKES_DL;
             if (needF && needLap) rc = launch_self<true, false, true>(ctx, fcoef_d, nullptr, sigcoef_d, k1, cm);
             else if (needF) rc = launch_self<true, false, false>(ctx, fcoef_d, nullptr, sigcoef_d, k1, cm);
@@ -3414,7 +3848,7 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
     };
     const OverlapPlan pl = overlap_plan(ctx, far_prec, kinds, needF, needU, needLap);
     const int nchunk = far_chunks(ctx, far_prec);
-    const long long nvb = pl.nvb, split = pl.split;
+    const long long nvb = pl.nvb, split = matrices ? 0 : pl.split;
     const bool whole = pl.whole;
     const unsigned beside = whole ? 0xFu : pl.beside;
     const bool expanded = far_prec == EHD_FAR_FP64 && ctx->ex.on;
@@ -3431,7 +3865,7 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
         ctx->mark(2);
         if ((rc = expansions())) return rc;
         // 3b. far field: direct sums
-        if ((rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, nchunk))) return rc;
+        if (!single && (rc = launch_far(ctx, far_prec, kinds, ctx->far_tpt, nchunk))) return rc;
     } else {
         if (!whole && (rc = self_classes(0xFu & ~beside))) return rc;
         EHD_HIP(ctx, hipEventRecord(ctx->ev_fork, ctx->ls));
@@ -3453,7 +3887,7 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
     ctx->mark(3);
     // 4. outputs
     hipLaunchKernelGGL(k_combine, dim3((T + 255) / 256, rows.n), dim3(256), 0, ctx->ls, ctx->d_raw, ctx->d_partial,
-                       far_parts(ctx, far_prec, ctx->far_tpt, nchunk), expanded ? ctx->d_expanded : nullptr, T, rows,
+                       single ? 0 : far_parts(ctx, far_prec, ctx->far_tpt, nchunk), expanded ? ctx->d_expanded : nullptr, T, rows,
                        self_out_d, far_out_d);
     EHD_HIP(ctx, hipGetLastError());
     // 5. nearly singular targets: replace the affected drops' far sums
@@ -3466,6 +3900,191 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
     ctx->mark(4);
     return EHD_OK;
 }
+
+}  // extern "C"
+
+// Weights of the singular rule of one degree class's targets
+// [first, first + count) of its order, into ctx->opgrid.
+template <int PMAX>
+static int launch_weights(ehd_ctx* ctx, int cls, int mode, int first, int count, long long gstride)
+{
+    const size_t lds = self_lds_bytes(ctx, ctx->cls_drops[cls], 3);
+    if (lds + (size_t)SelfClass<PMAX>::NW * 9 * 8 > (size_t)ctx->max_lds)
+        EHD_FAIL(ctx, EHD_E_SHAPE, "self-interaction needs %zu bytes of LDS (limit %d)", lds, ctx->max_lds);
+    const void* fn = mode == 1 ? (const void*)k_self<PMAX, false, false, false, 0, 1>
+                               : (const void*)k_self<PMAX, false, false, false, 0, 2>;
+    if (lds > 65536) EHD_HIP(ctx, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const DropInfo* a0 = ctx->d_info;
+    const LegTab* a1 = ctx->d_legs;
+    const WigTab* a2 = ctx->d_wigs;
+    const int *a3 = ctx->d_order + first, *a4 = ctx->d_tdrop;
+    const double *a5 = ctx->d_x, *none = nullptr, *a9 = ctx->d_tx, *a10 = ctx->d_tn;
+    long long a11 = ctx->T;
+    unsigned kinds = 0;
+    double* a13 = (double*)ctx->opgrid.p;
+    void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4, (void*)&a5, (void*)&none, (void*)&none,
+                    (void*)&none, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&gstride};
+    EHD_HIP(ctx, hipLaunchKernel(fn, dim3((unsigned)count), dim3(SelfClass<PMAX>::NT), args, lds, ctx->stream));
+    return EHD_OK;
+}
+
+// The operand tables of k_adj_grid and its groups of targets, once per set of
+// drops: eight targets of one drop a group for one weight field, one for six.
+static hipError_t matrix_tables(ehd_ctx* ctx)
+{
+    if (ctx->opready) return hipSuccess;
+    const size_t nlegs = ctx->adjtab_h.size();
+    size_t doubles = 0, most = 0;
+    std::vector<AdjTab> tabs = ctx->adjtab_h;
+    std::vector<std::pair<size_t, size_t>> at;               // offsets of each grid's tables
+    for (AdjTab& A : tabs) {
+        if (!A.nk) continue;
+        const size_t nt = (size_t)A.ntrig * A.nk * 64, np = (size_t)A.nrow * A.nleg * 4 * 64;
+        at.push_back({doubles, doubles + nt});
+        doubles += nt + np;
+        most = std::max(most, std::max(nt, np));
+    }
+    for (int i = 0; i < 2; ++i) {
+        std::vector<int2>& g = ctx->opgroup_h[i];
+        g.clear();
+        const int per = i ? 1 : kOpGroup;
+        for (int c = 0; c < 4; ++c) {
+            ctx->opgroup_off[i][c] = (int)g.size();
+            int slot = ctx->cls_off[c];
+            for (int d : ctx->cls_drops[c]) {                // the order of the class's targets
+                const int n = (ctx->info[d].p + 1) * ctx->info[d].nlon_p;
+                for (int t = 0; t < n; t += per) g.push_back(make_int2(slot + t, std::min(per, n - t)));
+                slot += n;
+            }
+        }
+        ctx->opgroup_off[i][4] = (int)g.size();
+    }
+    const size_t head = (sizeof(AdjTab) * nlegs + 255) / 256 * 256;
+    hipError_t e = ehd::ensure(ctx->optab, head + sizeof(double) * doubles);
+    if (e == hipSuccess)
+        e = ehd::ensure(ctx->opgroups, sizeof(int2) * (ctx->opgroup_h[0].size() + ctx->opgroup_h[1].size()));
+    if (e != hipSuccess) return e;
+    double* const base = (double*)((char*)ctx->optab.p + head);
+    size_t k = 0;
+    for (AdjTab& A : tabs)
+        if (A.nk) {
+            A.trig = base + at[k].first;
+            A.P = base + at[k++].second;
+        }
+    e = hipMemcpyAsync(ctx->optab.p, tabs.data(), sizeof(AdjTab) * nlegs, hipMemcpyHostToDevice, ctx->stream);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i)
+        e = hipMemcpyAsync((int2*)ctx->opgroups.p + (i ? ctx->opgroup_h[0].size() : 0), ctx->opgroup_h[i].data(),
+                           sizeof(int2) * ctx->opgroup_h[i].size(), hipMemcpyHostToDevice, ctx->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);   // the table of pointers goes out of scope
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_adj_tables, dim3((unsigned)((most + 255) / 256), (unsigned)nlegs), dim3(256), 0, ctx->stream,
+                       ctx->d_legs, (const AdjTab*)ctx->optab.p);
+    e = hipGetLastError();
+    ctx->opready = e == hipSuccess;
+    return e;
+}
+
+// Operator matrices of the singular rule for kind EHD_LAP_DLADJ or
+// EHD_STOKES_DL on the current shapes, enqueued on the context's stream;
+// *ready = false (and nothing done) where the evaluations have to stay: the
+// nearly singular correction needs other kinds' values too, or the device
+// memory does not suffice.  They hold until ehd_ctx_matrices_done.
+int ehd_ctx_matrices(ehd_ctx* ctx, unsigned kind, bool* ready)
+{
+    *ready = false;
+    ctx->opkind = 0;
+    if (ctx->near.npairs) return EHD_OK;
+    const int nf = kind == EHD_STOKES_DL ? 6 : 1;
+    const DropInfo& Z = ctx->info[ctx->nd - 1];
+    const size_t total = sizeof(double) * nf *
+                         (size_t)(Z.moff + (long long)(Z.p + 1) * Z.nlon_p * (Z.p + 1) * (Z.p + 2));
+    hipError_t e = matrix_tables(ctx);
+    struct Plan { long long gstride, cstride; int batch; } plan[4] = {};
+    size_t gbytes = 0, cbytes = 0, lds[4] = {};
+    const int gi = nf == 1 ? 0 : 1;
+    for (int c = 0; c < 4; ++c) {
+        const int count = ctx->opgroup_off[gi][c + 1] - ctx->opgroup_off[gi][c];
+        if (!count) continue;
+        Plan& P = plan[c];
+        for (int d : ctx->cls_drops[c]) {
+            const DropInfo& D = ctx->info[d];
+            P.gstride = std::max(P.gstride, nf * (D.qs + 1LL) * D.nlon_s);
+            P.cstride = std::max(P.cstride, nf * (D.p + 1LL) * (D.p + 2));
+            lds[c] = std::max(lds[c], sizeof(double) * 256 * (D.p + 1));
+        }
+        // groups of targets at a time: their weights within a GiB, at least two
+        // rounds of the device
+        const int per = nf == 1 ? kOpGroup : 1;
+        P.batch = (int)std::min<long long>(count, std::max<long long>(2LL * ctx->ncu, kOpGrid / (8 * P.gstride)) / per);
+        gbytes = std::max(gbytes, sizeof(double) * (size_t)P.gstride * P.batch * per);
+        cbytes = std::max(cbytes, sizeof(double) * (size_t)P.cstride * P.batch * per);
+    }
+    if (e == hipSuccess) e = ehd::ensure(ctx->opmat, total);
+    if (e == hipSuccess) e = ehd::ensure(ctx->opgrid, gbytes);
+    if (e == hipSuccess) e = ehd::ensure(ctx->opcoef, cbytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        ehd_ctx_matrices_done(ctx, true);
+        if (e == hipErrorOutOfMemory) return EHD_OK;
+        EHD_HIP(ctx, e);
+    }
+    const int2* const groups = (const int2*)ctx->opgroups.p + (gi ? ctx->opgroup_h[0].size() : 0);
+    for (int c = 3; c >= 0; --c) {
+        const Plan& P = plan[c];
+        const int end = ctx->opgroup_off[gi][c + 1];
+        for (int first = ctx->opgroup_off[gi][c]; first < end; first += P.batch) {
+            const int ng = std::min(P.batch, end - first), mode = nf == 1 ? 1 : 2;
+            const int2 a = ctx->opgroup_h[gi][first], z = ctx->opgroup_h[gi][first + ng - 1];
+            const int slot0 = a.x, n = z.x + z.y - a.x;      // the groups' targets follow one another in the order
+            const int rc = c == 3   ? launch_weights<48>(ctx, c, mode, slot0, n, P.gstride)
+                           : c == 2 ? launch_weights<32>(ctx, c, mode, slot0, n, P.gstride)
+                           : c == 1 ? launch_weights<24>(ctx, c, mode, slot0, n, P.gstride)
+                                    : launch_weights<16>(ctx, c, mode, slot0, n, P.gstride);
+            if (rc) return rc;
+            auto grid = [&](auto kernel) -> int {
+                EHD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds[c]));
+                hipLaunchKernelGGL(kernel, dim3(ng), dim3(512), lds[c], ctx->stream, ctx->d_info, ctx->d_legs,
+                                   (const AdjTab*)ctx->optab.p, ctx->d_order, ctx->d_tdrop, groups + first, slot0, nf,
+                                   P.gstride, P.cstride, (const double*)ctx->opgrid.p, (double*)ctx->opcoef.p);
+                return EHD_OK;
+            };
+            if (const int r = c == 3 ? grid(k_adj_grid<13>) : grid(k_adj_grid<7>)) return r;
+            auto rot = [&](auto kernel, int nb) {
+                hipLaunchKernelGGL(kernel, dim3(n, nf / nb), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_legs,
+                                   ctx->d_wigs, ctx->d_order + slot0, ctx->d_tdrop, nf, P.cstride,
+                                   (const double*)ctx->opcoef.p, (double*)ctx->opmat.p);
+            };
+            if (nf == 1) rot(k_adj_rot<1>, 1);
+            else rot(k_adj_rot<2>, 2);
+            EHD_HIP(ctx, hipGetLastError());
+        }
+    }
+    ctx->opkind = kind;
+    *ready = true;
+    return EHD_OK;
+}
+
+// Layer potential of the matrices' kind at all targets, out [rows][T].
+int ehd_ctx_matrix_potential(ehd_ctx* ctx, const double* in, int far_prec, double* out)
+{
+    const bool lap = ctx->opkind == EHD_LAP_DLADJ;
+    ctx->ls = ctx->stream;
+    return enqueue_evaluation(ctx, nullptr, lap ? nullptr : in, lap ? in : nullptr, ctx->opkind, far_prec, out, nullptr, true);
+}
+
+// The matrices are not needed any more; large ones give their memory back.
+void ehd_ctx_matrices_done(ehd_ctx* ctx, bool all)
+{
+    ctx->opkind = 0;
+    if (!all && ctx->opmat.cap + ctx->opgrid.cap + ctx->opcoef.cap <= kOpKeep) return;
+    (void)hipStreamSynchronize(ctx->stream);
+    for (ehd::Expand::Buf* b : {&ctx->opmat, &ctx->opgrid, &ctx->opcoef}) {
+        if (b->p) (void)hipFree(b->p);
+        *b = {};
+    }
+}
+
+extern "C" {
 
 int ehd_layer_potentials(ehd_ctx* ctx, const double* fcoef_d, const double* ucoef_d,
                          const double* sigcoef_d, unsigned kinds, int far_prec, double* self_out_d,

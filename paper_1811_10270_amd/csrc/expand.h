@@ -53,6 +53,9 @@ struct Expand {
     }
 };
 
+// Device memory of at least `bytes` in b (its content is lost when it grows).
+hipError_t ensure(Expand::Buf& b, size_t bytes);
+
 // Plan for the given drops: which pairs are expanded, to what order, and the
 // work lists; on = false where the direct sums alone are expected to be
 // faster or the device memory does not suffice.  Synchronous on `stream`.

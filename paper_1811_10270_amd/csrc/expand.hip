@@ -29,6 +29,21 @@
 
 #include "ehdbim.h"
 
+namespace ehd {
+
+hipError_t ensure(Expand::Buf& b, size_t bytes)
+{
+    if (bytes <= b.cap) return hipSuccess;
+    if (b.p) (void)hipFree(b.p);
+    b = Expand::Buf{};
+    const hipError_t e = hipMalloc(&b.p, bytes);
+    if (e == hipSuccess) b.cap = bytes;
+    else b.p = nullptr;
+    return e;
+}
+
+}  // namespace ehd
+
 namespace {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
@@ -636,21 +651,10 @@ int order_for(double rho)
     return -1;
 }
 
-hipError_t ensure(ehd::Expand::Buf& b, size_t bytes)
-{
-    if (bytes <= b.cap) return hipSuccess;
-    if (b.p) (void)hipFree(b.p);
-    b = ehd::Expand::Buf{};
-    const hipError_t e = hipMalloc(&b.p, bytes);
-    if (e == hipSuccess) b.cap = bytes;
-    else b.p = nullptr;
-    return e;
-}
-
 template <typename T>
 hipError_t put(ehd::Expand::Buf& b, const std::vector<T>& v, hipStream_t st)
 {
-    hipError_t e = ensure(b, sizeof(T) * std::max<size_t>(v.size(), 1));
+    hipError_t e = ehd::ensure(b, sizeof(T) * std::max<size_t>(v.size(), 1));
     if (e == hipSuccess && !v.empty()) e = hipMemcpyAsync(b.p, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice, st);
     return e;
 }

@@ -367,6 +367,21 @@ int gmres(ehd_ctx* ctx, long long n, const Op& A, const double* b, double* x, in
     return gmres_ws(ctx, n, A, b, x, m, maxit, tol, ws, iters, relres);
 }
 
+// A solve's operator matrices (ehd_ctx_matrices), where its mat-vecs repay
+// them: they cost about as much as one evaluation (K*) or two (D), so a solve
+// of at least kMatrixSteps steps may use them.
+constexpr int kMatrixSteps = 4;
+struct Matrices {
+    ehd_ctx* ctx;
+    bool on = false;
+    explicit Matrices(ehd_ctx* c) : ctx(c) {}
+    ~Matrices()
+    {
+        if (on) ehd_ctx_matrices_done(ctx, false);
+    }
+    int build(unsigned kind, int maxit) { return maxit < kMatrixSteps ? EHD_OK : ehd_ctx_matrices(ctx, kind, &on); }
+};
+
 int check_opts(ehd_ctx* ctx, int far_prec, int restart, int maxit, double tol)
 {
     if (far_prec != EHD_FAR_FP64 && far_prec != EHD_FAR_FP32C)
@@ -407,8 +422,11 @@ int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, in
     SOLVE_HIP(hipGetLastError());
     // operator E -> E/2 - (R-1)/(R+1) P[K*[E]]
     const double c = (R - 1.0) / (R + 1.0);
+    Matrices mats(ctx);
+    if (!ws && (rc = mats.build(EHD_LAP_DLADJ, maxit))) return rc;
     auto A = [&](const double* in, double* out) -> int {
-        int r = ehd_layer_potentials(ctx, nullptr, nullptr, in, EHD_LAP_DLADJ, far_prec, grid, nullptr);
+        int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid)
+                        : ehd_layer_potentials(ctx, nullptr, nullptr, in, EHD_LAP_DLADJ, far_prec, grid, nullptr);
         if (!r) r = ehd_analyze(ctx, 1, grid, out);
         if (r) return r;
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, 0.5, in, -c, out, n);
@@ -534,8 +552,11 @@ int ehd_solve_velocity(ehd_ctx* ctx, double lambda, const double* fcoef_d, int f
     if ((rc = ehd_layer_potentials(ctx, fcoef_d, nullptr, nullptr, EHD_STOKES_SL, far_prec, grid.p, nullptr))) return rc;
     if ((rc = ehd_analyze(ctx, 3, grid.p, rhs.p))) return rc;
     // operator u -> (lambda+1) u - (lambda-1) P[D[u]]
+    Matrices mats(ctx);
+    if ((rc = mats.build(EHD_STOKES_DL, maxit))) return rc;
     const Op A = [&](const double* in, double* out) -> int {
-        int r = ehd_layer_potentials(ctx, nullptr, in, nullptr, EHD_STOKES_DL, far_prec, grid.p, nullptr);
+        int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid.p)
+                        : ehd_layer_potentials(ctx, nullptr, in, nullptr, EHD_STOKES_DL, far_prec, grid.p, nullptr);
         if (!r) r = ehd_analyze(ctx, 3, grid.p, out);
         if (r) return r;
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, lambda + 1.0, in, -(lambda - 1.0), out, n);

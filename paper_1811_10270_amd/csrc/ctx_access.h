@@ -19,6 +19,11 @@ int ehd_ctx_graph_on(const ehd_ctx* ctx);
 int ehd_ctx_matrices(ehd_ctx* ctx, unsigned kind, bool* ready);
 int ehd_ctx_matrix_potential(ehd_ctx* ctx, const double* in, int far_prec, double* out);
 void ehd_ctx_matrices_done(ehd_ctx* ctx, bool all);
+// The Laplace-Beltrami operator on the current surfaces as five coefficients
+// per target node, geo[5][T] (of g_tt, g_tp, g_pp, g_t, g_p), and its values of
+// one packed field from them, lap[T].
+int ehd_ctx_lap_geometry(ehd_ctx* ctx, double* geo);
+int ehd_ctx_lap_values(ehd_ctx* ctx, const double* geo, const double* coef, double* lap);
 // Record `msg` as the context's last error and return `code`.
 int ehd_ctx_fail(ehd_ctx* ctx, int code, const char* msg);
 

@@ -171,18 +171,24 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
 
 // ---------------------------------------------------------------------------
 // Synthesis of K packed fields on a grid (own p-grid or far q-grid), one
-// block per (drop, latitude).  Legendre sums per m into LDS, then the
-// longitude sums per node.  Optional theta derivative and (1/sin) phi
-// derivative (paper Sec. 2: derivatives from the SH coefficients).
-// out[v * vstride + node], v = f (value), K+f (d/dtheta), 2K+f ((1/s) d/dphi).
+// block per (drop, latitude) and K of the nf fields per drop.  Legendre sums
+// per m into LDS (each split over four threads, whose chains of loads are the
+// latency that bounds a small call), then the longitude sums per node.
+// Optional theta derivative and (1/sin) phi derivative (paper Sec. 2:
+// derivatives from the SH coefficients).
+// out[v * vstride + node], v = f (value), K+f (d/dtheta), 2K+f ((1/s) d/dphi);
+// the next K fields' values K rows further on.
 // ---------------------------------------------------------------------------
+constexpr int kSynParts = 4;
 template <int K, bool DERIV>
 __global__ __launch_bounds__(kThreads) void k_synth(const DropInfo* __restrict__ drops,
                                                     const LegTab* __restrict__ legs, int far_grid,
-                                                    const int2* __restrict__ rows,
+                                                    const int2* __restrict__ rows, int nf,
                                                     const double* __restrict__ coef,
                                                     double* __restrict__ out, long long vstride)
 {
+    constexpr int V = DERIV ? 2 : 1;
+    __shared__ double2 part[V][K][kSynParts][EHD_MAX_P + 1];
     __shared__ double2 G[K][EHD_MAX_P + 1];
     __shared__ double2 Gd[DERIV ? K : 1][EHD_MAX_P + 1];
     const int2 r = rows[blockIdx.x];
@@ -190,13 +196,17 @@ __global__ __launch_bounds__(kThreads) void k_synth(const DropInfo* __restrict__
     const LegTab L = legs[far_grid ? D.leg_pf : D.leg_pp];
     const int p = L.p, i = r.y;
     const long nc = ncoef(p);
-    const double* cf = coef + (long long)K * D.coff;
+    const long long fb = (long long)(blockIdx.y + gridDim.y * blockIdx.z) * K;
+    if (fb >= nf) return;
+    const double* cf = coef + (long long)nf * D.coff + fb * 2 * nc;
+    out += fb * vstride;
     const double* Prow = L.P + (long long)i * nc;
     const double* dProw = L.dP + (long long)i * nc;
-    for (int it = threadIdx.x; it < K * (p + 1); it += blockDim.x) {
-        const int f = it / (p + 1), m = it % (p + 1);
+    for (int it = threadIdx.x; it < K * kSynParts * (p + 1); it += blockDim.x) {
+        const int m = it % (p + 1), s = it / (p + 1) % kSynParts, f = it / (p + 1) / kSynParts;
         double ar = 0.0, ai = 0.0, dr = 0.0, di = 0.0;
-        for (int n = m; n <= p; ++n) {
+#pragma unroll 4
+        for (int n = m + s; n <= p; n += kSynParts) {
             const long k = tri(n, m);
             const double cr = cf[2 * (f * nc + k)], ci = (m == 0) ? 0.0 : cf[2 * (f * nc + k) + 1];
             const double pv = Prow[k];
@@ -208,8 +218,20 @@ __global__ __launch_bounds__(kThreads) void k_synth(const DropInfo* __restrict__
                 di += dv * ci;
             }
         }
-        G[f][m] = make_double2(ar, ai);
-        if (DERIV) Gd[f][m] = make_double2(dr, di);
+        part[0][f][s][m] = make_double2(ar, ai);
+        if (DERIV) part[V - 1][f][s][m] = make_double2(dr, di);
+    }
+    __syncthreads();
+    for (int it = threadIdx.x; it < V * K * (p + 1); it += blockDim.x) {
+        const int m = it % (p + 1), f = it / (p + 1) % K, v = it / (p + 1) / K;
+        double2 a = part[v][f][0][m];
+#pragma unroll
+        for (int s = 1; s < kSynParts; ++s) {
+            a.x += part[v][f][s][m].x;
+            a.y += part[v][f][s][m].y;
+        }
+        if (v) Gd[DERIV ? f : 0][m] = a;
+        else G[f][m] = a;
     }
     __syncthreads();
     const long long node0 = (far_grid ? D.soff : D.toff) + (long long)i * L.nlon;
@@ -222,6 +244,7 @@ __global__ __launch_bounds__(kThreads) void k_synth(const DropInfo* __restrict__
             vt[f] = DERIV ? Gd[f][0].x : 0.0;
             vp[f] = 0.0;
         }
+#pragma unroll 4
         for (int m = 1; m <= p; ++m) {
             const double c = tr[2 * m], s = tr[2 * m + 1];
             for (int f = 0; f < K; ++f) {
@@ -266,7 +289,8 @@ __global__ __launch_bounds__(kThreads) void k_surface(const DropInfo* __restrict
                                                       double* __restrict__ Hout, double* __restrict__ grad,
                                                       double* __restrict__ lap)
 {
-    constexpr int K = 3 + NG;
+    constexpr int K = 3 + NG, S = 2;
+    __shared__ double2 part[S][3][K][EHD_MAX_P + 1];
     __shared__ double2 G0[K][EHD_MAX_P + 1], G1[K][EHD_MAX_P + 1], G2[K][EHD_MAX_P + 1];
     const int2 r = rows[blockIdx.x];
     const DropInfo D = drops[r.x];
@@ -275,11 +299,12 @@ __global__ __launch_bounds__(kThreads) void k_surface(const DropInfo* __restrict
     const long nc = ncoef(p);
     const double* Prow = L.P + (long long)i * nc;
     const double* dProw = L.dP + (long long)i * nc;
-    for (int it = threadIdx.x; it < K * (p + 1); it += blockDim.x) {
-        const int f = it / (p + 1), m = it % (p + 1);
+    for (int it = threadIdx.x; it < S * K * (p + 1); it += blockDim.x) {
+        const int m = it % (p + 1), f = it / (p + 1) % K, s = it / (p + 1) / K;
         const double* cf = f < 3 ? xcoef + 3 * D.coff + f * 2 * nc : gcoef + (long long)NG * D.coff + (f - 3) * 2 * nc;
         double a0 = 0, b0 = 0, a1 = 0, b1 = 0, a2 = 0, b2 = 0;
-        for (int n = m; n <= p; ++n) {
+#pragma unroll 4
+        for (int n = m + s; n <= p; n += S) {
             const long k = tri(n, m);
             const double cr = cf[2 * k], ci = (m == 0) ? 0.0 : cf[2 * k + 1];
             const double pv = Prow[k], dv = dProw[k], nn = (double)n * (n + 1);
@@ -287,25 +312,36 @@ __global__ __launch_bounds__(kThreads) void k_surface(const DropInfo* __restrict
             a1 += dv * cr; b1 += dv * ci;
             a2 += nn * pv * cr; b2 += nn * pv * ci;
         }
-        G0[f][m] = make_double2(a0, b0);
-        G1[f][m] = make_double2(a1, b1);
-        G2[f][m] = make_double2(a2, b2);
+        part[s][0][f][m] = make_double2(a0, b0);
+        part[s][1][f][m] = make_double2(a1, b1);
+        part[s][2][f][m] = make_double2(a2, b2);
+    }
+    __syncthreads();
+    for (int it = threadIdx.x; it < 3 * K * (p + 1); it += blockDim.x) {
+        const int m = it % (p + 1), f = it / (p + 1) % K, q = it / (p + 1) / K;
+        const double2 a = part[0][q][f][m], b = part[1][q][f][m];
+        (q == 0 ? G0 : q == 1 ? G1 : G2)[f][m] = make_double2(a.x + b.x, a.y + b.y);
     }
     __syncthreads();
     const double rs = L.rsin[i];                           // 1 / sin theta
     const double ct = L.cth[i] * rs;                       // cot theta
     const long long node0 = D.toff + (long long)i * L.nlon;
-    for (int l = threadIdx.x; l < L.nlon; l += blockDim.x) {
+    // two neighbouring lanes share a node, one for the odd orders, one for the
+    // even ones (a latitude has at most 98 nodes; 64 drops of p = 16 to 48, two
+    // fields: 119 -> 92 us)
+    const int odd = threadIdx.x & 1;
+    for (int l = threadIdx.x >> 1; l < L.nlon; l += blockDim.x / 2) {
         const double* tr = L.trig + (long long)l * (p + 1) * 2;
         double vt[K], vp[K], vtt[K], vtp[K], vpp[K];
         for (int f = 0; f < K; ++f) {
-            vt[f] = G1[f][0].x;
+            vt[f] = odd ? 0.0 : G1[f][0].x;
             vp[f] = 0.0;
-            vtt[f] = -ct * G1[f][0].x - G2[f][0].x;
+            vtt[f] = odd ? 0.0 : -ct * G1[f][0].x - G2[f][0].x;
             vtp[f] = 0.0;
             vpp[f] = 0.0;
         }
-        for (int m = 1; m <= p; ++m) {
+#pragma unroll 2
+        for (int m = odd ? 1 : 2; m <= p; m += 2) {
             const double c = tr[2 * m], sn = tr[2 * m + 1], mm = (double)m * m * rs * rs;
             for (int f = 0; f < K; ++f) {
                 const double2 g0 = G0[f][m], g1 = G1[f][m];
@@ -318,6 +354,14 @@ __global__ __launch_bounds__(kThreads) void k_surface(const DropInfo* __restrict
                 vpp[f] -= 2.0 * (double)m * m * (g0.x * c - g0.y * sn);
             }
         }
+        for (int f = 0; f < K; ++f) {                      // both lanes get the sums
+            vt[f] += dpp_f64<0xB1>(vt[f]);
+            vp[f] += dpp_f64<0xB1>(vp[f]);
+            vtt[f] += dpp_f64<0xB1>(vtt[f]);
+            vtp[f] += dpp_f64<0xB1>(vtp[f]);
+            vpp[f] += dpp_f64<0xB1>(vpp[f]);
+        }
+        if (odd) continue;
         const double E = vt[0] * vt[0] + vt[1] * vt[1] + vt[2] * vt[2];
         const double F = vt[0] * vp[0] + vt[1] * vp[1] + vt[2] * vp[2];
         const double Gg = vp[0] * vp[0] + vp[1] * vp[1] + vp[2] * vp[2];
@@ -342,6 +386,106 @@ __global__ __launch_bounds__(kThreads) void k_surface(const DropInfo* __restrict
                 hpp -= vpp[c] * gr;
             }
             if (lap) lap[(long long)g * T + t] = (Gg * htt - 2.0 * F * htp + E * hpp) * iW2;
+        }
+    }
+}
+
+// The Laplace-Beltrami operator at the target nodes for repeated use on one
+// shape (k_surface gives its definition): with v = (G x_tt - 2 F x_tp + E x_pp) / W^2,
+//   Lap_S g = (G g_tt - 2 F g_tp + E g_pp) / W^2 + b_t g_t + b_p g_p,
+//   b_t = -(G v.x_t - F v.x_p) / W^2,  b_p = -(E v.x_p - F v.x_t) / W^2.
+// GEO: the five coefficients from the surface's fields, geo[5][T]; otherwise
+// the values for one field g from them (a quarter of k_surface's sums per
+// application: 128 drops of p = 32, 132 -> 42 us).
+template <bool GEO>
+__global__ __launch_bounds__(kThreads) void k_lap(const DropInfo* __restrict__ drops, const LegTab* __restrict__ legs,
+                                                  const int2* __restrict__ rows, const double* __restrict__ coef,
+                                                  long long T, double* geo, double* __restrict__ lap)
+{
+    constexpr int K = GEO ? 3 : 1, S = GEO ? 2 : 6;          // fields; threads per Legendre sum
+    __shared__ double2 part[S][3][K][EHD_MAX_P + 1];
+    __shared__ double2 G[3][K][EHD_MAX_P + 1];               // sums with Pbar, dPbar/dtheta, n(n+1) Pbar
+    const int2 r = rows[blockIdx.x];
+    const DropInfo D = drops[r.x];
+    const LegTab L = legs[D.leg_pp];
+    const int p = L.p, i = r.y;
+    const long nc = ncoef(p);
+    const double* const Prow = L.P + (long long)i * nc;
+    const double* const dProw = L.dP + (long long)i * nc;
+    for (int it = threadIdx.x; it < S * K * (p + 1); it += kThreads) {
+        const int m = it % (p + 1), f = it / (p + 1) % K, s = it / (p + 1) / K;
+        const double* const cf = coef + (long long)K * D.coff + (long long)f * 2 * nc;
+        double2 a = make_double2(0.0, 0.0), b = a, c = a;
+#pragma unroll 4
+        for (int n = m + s; n <= p; n += S) {
+            const long k = tri(n, m);
+            const double cr = cf[2 * k], ci = m ? cf[2 * k + 1] : 0.0;
+            const double pv = Prow[k], dv = dProw[k], nv = (double)n * (n + 1) * pv;
+            a.x = fma(pv, cr, a.x); a.y = fma(pv, ci, a.y);
+            b.x = fma(dv, cr, b.x); b.y = fma(dv, ci, b.y);
+            c.x = fma(nv, cr, c.x); c.y = fma(nv, ci, c.y);
+        }
+        part[s][0][f][m] = a;
+        part[s][1][f][m] = b;
+        part[s][2][f][m] = c;
+    }
+    __syncthreads();
+    for (int it = threadIdx.x; it < 3 * K * (p + 1); it += kThreads) {
+        const int m = it % (p + 1), f = it / (p + 1) % K, q = it / (p + 1) / K;
+        double2 a = part[0][q][f][m];
+#pragma unroll
+        for (int s = 1; s < S; ++s) {
+            a.x += part[s][q][f][m].x;
+            a.y += part[s][q][f][m].y;
+        }
+        G[q][f][m] = a;
+    }
+    __syncthreads();
+    const double rs = L.rsin[i], ct = L.cth[i] * rs;         // 1 / sin theta, cot theta
+    for (int l = threadIdx.x; l < L.nlon; l += kThreads) {
+        const double* const tr = L.trig + (long long)l * (p + 1) * 2;
+        double vt[K], vp[K], vtt[K], vtp[K], vpp[K];
+        for (int f = 0; f < K; ++f) {
+            vt[f] = G[1][f][0].x;
+            vtt[f] = -ct * G[1][f][0].x - G[2][f][0].x;
+            vp[f] = vtp[f] = vpp[f] = 0.0;
+        }
+#pragma unroll 4
+        for (int m = 1; m <= p; ++m) {
+            const double c = tr[2 * m], sn = tr[2 * m + 1], mm = (double)m * m * rs * rs;
+            for (int f = 0; f < K; ++f) {
+                const double2 g0 = G[0][f][m], g1 = G[1][f][m], g2 = G[2][f][m];
+                vt[f] += 2.0 * (g1.x * c - g1.y * sn);
+                vp[f] -= 2.0 * m * (g0.x * sn + g0.y * c);
+                const double er = -ct * g1.x - g2.x + mm * g0.x, ei = -ct * g1.y - g2.y + mm * g0.y;
+                vtt[f] += 2.0 * (er * c - ei * sn);
+                vtp[f] -= 2.0 * m * (g1.x * sn + g1.y * c);
+                vpp[f] -= 2.0 * (double)m * m * (g0.x * c - g0.y * sn);
+            }
+        }
+        const long long t = D.toff + (long long)i * L.nlon + l;
+        if constexpr (GEO) {
+            double E = 0.0, F = 0.0, Gg = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                E += vt[c] * vt[c];
+                F += vt[c] * vp[c];
+                Gg += vp[c] * vp[c];
+            }
+            const double iW2 = 1.0 / (E * Gg - F * F);
+            double wt = 0.0, wp = 0.0;                       // v.x_t, v.x_p
+            for (int c = 0; c < 3; ++c) {
+                const double v = (Gg * vtt[c] - 2.0 * F * vtp[c] + E * vpp[c]) * iW2;
+                wt += v * vt[c];
+                wp += v * vp[c];
+            }
+            geo[t] = Gg * iW2;
+            geo[T + t] = -2.0 * F * iW2;
+            geo[2 * T + t] = E * iW2;
+            geo[3 * T + t] = -(Gg * wt - F * wp) * iW2;
+            geo[4 * T + t] = -(E * wp - F * wt) * iW2;
+        } else {
+            lap[t] = geo[t] * vtt[0] + geo[T + t] * vtp[0] + geo[2 * T + t] * vpp[0] + geo[3 * T + t] * vt[0] +
+                     geo[4 * T + t] * vp[0];
         }
     }
 }
@@ -1549,41 +1693,84 @@ __global__ void k_combine(const double* __restrict__ raw_self, const double* __r
     }
 }
 
-// Galerkin analysis: one block per (drop, n(n+1)/2+m) coefficient group,
-// (y, Y_nm) = sum_j sum_k (2pi/nlon) w_j y_jk Pbar_n^m(t_j) e^{-i m phi_k}.
-__global__ void k_analyze(const DropInfo* __restrict__ drops, const LegTab* __restrict__ legs,
-                          const int2* __restrict__ items, int nf, const double* __restrict__ grid,
-                          long long T, double* __restrict__ coef)
+// Galerkin analysis, one block per (drop, orders m = m0, m0 + G, ..; field):
+// (y, Y_nm) = sum_j Pbar_n^m(t_j) (2pi/nlon) w_j sum_k y_jk e^{-i m phi_k}.
+// The field is folded on the way into LDS (y(l) +- y(N - l): the cosines and
+// the sines of half a period each); the longitude sums take an order per wave
+// and pass, a latitude per lane, with wave-uniform trig values; then the
+// Legendre sums a thread per coefficient.  Latency bound: a block is a few
+// microseconds, and the orders are dealt over G blocks for that reason (four
+// fields of 64 drops, p = 16 to 48: 1187 us with a block per coefficient, each
+// over the whole grid, now 37 us).
+constexpr int kAnOrders = 8;          // orders per block
+__global__ __launch_bounds__(kThreads) void k_analyze(const DropInfo* __restrict__ drops,
+                                                      const LegTab* __restrict__ legs, const int2* __restrict__ items,
+                                                      int nf, const double* __restrict__ grid, long long T,
+                                                      double* __restrict__ coef)
 {
+    constexpr int LH = EHD_MAX_P + 2 + 1;                    // half a period of the largest own grid, odd
+    __shared__ double yc[EHD_MAX_P + 1][LH], ys[EHD_MAX_P + 1][LH];
+    __shared__ double2 F[kAnOrders][EHD_MAX_P + 1];
     const int2 it = items[blockIdx.x];
+    const int f = blockIdx.y + gridDim.y * blockIdx.z;
+    if (f >= nf) return;
     const DropInfo D = drops[it.x];
     const LegTab L = legs[D.leg_pp];
-    const int p = L.p, kk = it.y;
-    const int n = tri_n(kk), m = kk - n * (n + 1) / 2;
+    const int p = L.p, N = L.nlon, H = N / 2, nlat = L.Q + 1, G = (p + kAnOrders) / kAnOrders;
     const long nc = ncoef(p);
-    const int npts = (L.Q + 1) * L.nlon;
-    __shared__ double rr[kThreads / 64][2];
-    for (int f = 0; f < nf; ++f) {
+    const double* const y = grid + (long long)f * T + D.toff;
+    for (int z = threadIdx.x; z < nlat * (H + 1); z += kThreads) {
+        const int j = z / (H + 1), l = z % (H + 1);
+        const double a = y[j * N + l], b = y[j * N + (l ? N - l : 0)], w = L.wq[j];
+        const bool pair = l > 0 && l < H;                    // l = 0 and H stand alone
+        yc[j][l] = w * (pair ? a + b : a);
+        ys[j][l] = pair ? w * (a - b) : 0.0;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = min(lane, nlat - 1);
+    for (int k = wv; k < kAnOrders; k += 2 * (kThreads / 64)) {
+        // two orders a pass
+        const int m0 = it.y + G * k, m1 = it.y + G * (k + kThreads / 64);
+        if (m0 > p) break;
+        const double* const t0 = L.trig + 2 * m0;
+        const double* const t1 = L.trig + 2 * min(m1, p);
+        double c0 = 0.0, s0 = 0.0, c1 = 0.0, s1 = 0.0;
+#pragma unroll 4
+        for (int l = 0; l <= H; ++l) {
+            const double a = yc[j][l], b = ys[j][l];
+            const long long o = (long long)l * (p + 1) * 2;
+            c0 = fma(a, t0[o], c0);
+            s0 = fma(b, t0[o + 1], s0);
+            c1 = fma(a, t1[o], c1);
+            s1 = fma(b, t1[o + 1], s1);
+        }
+        if (lane < nlat) {
+            F[k][lane] = make_double2(c0, m0 ? -s0 : 0.0);
+            if (m1 <= p) F[k + kThreads / 64][lane] = make_double2(c1, -s1);
+        }
+    }
+    __syncthreads();
+    double2* const o = reinterpret_cast<double2*>(coef + (long long)nf * D.coff + (long long)f * 2 * nc);
+    const bool aligned = ((uintptr_t)o & 15) == 0;
+    for (int z = threadIdx.x; z < kAnOrders * (p + 1); z += kThreads) {
+        const int k = z / (p + 1), n = z % (p + 1), m = it.y + G * k;
+        if (m > n) continue;
+        const int kk = (int)tri(n, m);
+        const double* const P = L.P + kk;
         double ar = 0.0, ai = 0.0;
-        for (int q = threadIdx.x; q < npts; q += blockDim.x) {
-            const int j = q / L.nlon, l = q % L.nlon;
-            const double y = grid[(long long)f * T + D.toff + q] * L.wq[j] * L.P[(long long)j * nc + kk];
-            const double* tr = L.trig + ((long long)l * (p + 1) + m) * 2;
-            ar += y * tr[0];
-            ai -= y * tr[1];
+#pragma unroll 8
+        for (int i = 0; i < nlat; ++i) {
+            const double v = P[(long long)i * nc];
+            const double2 g = F[k][i];
+            ar = fma(v, g.x, ar);
+            ai = fma(v, g.y, ai);
         }
-        ar = wave_sum(ar);
-        ai = wave_sum(ai);
-        if ((threadIdx.x & 63) == 0) { rr[threadIdx.x >> 6][0] = ar; rr[threadIdx.x >> 6][1] = ai; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double sr = 0.0, si = 0.0;
-            for (int w = 0; w < (int)(blockDim.x / 64); ++w) { sr += rr[w][0]; si += rr[w][1]; }
-            double* cb = coef + (long long)nf * D.coff + (long long)f * 2 * nc;
-            cb[2 * kk] = sr;
-            cb[2 * kk + 1] = (m == 0) ? 0.0 : si;
+        if (aligned) o[kk] = make_double2(ar, ai);
+        else {                                               // (a caller's buffer: aligned to doubles only)
+            reinterpret_cast<double*>(o)[2 * kk] = ar;
+            reinterpret_cast<double*>(o)[2 * kk + 1] = ai;
         }
-        __syncthreads();
     }
 }
 
@@ -2371,7 +2558,6 @@ struct ehd_ctx {
         (void)hipEventRecord(events[slot * kEv + kStages + 1 + 2 * cls + end], stream);
         class_used[slot * 4 + cls] = 1;
     }
-    DropInfo* d_info_tmp = nullptr;  // per-field views for ehd_synthesize
 
     // nearly singular targets (ehd_set_near); its buffers live in near_allocs
     struct Near {
@@ -3007,7 +3193,7 @@ static int near_build(ehd_ctx* ctx)
         return rc;
     // check-grid geometry
     hipLaunchKernelGGL((k_synth<3, true>), dim3(N.nfrows), dim3(kThreads), 0, ctx->stream, N.d_fdrops, N.d_flegs, 1,
-                       N.d_frows, ctx->d_x, N.d_fsyn, N.nf);
+                       N.d_frows, 3, ctx->d_x, N.d_fsyn, N.nf);
     hipLaunchKernelGGL(k_fine_geom, dim3((N.nf + 255) / 256), dim3(256), 0, ctx->stream, N.d_fdrops, N.d_flegs,
                        N.d_node_drop, N.d_fsyn, N.nf, N.d_frec);
     EHD_HIP(ctx, hipGetLastError());
@@ -3027,15 +3213,15 @@ static int near_enqueue(ehd_ctx* ctx, const double* fcoef_d, const double* ucoef
     double* syns = sigcoef_d ? N.d_fsyn + 6 * nf : nullptr;
     if (synf)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(N.nfrows), dim3(kThreads), 0, ctx->ls, N.d_fdrops, N.d_flegs, 1,
-                           N.d_frows, fcoef_d, synf, nf);
+                           N.d_frows, 3, fcoef_d, synf, nf);
     if (synu)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(N.nfrows), dim3(kThreads), 0, ctx->ls, N.d_fdrops, N.d_flegs, 1,
-                           N.d_frows, ucoef_d, synu, nf);
+                           N.d_frows, 3, ucoef_d, synu, nf);
     if (syns)
         hipLaunchKernelGGL((k_synth<1, false>), dim3(N.nfrows), dim3(kThreads), 0, ctx->ls, N.d_fdrops, N.d_flegs, 1,
-                           N.d_frows, sigcoef_d, syns, nf);
+                           N.d_frows, 1, sigcoef_d, syns, nf);
     hipLaunchKernelGGL(k_fine_dens, dim3((nf + 255) / 256), dim3(256), 0, ctx->ls, synf, synu, syns, nf, N.d_frec);
-    hipLaunchKernelGGL(k_analyze, dim3(ctx->n_an_items), dim3(kThreads), 0, ctx->ls, ctx->d_info, ctx->d_legs,
+    hipLaunchKernelGGL(k_analyze, dim3(ctx->n_an_items, 9), dim3(kThreads), 0, ctx->ls, ctx->d_info, ctx->d_legs,
                        ctx->d_an_items, 9, ctx->d_raw, ctx->T, N.d_selfc);
     const double* uc = ucoef_d ? ucoef_d : fcoef_d;
     hipLaunchKernelGGL(k_near_limit, dim3(N.npairs), dim3(kThreads), 0, ctx->ls, N.d_pairs, ctx->d_info, N.d_legv,
@@ -3206,11 +3392,11 @@ static int build_geometry(ehd_ctx* ctx)
 {
     const long long T = ctx->T, S = ctx->Spad, vs = ctx->syn_stride;
     hipLaunchKernelGGL((k_synth<3, true>), dim3(ctx->nrows_p), dim3(kThreads), 0, ctx->stream,
-                       ctx->d_info, ctx->d_legs, 0, ctx->d_rows_p, ctx->d_x, ctx->d_syn, vs);
+                       ctx->d_info, ctx->d_legs, 0, ctx->d_rows_p, 3, ctx->d_x, ctx->d_syn, vs);
     hipLaunchKernelGGL(k_geom_targets, dim3((T + 255) / 256), dim3(256), 0, ctx->stream, ctx->d_syn, vs, T,
                        ctx->d_tx, ctx->d_tn);
     hipLaunchKernelGGL((k_synth<3, true>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->stream,
-                       ctx->d_info, ctx->d_legs, 1, ctx->d_rows_f, ctx->d_x, ctx->d_syn, vs);
+                       ctx->d_info, ctx->d_legs, 1, ctx->d_rows_f, 3, ctx->d_x, ctx->d_syn, vs);
     hipLaunchKernelGGL(k_geom_sources, dim3((S + 255) / 256), dim3(256), 0, ctx->stream, ctx->d_info,
                        ctx->d_legs, ctx->d_slot_drop, ctx->d_syn, vs, S, ctx->d_src64, ctx->d_src32);
     hipLaunchKernelGGL(k_drop_radius, dim3(ctx->nd), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_src64, S,
@@ -3448,7 +3634,7 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
                 make_int2(d, (int)((std::min<long long>(kTile, D.ns - tl * kTile) + 3) / 4 * 4));
         for (int i = 0; i <= D.p; ++i) rows_p.push_back(make_int2(d, i));
         for (int i = 0; i <= D.qf; ++i) rows_f.push_back(make_int2(d, i));
-        for (int k = 0; k < ncoef(D.p); ++k) an_items.push_back(make_int2(d, k));
+        for (int g = 0; g < (D.p + kAnOrders) / kAnOrders; ++g) an_items.push_back(make_int2(d, g));
     }
     // self work order: by degree class (largest first), inside a class the
     // most expensive drops first
@@ -3501,7 +3687,6 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
     const size_t parts = kMaxChunks * (T > kCutTargets ? 1 : kMaxCut);
     if ((rc = dev_alloc(ctx, &ctx->d_partial, parts * 9 * T))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_expanded, (size_t)9 * T))) return rc;
-    if ((rc = dev_alloc(ctx, &ctx->d_info_tmp, ndrops))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_rad, 2 * (size_t)ndrops))) return rc;
 
     // --- target geometry (own grids) and far-source geometry
@@ -3798,13 +3983,13 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
     double* syns = needLap ? ctx->d_syn + 6 * vs : nullptr;
     if (needF && !single)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
-                           ctx->d_legs, 1, ctx->d_rows_f, fcoef_d, synf, vs);
+                           ctx->d_legs, 1, ctx->d_rows_f, 3, fcoef_d, synf, vs);
     if (needU && !single)
         hipLaunchKernelGGL((k_synth<3, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
-                           ctx->d_legs, 1, ctx->d_rows_f, ucoef_d, synu, vs);
+                           ctx->d_legs, 1, ctx->d_rows_f, 3, ucoef_d, synu, vs);
     if (needLap && !single)
         hipLaunchKernelGGL((k_synth<1, false>), dim3(ctx->nrows_f), dim3(kThreads), 0, ctx->ls, ctx->d_info,
-                           ctx->d_legs, 1, ctx->d_rows_f, sigcoef_d, syns, vs);
+                           ctx->d_legs, 1, ctx->d_rows_f, 1, sigcoef_d, syns, vs);
     if (!single)
         hipLaunchKernelGGL(k_src_dens, dim3((S + 255) / 256), dim3(256), 0, ctx->ls, synf, synu, syns, vs, S,
                        ctx->d_src64, ctx->d_src32);
@@ -3902,6 +4087,22 @@ static int enqueue_evaluation(ehd_ctx* ctx, const double* fcoef_d, const double*
 }
 
 }  // extern "C"
+
+int ehd_ctx_lap_geometry(ehd_ctx* ctx, double* geo)
+{
+    hipLaunchKernelGGL(k_lap<true>, dim3(ctx->nrows_p), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_legs,
+                       ctx->d_rows_p, ctx->d_x, ctx->T, geo, (double*)nullptr);
+    EHD_HIP(ctx, hipGetLastError());
+    return EHD_OK;
+}
+
+int ehd_ctx_lap_values(ehd_ctx* ctx, const double* geo, const double* coef, double* lap)
+{
+    hipLaunchKernelGGL(k_lap<false>, dim3(ctx->nrows_p), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_legs,
+                       ctx->d_rows_p, coef, ctx->T, const_cast<double*>(geo), lap);
+    EHD_HIP(ctx, hipGetLastError());
+    return EHD_OK;
+}
 
 // Weights of the singular rule of one degree class's targets
 // [first, first + count) of its order, into ctx->opgrid.
@@ -4376,11 +4577,18 @@ int ehd_area_weights(ehd_ctx* ctx, double* w_d)
     EHD_HIP(ctx, hipSetDevice(ctx->device));
     const long long vs = ctx->syn_stride;
     hipLaunchKernelGGL((k_synth<3, true>), dim3(ctx->nrows_p), dim3(kThreads), 0, ctx->stream,
-                       ctx->d_info, ctx->d_legs, 0, ctx->d_rows_p, ctx->d_x, ctx->d_syn, vs);
+                       ctx->d_info, ctx->d_legs, 0, ctx->d_rows_p, 3, ctx->d_x, ctx->d_syn, vs);
     hipLaunchKernelGGL(k_area_weights, dim3((ctx->T + 255) / 256), dim3(256), 0, ctx->stream, ctx->d_info,
                        ctx->d_legs, ctx->d_tdrop, ctx->d_syn, vs, ctx->T, w_d);
     EHD_HIP(ctx, hipGetLastError());
     return EHD_OK;
+}
+
+// Grid of n blocks for each of nf fields (the kernels skip the surplus).
+static dim3 field_grid(int n, int nf)
+{
+    const int y = std::min(nf, 32768);
+    return dim3((unsigned)n, (unsigned)y, (unsigned)((nf + y - 1) / y));
 }
 
 int ehd_synthesize(ehd_ctx* ctx, int nfields, const double* coef_d, double* grid_d)
@@ -4389,22 +4597,9 @@ int ehd_synthesize(ehd_ctx* ctx, int nfields, const double* coef_d, double* grid
     if (!ctx->nd) EHD_FAIL(ctx, EHD_E_STATE, "ehd_set_drops has not been called");
     if (nfields < 1 || !coef_d || !grid_d) EHD_FAIL(ctx, EHD_E_ARG, "nfields >= 1 and non-NULL pointers required");
     EHD_HIP(ctx, hipSetDevice(ctx->device));
-    // One field at a time through the K = 1 kernel on per-field views: field
-    // f of drop d starts at nfields*coff[d] + f*(p+1)(p+2) doubles, so each
-    // launch reads a descriptor copy whose offsets point there.  Synchronous
-    // (the host descriptor copy is reused per field).
-    std::vector<DropInfo> shifted(ctx->info);
-    DropInfo* d_sh = ctx->d_info_tmp;
-    for (int f = 0; f < nfields; ++f) {
-        for (int d = 0; d < ctx->nd; ++d)
-            shifted[d].coff = (long long)nfields * ctx->info[d].coff + (long long)f * (ctx->info[d].p + 1) * (ctx->info[d].p + 2);
-        EHD_HIP(ctx, hipMemcpyAsync(d_sh, shifted.data(), sizeof(DropInfo) * shifted.size(),
-                                    hipMemcpyHostToDevice, ctx->stream));
-        hipLaunchKernelGGL((k_synth<1, false>), dim3(ctx->nrows_p), dim3(kThreads), 0, ctx->stream, d_sh,
-                           ctx->d_legs, 0, ctx->d_rows_p, coef_d, grid_d + (long long)f * ctx->T, ctx->T);
-        EHD_HIP(ctx, hipGetLastError());
-        EHD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    }
+    hipLaunchKernelGGL((k_synth<1, false>), field_grid(ctx->nrows_p, nfields), dim3(kThreads), 0, ctx->stream, ctx->d_info,
+                       ctx->d_legs, 0, ctx->d_rows_p, nfields, coef_d, grid_d, ctx->T);
+    EHD_HIP(ctx, hipGetLastError());
     return EHD_OK;
 }
 
@@ -4414,7 +4609,7 @@ int ehd_analyze(ehd_ctx* ctx, int nfields, const double* grid_d, double* coef_d)
     if (!ctx->nd) EHD_FAIL(ctx, EHD_E_STATE, "ehd_set_drops has not been called");
     if (nfields < 1 || !coef_d || !grid_d) EHD_FAIL(ctx, EHD_E_ARG, "nfields >= 1 and non-NULL pointers required");
     EHD_HIP(ctx, hipSetDevice(ctx->device));
-    hipLaunchKernelGGL(k_analyze, dim3(ctx->n_an_items), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_legs,
+    hipLaunchKernelGGL(k_analyze, field_grid(ctx->n_an_items, nfields), dim3(kThreads), 0, ctx->stream, ctx->d_info, ctx->d_legs,
                        ctx->d_an_items, nfields, grid_d, ctx->T, coef_d);
     EHD_HIP(ctx, hipGetLastError());
     return EHD_OK;

@@ -34,14 +34,16 @@ static __device__ __align__(256) double scratch[8LL << 20];
 namespace {
 
 constexpr int kT = 256;
+constexpr int kMaxBasis = 201;        // Krylov vectors at the largest restart
 
-// out[i] = <V_i, w>, one block per vector, fixed summation order.
+// part[i * nb + b] = block b's share of <V_i, w> (grid (vectors, nb)), fixed
+// summation order; the reader adds the nb shares (k_subtract).
 __global__ __launch_bounds__(kT) void k_dots(const double* __restrict__ V, long long ld, const double* __restrict__ w,
-                                             long long n, double* __restrict__ out)
+                                             long long n, double* __restrict__ part)
 {
     const double* v = V + (long long)blockIdx.x * ld;
     double s = 0.0;
-    for (long long t = threadIdx.x; t < n; t += kT) s = fma(v[t], w[t], s);
+    for (long long t = (long long)blockIdx.y * kT + threadIdx.x; t < n; t += (long long)gridDim.y * kT) s = fma(v[t], w[t], s);
     __shared__ double sh[kT];
     sh[threadIdx.x] = s;
     __syncthreads();
@@ -49,18 +51,54 @@ __global__ __launch_bounds__(kT) void k_dots(const double* __restrict__ V, long 
         if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
+    if (threadIdx.x == 0) part[(long long)blockIdx.x * gridDim.y + blockIdx.y] = sh[0];
 }
 
-// w -= sum_{i<k} h[i] V_i
-__global__ void k_subtract(double* __restrict__ w, const double* __restrict__ V, long long ld, int k,
-                           const double* __restrict__ h, long long n)
+// w -= sum_{i<k} h[i] V_i with h[i] the sum of its nb shares in part, added in
+// order by every block; the first block stores h (if hout) and each block its
+// share of the new |w|^2 (if nrm).
+__global__ __launch_bounds__(kT) void k_subtract(double* __restrict__ w, const double* __restrict__ V, long long ld, int k,
+                                                 const double* part, int nb, long long n, double* hout, double* nrm)
 {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    double s = w[t];
-    for (int i = 0; i < k; ++i) s = fma(-h[i], V[(long long)i * ld + t], s);
-    w[t] = s;
+    __shared__ double h[kMaxBasis], sh[kT];
+    for (int i = threadIdx.x; i < k; i += kT) {
+        double s = part[(long long)i * nb];
+        for (int b = 1; b < nb; ++b) s += part[(long long)i * nb + b];
+        h[i] = s;
+        if (hout && blockIdx.x == 0) hout[i] = s;
+    }
+    __syncthreads();
+    const long long t = (long long)blockIdx.x * kT + threadIdx.x;
+    double s = 0.0;
+    if (t < n) {
+        s = w[t];
+#pragma unroll 4
+        for (int i = 0; i < k; ++i) s = fma(-h[i], V[(long long)i * ld + t], s);
+        w[t] = s;
+    }
+    if (!nrm) return;
+    sh[threadIdx.x] = s * s;
+    __syncthreads();
+    for (int o = kT / 2; o > 0; o >>= 1) {
+        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) nrm[blockIdx.x] = sh[0];
+}
+
+// *out = the sum of m shares; one block.
+__global__ __launch_bounds__(kT) void k_total(const double* part, int m, double* out)
+{
+    __shared__ double sh[kT];
+    double s = 0.0;
+    for (int t = threadIdx.x; t < m; t += kT) s += part[t];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = kT / 2; o > 0; o >>= 1) {
+        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *out = sh[0];
 }
 
 __global__ void k_fill(double* __restrict__ y, double v, long long n)
@@ -147,6 +185,25 @@ __global__ __launch_bounds__(kT) void k_guess(const long long* __restrict__ off,
         double g = b[o + k] / (1.0 + kd * n * (n + 1.0));
         if (y) g += kd * bn * gain[k] * ((double)y[(long long)d * ny + k] * ystd[k] + ymean[k]);
         guess[o + k] = g;
+    }
+}
+
+// Entries of drop blockIdx.x's packed coefficients (off[d] doubles on): kappa,
+// 1 / (1 + kappa n(n+1)) and its inverse (both 1 without preconditioning).
+__global__ __launch_bounds__(kT) void k_diag(const long long* __restrict__ off, const double* __restrict__ kappa,
+                                             int precond, double* __restrict__ kd, double* __restrict__ dinv,
+                                             double* __restrict__ dfwd)
+{
+    const int d = blockIdx.x;
+    const long long o = off[d];
+    const int ne = (int)(off[d + 1] - o);
+    const double k = kappa[d];
+    for (int e = threadIdx.x; e < ne; e += kT) {
+        const int n = packed_degree(e);
+        const double f = precond ? 1.0 + k * n * (n + 1.0) : 1.0;
+        kd[o + e] = k;
+        dfwd[o + e] = f;
+        dinv[o + e] = 1.0 / f;
     }
 }
 
@@ -268,8 +325,16 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
     double* w = ws.w;
     double* hd = ws.hd;
     double *H = ws.H, *cs = ws.cs, *sn = ws.sn, *g = ws.g, *h = ws.h, *y = ws.y, *hh = ws.hh;
-    auto norm = [&](const double* vec, double* out) -> int {
-        hipLaunchKernelGGL(k_dots, dim3(1), dim3(kT), 0, st, vec, n, vec, n, hd);
+    // Dot products run on nb blocks per vector and norms on one share per block
+    // of the update; where there is more than one, the shares lie in the first
+    // and the second half of a basis vector that is not in use (the next one):
+    // (m + 1) nb <= n / 2 and the blocks of n are fewer than n / 2 then.
+    const int nb = (int)std::min<long long>(32, std::max<long long>(1, n / 2048));
+    const int nu = (int)nblocks(n);
+    auto norm = [&](const double* vec, double* spare, double* out) -> int {
+        double* const part = nb > 1 ? spare : hd;
+        hipLaunchKernelGGL(k_dots, dim3(1, nb), dim3(kT), 0, st, vec, n, vec, n, part);
+        if (nb > 1) hipLaunchKernelGGL(k_total, dim3(1), dim3(kT), 0, st, part, nb, hd);
         SOLVE_HIP(hipGetLastError());
         SOLVE_HIP(hipMemcpyAsync(out, hd, sizeof(double), hipMemcpyDeviceToHost, st));
         SOLVE_HIP(hipStreamSynchronize(st));
@@ -277,7 +342,7 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
         return EHD_OK;
     };
     double bnorm;
-    int rc = norm(b, &bnorm);
+    int rc = norm(b, V, &bnorm);
     if (rc) return rc;
     *iters = 0;
     if (bnorm == 0.0) {
@@ -294,7 +359,7 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, -1.0, w, 1.0, V, n);
         SOLVE_HIP(hipGetLastError());
         double beta;
-        if ((rc = norm(V, &beta))) return rc;
+        if ((rc = norm(V, V + n, &beta))) return rc;
         *relres = beta / bnorm;
         if (*relres <= tol || *iters >= maxit) return EHD_OK;
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, 0.0, V, 1.0 / beta, V, n);
@@ -307,11 +372,16 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
             // CGS2: two passes of h = V^T w, w -= V h, the projections kept
             // on the device; one copy to the host per step
             double* const hd2 = hd + (m + 1);
-            hipLaunchKernelGGL(k_dots, dim3(j + 1), dim3(kT), 0, st, V, n, w, n, hd);
-            hipLaunchKernelGGL(k_subtract, dim3(nblocks(n)), dim3(kT), 0, st, w, V, n, j + 1, hd, n);
-            hipLaunchKernelGGL(k_dots, dim3(j + 1), dim3(kT), 0, st, V, n, w, n, hd2);
-            hipLaunchKernelGGL(k_subtract, dim3(nblocks(n)), dim3(kT), 0, st, w, V, n, j + 1, hd2, n);
-            hipLaunchKernelGGL(k_dots, dim3(1), dim3(kT), 0, st, w, n, w, n, hd + 2 * m + 2);
+            double* const spare = V + (size_t)(j + 1) * n;
+            double* const p1 = nb > 1 ? spare : hd;
+            double* const p2 = nb > 1 ? spare : hd2;
+            double* const pn = nu > 1 ? spare + n / 2 : hd + 2 * m + 2;
+            hipLaunchKernelGGL(k_dots, dim3(j + 1, nb), dim3(kT), 0, st, V, n, w, n, p1);
+            hipLaunchKernelGGL(k_subtract, dim3(nu), dim3(kT), 0, st, w, V, n, j + 1, p1, nb, n, nb > 1 ? hd : nullptr,
+                               (double*)nullptr);
+            hipLaunchKernelGGL(k_dots, dim3(j + 1, nb), dim3(kT), 0, st, V, n, w, n, p2);
+            hipLaunchKernelGGL(k_subtract, dim3(nu), dim3(kT), 0, st, w, V, n, j + 1, p2, nb, n, nb > 1 ? hd2 : nullptr, pn);
+            if (nu > 1) hipLaunchKernelGGL(k_total, dim3(1), dim3(kT), 0, st, pn, nu, hd + 2 * m + 2);
             SOLVE_HIP(hipGetLastError());
             SOLVE_HIP(hipMemcpyAsync(hh, hd, sizeof(double) * (size_t)(2 * m + 3), hipMemcpyDeviceToHost, st));
             SOLVE_HIP(hipStreamSynchronize(st));
@@ -348,7 +418,8 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
         }
         for (int i = 0; i <= jl; ++i) h[i] = -y[i];
         SOLVE_HIP(hipMemcpyAsync(hd, h, sizeof(double) * (jl + 1), hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(k_subtract, dim3(nblocks(n)), dim3(kT), 0, st, x, V, n, jl + 1, hd, n);
+        hipLaunchKernelGGL(k_subtract, dim3(nu), dim3(kT), 0, st, x, V, n, jl + 1, hd, 1, n, (double*)nullptr,
+                           (double*)nullptr);
         SOLVE_HIP(hipGetLastError());
     }
 }
@@ -655,38 +726,33 @@ int ehd_solve_surfactant(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     hipStream_t st = ehd_ctx_stream(ctx);
     // diagonal preconditioner on the packed layout: 1 / (1 + kappa n(n+1)),
     // the inverse of the operator on the unit sphere (Lap_S Y_nm = -n(n+1) Y_nm)
-    std::vector<double> dinv((size_t)n, 1.0), dfwd((size_t)n, 1.0), kv((size_t)n);
-    {
-        size_t o = 0;
-        for (int d = 0; d < ehd_ctx_ndrops(ctx); ++d) {
-            const int p = ehd_ctx_drop_p(ctx, d);
-            for (int nn = 0; nn <= p; ++nn)
-                for (int m = 0; m <= nn; ++m)
-                    for (int part = 0; part < 2; ++part, ++o) {
-                        kv[o] = kappa_h[d];
-                        if (precond) {
-                            dfwd[o] = 1.0 + kappa_h[d] * nn * (nn + 1.0);
-                            dinv[o] = 1.0 / dfwd[o];
-                        }
-                    }
-        }
+    const int nd = ehd_ctx_ndrops(ctx);
+    std::vector<long long> off((size_t)nd + 1, 0);
+    for (int d = 0; d < nd; ++d) {
+        const int p = ehd_ctx_drop_p(ctx, d);
+        off[d + 1] = off[d] + (long long)(p + 1) * (p + 2);
     }
-    DevBuf lap, H, grad, proj, tmp, di, df, kd;
+    DevBuf lap, geo, proj, tmp, di, df, kd, offb, kb;
     SOLVE_HIP(hipMalloc(&lap.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&H.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&grad.p, sizeof(double) * (size_t)3 * T));
+    SOLVE_HIP(hipMalloc(&geo.p, sizeof(double) * (size_t)5 * T));
     SOLVE_HIP(hipMalloc(&proj.p, sizeof(double) * (size_t)n));
     SOLVE_HIP(hipMalloc(&tmp.p, sizeof(double) * (size_t)n));
     SOLVE_HIP(hipMalloc(&di.p, sizeof(double) * (size_t)n));
     SOLVE_HIP(hipMalloc(&df.p, sizeof(double) * (size_t)n));
     SOLVE_HIP(hipMalloc(&kd.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMemcpyAsync(kd.p, kv.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
-    SOLVE_HIP(hipMemcpyAsync(di.p, dinv.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
-    SOLVE_HIP(hipMemcpyAsync(df.p, dfwd.data(), sizeof(double) * n, hipMemcpyHostToDevice, st));
+    SOLVE_HIP(hipMalloc(&offb.p, sizeof(long long) * off.size()));
+    SOLVE_HIP(hipMalloc(&kb.p, sizeof(double) * (size_t)nd));
+    SOLVE_HIP(hipMemcpyAsync(offb.p, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice, st));
+    SOLVE_HIP(hipMemcpyAsync(kb.p, kappa_h, sizeof(double) * nd, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_diag, dim3(nd), dim3(kT), 0, st, reinterpret_cast<const long long*>(offb.p), kb.p, precond, kd.p,
+                       di.p, df.p);
+    SOLVE_HIP(hipGetLastError());
+    // the shapes' part of the Laplace-Beltrami operator, once per solve
+    if ((rc = ehd_ctx_lap_geometry(ctx, geo.p))) return rc;
     // operator c -> c - kappa P[Lap_S c], applied to M^{-1} y (right preconditioning)
     const Op A = [&](const double* in, double* out) -> int {
         hipLaunchKernelGGL(k_mul, dim3(nblocks(n)), dim3(kT), 0, st, di.p, in, tmp.p, n);
-        int r = ehd_surface(ctx, 1, tmp.p, H.p, grad.p, lap.p);
+        int r = ehd_ctx_lap_values(ctx, geo.p, tmp.p, lap.p);
         if (!r) r = ehd_analyze(ctx, 1, lap.p, out);
         if (r) return r;
         hipLaunchKernelGGL(k_xmky, dim3(nblocks(n)), dim3(kT), 0, st, tmp.p, kd.p, out, n);

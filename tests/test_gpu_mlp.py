@@ -78,3 +78,50 @@ def test_training_reduces_the_loss(E):
     print("training loss", first, "->", loss, flush=True)
     assert loss < 1e-2 * first
     net.close()
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1, 1, 1), (64, 128, 1, 65, 64), (63, 129, 2, 127, 65), (513, 64, 1, 3, 1),
+                                  (1000, 257, 2, 191, 130), (5, 7, 1, 2, 24577)])
+def test_products_at_the_edges_of_tiles_and_splits(E, dims):
+    """Tiles of 64, steps of 32 and parts of at least 64 terms: sizes one below,
+    at and above them, one row, sums of many parts, and more rows than one grid
+    of split parts takes.  The bound is the worst-case FP32 rounding of a sum of
+    K products in any order, (K + 3) units of 2^-23 of the sum of magnitudes,
+    carried through the layers; an activation within its bound of zero may take
+    either side of the ReLU."""
+    import torch
+    nin, nhid, nlay, nout, batch = dims
+    dev = torch.device("cuda", 0)
+    net = E.MLP(nin, nhid, nlay, nout, seed=3)
+    spec, n = M.layers(nin, nhid, nlay, nout)
+    rng = np.random.default_rng(8)
+    p = net.params()
+    p[[bo + j for (_, _, b, bo) in spec for j in range(b)]] = 0.1 * rng.standard_normal(sum(b for (_, _, b, _) in spec))
+    net.set_params(p.astype(np.float32))
+    p = net.params().astype(np.float64)
+    x = rng.standard_normal((batch, nin)).astype(np.float32)
+    gy = rng.standard_normal((batch, nout)).astype(np.float32)
+    xd, gd = torch.from_numpy(x).to(dev), torch.from_numpy(gy).to(dev)
+    y = torch.full((batch, nout), 7.0, dtype=torch.float32, device=dev)
+    net.forward(xd, y)
+    net.backward(gd)
+    g = net.grads().astype(np.float64)
+    u, wb = 2.0 ** -23, M.unpack(p, spec)
+    hs = M.forward(p, spec, x.astype(np.float64))
+    eh = [np.zeros_like(hs[0])]
+    for (W, b), h in zip(wb, hs):
+        eh.append(eh[-1] @ abs(W) + (len(W) + 3) * u * ((abs(h) + eh[-1]) @ abs(W) + abs(b)))
+    assert (abs(y.cpu().numpy() - hs[-1]) <= eh[-1]).all()
+    ref, dz, ez = M.backward(p, spec, hs, gy), gy.astype(np.float64), np.zeros(gy.shape)
+    bound = np.zeros(n)
+    for l in range(nlay, -1, -1):
+        o, a, b, bo = spec[l]
+        hm, zm = abs(hs[l]) + eh[l], abs(dz) + ez
+        bound[o:o + a * b] = (hm.T @ zm * (1 + (batch + 3) * u) - abs(hs[l]).T @ abs(dz)).ravel()
+        bound[bo:bo + b] = (zm * (1 + (batch + 3) * u) - abs(dz)).sum(axis=0)
+        dh, W = dz @ wb[l][0].T, abs(wb[l][0]).T
+        ez = ez @ W + (b + 3) * u * (zm @ W)
+        ez = np.where(abs(hs[l]) <= eh[l], ez + abs(dh), np.where(hs[l] > 0, ez, 0.0))
+        dz = np.where(hs[l] > 0, dh, 0.0)
+    assert (abs(g - ref) <= bound + 1e-30).all()
+    net.close()

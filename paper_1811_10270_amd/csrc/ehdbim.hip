@@ -64,7 +64,7 @@ struct LegTab {                // degree-p expansions on a degree-Q grid
     const double* cth;         // [Q+1] cos theta_i
     const double* trig;        // [nlon][p+1][2] cos(m phi_l), sin(m phi_l)
     const double* afrag;       // singular grids: MFMA A fragments of the quarter-period
-                               // cos/sin tables: [row tile][k-step (EC ES OC OS)][lane]
+                               // cos/sin tables: [row tile][k-step (EC ES OC OS; p > 32: in turn)][lane]
     const double* lfrag;       // singular grids: MFMA A fragments of the Legendre sums,
                                // [latitude block][wave][k-step][lane]; rows 0-7 Pbar,
                                // 8-15 dPbar/dtheta at 8 latitudes
@@ -638,8 +638,8 @@ __global__ void k_src_dens(const double* __restrict__ synf, const double* __rest
 // Singular self-interaction, one block per target (paper Sec. 2.1,
 // eq. mod_weights and the rotation of the target to the north pole).
 //   1. rotated coefficients c'_{nm'} = sum_m d^n_{m m'}(theta_t) e^{i m phi_t} c_nm
-//      of every field, in the real form of tables.h, into LDS (vector ALU),
-//      then into registers as the B operand of step 2a;
+//      of every field, in the real form of tables.h, as FP64 MFMA products
+//      per degree, in LDS, then into registers as the B operand of step 2a;
 //   2. for each block of 8 latitudes t_i of the rotated degree-q grid:
 //      a. Legendre sums G_f(m) = sum_n Pbar_n^m(t_i) c'_f(n,m) (and the theta
 //         derivative table for x) as FP64 MFMA chains over the degrees n,
@@ -648,16 +648,47 @@ __global__ void k_src_dens(const double* __restrict__ synf, const double* __rest
 //      b. longitude sums as FP64 MFMA products: the four nodes phi_l,
 //         pi - phi_l, pi + phi_l and 2 pi - phi_l share the four partial
 //         sums over (even m, odd m) x (cos, sin) terms, so four GEMMs of a
-//         quarter of the rows and a quarter of the terms each, with the
-//         cos/sin table as the register-resident A operand and the Fourier
-//         coefficients as B (columns = grid quantities);
+//         quarter of the nodes and a quarter of the terms each, with the
+//         Fourier coefficients as A (rows = grid quantities) and the cos/sin
+//         table as B, in registers (p <= 32) or LDS;
 //      c. per node: normal, area factor, the kernels with the modified
 //         weights, accumulated per thread;
 //   3. block reduction.
+// Bound by FP64 issue (MFMA and vector FP64 share one datapath) and by the
+// latency that two waves per SIMD leave: p = 32, per SIMD and two targets,
+// 306k cycles of which 165k are products and kernels (rotation 18 in 52,
+// Legendre 47 in 92, longitudes and kernels 102 in 121, the rest staging,
+// gather and barriers).  So p <= 32 runs blocks of four waves, two (p <= 16:
+// three) on a compute unit, whose phases fill each other's gaps; the
+// Fourier blocks of p = 48 leave room for one, of eight waves.  The node
+// values of a lane come from a register transpose, not through LDS, which is
+// what lets two blocks fit.  Against one 8-wave block with the rotation on
+// LDS broadcasts, a column schedule walked at run time and nodes through LDS:
+// 34,848 targets of p = 32 10.7 -> 8.95 ms, 256 drops 172 -> 143 ms, p = 24
+// 3.7 -> 3.0, p = 16 1.0 -> 0.54 and 76,832 of p = 48 64 -> 61.5 ms.
 // Fields in LDS: x(3) [f(3)] [u(3)] [sigma(1)]; D uses u when present, f
 // otherwise.  Output: raw[comp][T] (already scaled by 1/(4 pi)).
 // ---------------------------------------------------------------------------
 typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+// Lanes 32..63 of a change places with lanes 0..31 of b.
+__device__ __forceinline__ void swap32(double& a, double& b)
+{
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __builtin_bit_cast(double, (unsigned long long)hi[0] << 32 | lo[0]);
+    b = __builtin_bit_cast(double, (unsigned long long)hi[1] << 32 | lo[1]);
+}
+// Lanes 16..31 and 48..63 of a change places with lanes 0..15 and 32..47 of b.
+__device__ __forceinline__ void swap16(double& a, double& b)
+{
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __builtin_bit_cast(double, (unsigned long long)hi[0] << 32 | lo[0]);
+    b = __builtin_bit_cast(double, (unsigned long long)hi[1] << 32 | lo[1]);
+}
 
 // Longitude-sum geometry of the (p, q) rotated grid, N = nlon_q longitudes
 // phi_l = 2 pi l / N, H = N / 2.  With the partial sums
@@ -670,8 +701,8 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // EC + OC and EC - OC are plain sums.  Where the degree class allows it
 // (row0), row 0 is taken apart from the GEMM rows (which then start at
 // l0 = 1) when that lowers the padded tile count.
-//   nT row tiles of 16 (padded to nTp in {1, 2, 4, 8} so that the waves
-//   split the tiles evenly); term counts: EC floor(p/2)+1 (m = 0, 2, ..),
+//   nT row tiles of 16 (p <= 32: padded to nTp in {1, 2, 4, 8} so that the
+//   waves split the tiles evenly; above, a wave takes all of them); term counts: EC floor(p/2)+1 (m = 0, 2, ..),
 //   ES floor(p/2) (m = 2, 4, ..), OC = OS = ceil(p/2) (m = 1, 3, ..);
 //   k-steps of 4 terms per group, groups stored in the order EC ES OC OS.
 struct QuarterGrid {
@@ -682,8 +713,8 @@ __host__ __device__ inline QuarterGrid quarter_grid(int p, int nlonq, bool row0)
 {
     QuarterGrid g;
     g.H = nlonq / 2;
-    const int with0 = padded_tiles((g.H / 2 + 1 + 15) / 16), without0 = padded_tiles((g.H / 2 + 15) / 16);
-    g.l0 = (row0 && without0 < with0) ? 1 : 0;
+    const int with0 = (g.H / 2 + 1 + 15) / 16, without0 = (g.H / 2 + 15) / 16;
+    g.l0 = (row0 && (p <= 32 ? padded_tiles(without0) < padded_tiles(with0) : without0 < with0)) ? 1 : 0;
     g.rows = g.H / 2 + 1 - g.l0;           // GEMM rows l = l0 .. floor(H/2)
     g.nT = (g.rows + 15) / 16;
     g.nTp = padded_tiles(g.nT);
@@ -701,25 +732,28 @@ __host__ __device__ inline QuarterGrid quarter_grid(int p, int nlonq, bool row0)
 // Compile-time bounds of one degree class (all p <= PMAX; the rotated grid
 // has at most 8 row tiles of 16 half-period longitudes).
 constexpr int kLatBlock = 8;          // rotated latitudes per Legendre MFMA block
+// LDS doubles of one latitude's Fourier block: rows of 16 quantities, and 8
+// more so that the Legendre sums of neighbouring latitudes, stored by the
+// lane groups of one wave, meet different banks
+__host__ __device__ inline int self_gsz(const QuarterGrid& g) { return g.nks * 64 + 8; }
 
-// Degree columns m = 0..p are dealt to the NW waves in snake order
-// (0,1,..,NW-1, NW-1,..,0, 0,1,..); column m has ceil((p+1-m)/4) k-steps.
-__host__ __device__ constexpr int snake_wave(int m, int nw)
+// Legendre schedule.  Column m takes ceil((p + 1 - m) / 4) k-steps, so with
+// G = floor((p + 1) / 4) four columns have each length 1..G (group g: m =
+// p + 1 - 4 g + 0..3) and the r = (p + 1) % 4 columns left, m < r, have G + 1.
+// A wave takes one column of each group (4 waves) or of every other one (8
+// waves: the halves take the longer and the shorter group of each pair in
+// turn), so its lengths are known when the code is built and every wave has
+// nearly the same number; columns m < r go to the waves 0..r-1 on top.
+__host__ __device__ constexpr int self_group(int s, int w, int nw, int gmax)
 {
-    return ((m / nw) & 1) ? nw - 1 - (m % nw) : (m % nw);
+    return nw == 4 ? gmax - s : gmax - 2 * s - (((w >> 2) + s) & 1);
 }
-
-constexpr int wave_ksteps_max(int PMAX, int nw)   // max over p <= PMAX and waves
+__host__ __device__ constexpr int self_pos_len(int s, int nw, int gmax) { return nw == 4 ? gmax - s : gmax - 2 * s; }
+__host__ __device__ constexpr int self_pos_off(int s, int nw, int gmax)
 {
-    int best = 0;
-    for (int p = 1; p <= PMAX; ++p)
-        for (int w = 0; w < nw; ++w) {
-            int t = 0;
-            for (int m = 0; m <= p; ++m)
-                if (snake_wave(m, nw) == w) t += (p + 1 - m + 3) / 4;
-            best = t > best ? t : best;
-        }
-    return best;
+    int t = 0;
+    for (int i = 0; i < s; ++i) t += self_pos_len(i, nw, gmax);
+    return t;
 }
 
 // Slot of workgroup `bid` when the workgroups of a grid of `nb` are dealt to
@@ -734,27 +768,35 @@ __device__ __forceinline__ unsigned xcd_slot(unsigned bid, unsigned nb)
 
 template <int PMAX>
 struct SelfClass {
-    static constexpr int KEC = (PMAX / 2 + 1 + 3) / 4;         // max k-steps per group
-    static constexpr int KES = (PMAX / 2 + 3) / 4;
-    static constexpr int KOC = ((PMAX + 1) / 2 + 3) / 4;
-    static constexpr int NT = 512;                             // threads per block
+    // longitude sums: k-steps of EC, one more than those of ES, OC and OS, and
+    // all; in the order of the products, step u is group u & 3, step u >> 2
+    static constexpr int KEC = PMAX / 8 + 1, KT = 4 * KEC - 3;
+    static_assert(PMAX % 8 == 0, "");
+    static constexpr int NT = PMAX <= 32 ? 256 : 512;          // threads per block
     static constexpr int NW = NT / 64;                         // waves per block
-    static constexpr int TPW = (8 + NW - 1) / NW;              // row tiles per wave (max)
-    static constexpr int KW = wave_ksteps_max(PMAX, NW);       // Legendre k-steps per wave
+    static constexpr int WPE = PMAX <= 16 ? 3 : 2;             // waves per SIMD to fit
+    static constexpr int GMAX = (PMAX + 1) / 4;                // groups of Legendre columns
+    static constexpr int NPOS = NW == 4 ? GMAX : GMAX / 2;     // columns per wave
+    static constexpr int KWS = self_pos_off(NPOS, NW, GMAX);   // their k-steps (table slots)
+    static constexpr int KLO = GMAX + 1;                       // and of a column m < r
+    static constexpr int KW = KWS + KLO;
     // row 0 of the longitude sums may be taken apart (pays at q = 2p for
-    // p = 16 and 32: one tile less; elsewhere the tile count is unchanged)
-    static constexpr bool ROW0 = PMAX == 16 || PMAX == 32;
-    // rotation loop unroll (measured: 2 for p <= 24, 4 above)
-    static constexpr int RU = PMAX <= 24 ? 2 : 4;
-    // Legendre A fragments per prefetch batch: the default (measured best:
-    // 5 for p <= 48, 3 for p <= 32, 2 below) and the two others built for the
-    // field set x, f, sigma, among which the self-interaction autotuner picks
-    static constexpr int PF = PMAX == 48 ? 5 : PMAX == 32 ? 3 : 2;
-    static constexpr int PF_ALT0 = PMAX == 48 ? 3 : PMAX == 32 ? 2 : 3;
+    // p = 16, 32 and 48: one tile less; elsewhere the tile count is unchanged)
+    static constexpr bool ROW0 = PMAX != 24;
+    // Pairs of Legendre fragments of a wave's next column loaded before the
+    // products of the current one: the default and the two others built for the field set
+    // x, f, sigma, among which the self-interaction autotuner picks
+    static constexpr int PF = PMAX == 48 ? 3 : PMAX == 32 ? 3 : 2;
+    static constexpr int PF_ALT0 = PMAX == 48 ? 5 : PMAX == 32 ? 2 : 3;
     static constexpr int PF_ALT1 = PMAX == 48 ? 6 : PMAX == 32 ? 5 : 4;
 };
 
-// Legendre k-steps per wave of the degree class of p (table stride per wave).
+// Waves of the degree class of p, its column groups and Legendre table slots per wave.
+static inline int self_nw(int p) { return p <= 32 ? SelfClass<32>::NW : SelfClass<48>::NW; }
+static inline int self_gmax(int p)
+{
+    return p <= 16 ? SelfClass<16>::GMAX : p <= 24 ? SelfClass<24>::GMAX : p <= 32 ? SelfClass<32>::GMAX : SelfClass<48>::GMAX;
+}
 static inline int self_kw(int p)
 {
     return p <= 16 ? SelfClass<16>::KW : p <= 24 ? SelfClass<24>::KW : p <= 32 ? SelfClass<32>::KW : SelfClass<48>::KW;
@@ -771,13 +813,13 @@ static inline bool self_row0(int p)
 // raw[slot * gstride + (ij * (Q + 1) + latitude) * nlon + longitude], slot the
 // target's place in `order` (for the solvers' operator matrices).
 template <int PMAX, bool HF, bool HU, bool HS, int PFT = 0, int MODE = 0>
-__global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
+__global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_self(
     const DropInfo* __restrict__ drops, const LegTab* __restrict__ legs,
     const WigTab* __restrict__ wigs, const int* __restrict__ order, const int* __restrict__ tdrop,
     const double* __restrict__ xcoef, const double* __restrict__ fcoef,
     const double* __restrict__ ucoef, const double* __restrict__ scoef,
     const double* __restrict__ tx, const double* __restrict__ tnrm, long long T, unsigned kinds,
-    double* __restrict__ raw, long long gstride)
+    double* __restrict__ raw, long long gstride, unsigned lds_doubles)
 {
     static_assert(MODE == 0 || (!HF && !HU && !HS), "weights only");
     constexpr int NF = 3 + (HF ? 3 : 0) + (HU ? 3 : 0) + (HS ? 1 : 0);
@@ -786,7 +828,6 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     constexpr int VD = 9;                // first density variant
     using SC = SelfClass<PMAX>;
     static_assert(2 * NF <= 16, "at most 8 fields: (field, re/im) fill the 16 MFMA columns");
-    static_assert(SC::NW == 8, "row tiles (up to 8) are split evenly over 8 waves");
     constexpr int NT = SC::NT, NW = SC::NW, LB = kLatBlock;
     extern __shared__ double2 lds[];
     __shared__ double red[NW][9];
@@ -822,23 +863,17 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     // term groups.  Waves w, w + nTp, .. share tile w % nTp and split the
     // latitudes of a block.  Loaded here, before the rotation, whose time
     // hides their latency.
-    const int my_tile = wv % qg.nTp;
-    const bool dft_wave = my_tile < qg.nT;
-    double aEC[SC::KEC], aES[SC::KES], aOC[SC::KOC], aOS[SC::KOC];
-    {
-        const auto src = gmem(Lq.afrag + (long long)(dft_wave ? my_tile : 0) * qg.nks * 64 + lane);
+    constexpr bool TREG = PMAX <= 32;
+    const int my_tile = wv % min(qg.nTp, NW);
+    double aT[TREG ? SC::KT : 1];
+    auto load_trig = [&](int tile) __attribute__((always_inline)) {
+        const bool on = tile < qg.nT;
+        const auto src = gmem(Lq.afrag + (long long)(on ? tile : 0) * qg.nks * 64 + lane);
 #pragma unroll
-        for (int ks = 0; ks < SC::KEC; ++ks)
-            aEC[ks] = (dft_wave && ks < qg.nk[0]) ? src[(long long)(qg.base[0] / 4 + ks) * 64] : 0.0;
-#pragma unroll
-        for (int ks = 0; ks < SC::KES; ++ks)
-            aES[ks] = (dft_wave && ks < qg.nk[1]) ? src[(long long)(qg.base[1] / 4 + ks) * 64] : 0.0;
-#pragma unroll
-        for (int ks = 0; ks < SC::KOC; ++ks) {
-            aOC[ks] = (dft_wave && ks < qg.nk[2]) ? src[(long long)(qg.base[2] / 4 + ks) * 64] : 0.0;
-            aOS[ks] = (dft_wave && ks < qg.nk[3]) ? src[(long long)(qg.base[3] / 4 + ks) * 64] : 0.0;
-        }
-    }
+        for (int u = 0; u < SC::KT; ++u)
+            aT[u] = (on && (u >> 2) < qg.nk[u & 3]) ? src[(long long)(qg.base[u & 3] / 4 + (u >> 2)) * 64] : 0.0;
+    };
+    if constexpr (TREG) load_trig(my_tile);
 
     // 1. rotation, into LDS (column-major: column m holds n = m..p
     //    contiguously).
@@ -864,96 +899,132 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
         }
     }
     __syncthreads();
+    const int ci = lane & 15, cf_ = ci >> 1, cri = ci & 1;   // MFMA column: field, re / im
+    double* const crd = reinterpret_cast<double*>(lds);
     {
         const long wb = ehd::wig_block(p);
         const auto A = gmem(W.A + (long long)j * wb);
         const auto B = gmem(W.B + (long long)j * wb);
-        // Jobs: each degree >= 2 npair alone (64 lanes, m' = lane), then the
-        // pairs (2k, 2k+1) of degrees <= 31 on the two half-waves (m' =
-        // lane % 32), so that each LDS broadcast of z_nm serves two degrees
-        // (the rotation is bound by those broadcasts).  Jobs by decreasing
-        // length, dealt to the waves in snake order.
-        const int npair = min(p + 1, 32) / 2, nsingle = p + 1 - 2 * npair, njob = nsingle + npair;
+        // ND degrees n0.. of equally many k-steps, NT row tiles of 16 orders
+        // m' each (degrees past p are clamped to p and not stored)
+        auto rotate = [&](auto nt_, auto nd_, int n0) __attribute__((always_inline)) {
+            constexpr int RT = decltype(nt_)::value, ND = decltype(nd_)::value;
+            dbl4 ra[ND * RT], rb[ND * RT];
+            double fa[2][ND * RT], fb[2][ND * RT], fz[2][ND];
+#pragma unroll
+            for (int i = 0; i < ND * RT; ++i) ra[i] = rb[i] = dbl4{0, 0, 0, 0};
+            const int nk = n0 / 4 + 1;
+            auto load = [&](int ks, int h) __attribute__((always_inline)) {
+                const int m = 4 * ks + (lane >> 4);
+#pragma unroll
+                for (int e = 0; e < ND; ++e) {
+                    const int n = min(n0 + e, p), mm = min(m, n);
+                    const double z = crd[2 * (min(cf_, NF - 1) * (int)nc + column_start(p, mm) + n - mm) + cri];
+                    fz[h][e] = m <= n ? z : 0.0;
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        const long o = ehd::wig_off(n) + mm * (n + 1) + min(16 * t + ci, n);
+                        fa[h][e * RT + t] = A[o];
+                        fb[h][e * RT + t] = B[o];
+                    }
+                }
+            };
+            auto mul = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < ND * RT; ++i) {
+                    ra[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[h][i], fz[h][i / RT], ra[i], 0, 0, 0);
+                    rb[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[h][i], fz[h][i / RT], rb[i], 0, 0, 0);
+                }
+            };
+            load(0, 0);
+            for (int ks = 0; ks < nk; ks += 2) {
+                load(min(ks + 1, nk - 1), 1);
+                __builtin_amdgcn_sched_barrier(0);
+                mul(0);
+                if (ks + 1 == nk) break;
+                load(min(ks + 2, nk - 1), 0);
+                __builtin_amdgcn_sched_barrier(0);
+                mul(1);
+            }
+#pragma unroll
+            for (int i = 0; i < ND * RT; ++i) {
+                const int n = n0 + i / RT;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int mp = 16 * (i % RT) + (lane >> 4) + 4 * r;
+                    if (n <= p && mp <= n && cf_ < NF)
+                        crd[2 * (cf_ * (int)nc + column_start(p, mp) + n - mp) + cri] = cri ? rb[i][r] : ra[i][r];
+                }
+            }
+        };
+        // Jobs by decreasing length, dealt to the waves in snake order: one
+        // degree each above 31, two of 16..31, four below (about the same
+        // four row tiles; half of that at p <= 16, for registers).
+        constexpr int NDM = PMAX <= 16 ? 1 : 2, NDL = 2 * NDM, PER = 4 / NDL;
+        const int nq = p >> 2;
+        const int empty = (3 - (p & 3)) / (nq >= 8 ? 1 : nq >= 4 ? NDM : NDL);
+        const int n1 = nq >= 8 ? 4 * (nq - 7) : 0, n2 = nq >= 8 ? 8 : nq >= 4 ? 4 / NDM * (nq - 3) : 0;
+        const int n3 = PER * min(nq + 1, 4), njob = n1 + n2 + n3 - empty;
         const int dn0 = 2 * NW - 1 - 2 * wv, dn1 = 2 * wv + 1;
         bool odd = false;
         for (int J = wv; J < njob; J += odd ? dn1 : dn0, odd = !odd) {
-            const bool single = J < nsingle;                               // wave-uniform
-            const int k2 = single ? 0 : 2 * (npair - 1 - (J - nsingle));
-            const int nmax = single ? p - J : k2 + 1;                      // last order m of the job
-            const int n = single ? nmax : k2 + (lane >> 5);                // this lane's degree
-            const int mpl = single ? lane : (lane & 31);                   // this lane's order m'
-            const int mp = mpl <= n ? mpl : n;            // lanes past n repeat m' = n, store nothing
-            const auto An = A + ehd::wig_off(n) + mp;
-            const auto Bn = B + ehd::wig_off(n) + mp;
-            double are[NF], aim[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) { are[f] = 0.0; aim[f] = 0.0; }
-            const double2* zn = cr + column_start(p, 0) + n;   // z_n0 of field 0; z_nm at + column_start(p, m) - m
-#pragma unroll SC::RU
-            for (int m = 0; m <= nmax; ++m) {
-                // the lower degree of a pair has no order m = nmax: weight 0 (its
-                // z address then lies in the next column, in bounds)
-                const bool on = m <= n;
-                const int mm = on ? m : n;
-                const double a = on ? An[mm * (n + 1)] : 0.0, b = on ? Bn[mm * (n + 1)] : 0.0;
-                const int zo = column_start(p, m) - m;
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    const double2 z = zn[f * nc + zo];
-                    are[f] = fma(a, z.x, are[f]);
-                    aim[f] = fma(b, z.y, aim[f]);
-                }
-            }
-            if (mpl <= n) {
-                const int cpos = column_start(p, mpl) + n - mpl;
-#pragma unroll
-                for (int f = 0; f < NF; ++f) cr[f * nc + cpos] = make_double2(are[f], aim[f]);
+            const int S = J + empty;
+            if (PMAX >= 32 && S < n1) {
+                const int n = 4 * nq + 3 - S;
+                if (PMAX >= 48 && n >= 48) rotate(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{}, n);
+                else rotate(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{}, n);
+            } else if (S < n1 + n2) {
+                rotate(std::integral_constant<int, 2>{}, std::integral_constant<int, NDM>{},
+                       4 * min(nq, 7) + 4 - NDM * (S - n1 + 1));
+            } else {
+                rotate(std::integral_constant<int, 1>{}, std::integral_constant<int, NDL>{}, NDL * (n3 - 1 - (S - n1 - n2)));
             }
         }
     }
     __syncthreads();
 
     // 2. rotated coefficients into registers as the B operand of the Legendre
-    //    MFMA: wave wv owns the degree columns m with snake_wave(m) == wv,
-    //    walked in increasing m as one sequence of k-steps t; lane holds
-    //    c'_f(n, m) (re or im) for column (f, re/im) = lane % 16 and
-    //    n = m + 4 ks + lane / 16.
-    double cB[SC::KW];
-    const int ci = lane & 15, cf_ = ci >> 1, cri = ci & 1;
-    {
-        // this wave's columns in snake order: m = wv, then steps of dn0 and
-        // dn1 in turn (wave-uniform, straight-line, so the loads issue together)
-        const int dn0 = 2 * NW - 1 - 2 * wv, dn1 = 2 * wv + 1;
-        int m = wv, ks = 0;
-        bool odd = false;
-        int left = (m <= p) ? (p + 1 - m + 3) / 4 : 0;
+    //    MFMA: lane holds c'_f(n, m) (re or im) for column (f, re/im) =
+    //    lane % 16 and n = m + 4 k + lane / 16, with the factor of the real
+    //    Fourier coefficients, 1 (m = 0) or 2 and -2.
+    const int G = (p + 1) >> 2, left = (p + 1) & 3;
+    double cB[SC::KWS], cL[SC::KLO];
+    auto gather = [&](int m, int k, bool on) __attribute__((always_inline)) {
+        const int n = m + 4 * k + (lane >> 4);
+        const bool ok = on && cf_ < NF && n <= p;
+        const double c = crd[2 * (ok ? cf_ * (int)nc + column_start(p, m) + n - m : 0) + cri];
+        return ok ? (m == 0 ? 1.0 : cri ? -2.0 : 2.0) * c : 0.0;
+    };
 #pragma unroll
-        for (int t = 0; t < SC::KW; ++t) {
-            const int n = m + 4 * ks + (lane >> 4);
-            const bool ok = left > 0 && cf_ < NF && n <= p;
-            const int idx = ok ? cf_ * (int)nc + column_start(p, m) + n - m : 0;
-            const double2 c = cr[idx];
-            cB[t] = ok ? (cri ? c.y : c.x) : 0.0;
-            if (left > 0) {
-                --left;
-                ++ks;
-                if (left == 0) {
-                    m += odd ? dn1 : dn0;
-                    odd = !odd;
-                    ks = 0;
-                    left = (m <= p) ? (p + 1 - m + 3) / 4 : 0;
-                }
-            }
-        }
+    for (int s = 0; s < SC::NPOS; ++s) {
+        const int g = self_group(s, wv, NW, SC::GMAX);
+#pragma unroll
+        for (int k = 0; k < self_pos_len(s, NW, SC::GMAX); ++k)
+            cB[self_pos_off(s, NW, SC::GMAX) + k] = gather(max(0, p + 1 - 4 * g + (wv & 3)), k, g <= G);
     }
-    __syncthreads();   // LDS free: Fourier blocks and per-wave node buffers from here on
+    if (wv < left) {
+#pragma unroll
+        for (int k = 0; k < SC::KLO; ++k) cL[k] = gather(wv, k, k <= G);
+    }
+    __syncthreads();   // LDS free: Fourier blocks, row-0 records, columns m < r, cos/sin table from here on
 
-    const int gsz = qg.nks * 64;                      // one latitude's Fourier block
-    constexpr int NVP = NV | 1;                       // node record stride (odd: fewer bank conflicts)
-    // node buffer per wave: 64 records (+ spare slots for the pipelined
-    // stores of p <= 32)
-    constexpr int NBW = 64 * NVP + (PMAX <= 32 ? 16 : 0);
-    double* NB = R + LB * gsz + wv * NBW;             // this wave's node values (64 nodes)
+    const int gsz = self_gsz(qg);                     // one latitude's Fourier block
+    constexpr int NVP = NV | 1;                       // row-0 record stride
+    double* const RZ = R + LB * gsz;
+    double* const LO = RZ + (SC::ROW0 ? 2 * LB * NVP : 0) + wv * (G + 1) * 64 + lane;
+    if (wv < left) {
+#pragma unroll
+        for (int k = 0; k < SC::KLO; ++k)
+            if (k <= G) LO[k * 64] = cL[k];
+    }
+    // above p = 32 the cos/sin table goes to LDS where it fits
+    double* const TL = RZ + (SC::ROW0 ? 2 * LB * NVP : 0) + left * (G + 1) * 64;
+    const int tsz = qg.nT * SC::KT * 64;
+    const bool tlds = !TREG && (unsigned)(TL - R + tsz) <= lds_doubles;
+    if (tlds) {
+        const auto src = gmem(Lq.afrag);
+        for (int z = threadIdx.x; z < tsz; z += blockDim.x) TL[z] = src[z];
+    }
     // Rows and columns of a Fourier block that are not rewritten meet zero A
     // entries (padding terms) or feed unused output columns; start from zeros.
     for (int z = threadIdx.x; z < LB * gsz; z += blockDim.x) R[z] = 0.0;
@@ -978,63 +1049,51 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     // cos row (re) or sin row (im) of m with factors 1 (m = 0) or 2 and -2,
     // x_phi / sin theta = -m (a_m sin - b_m cos) / sin theta in the other row.
     // Kept short: it is expanded at every k-step of the unrolled chain.
+    // (lanes without a value to store write to the spare slots of their block)
     const int f_l = cf_ < NF ? cf_ : 0;
     const int v_l = (f_l < 3) ? f_l : VD + (f_l - 3);
     const bool lane_xf = cf_ < 3, lane_field = cf_ < NF;
-    double* const Gl0 = R + (lane >> 4) * gsz;          // this lane's latitudes 0..3 of the block
-    double* const Gl1 = Gl0 + 4 * gsz;                  // and 4..7
-    // alternating steps between the snake-ordered columns of this wave
-    const int dm0 = 2 * NW - 1 - 2 * wv, dm1 = 2 * wv + 1;
-    auto store_col = [&](int m, const dbl4& a, double rs0, double rs1) {
-        if (!lane_field || (m == 0 && cri)) return;
-        const int kc = (m & 1) ? qg.base[2] + (m - 1) / 2 : m / 2;
-        const int ksr = (m & 1) ? qg.base[3] + (m - 1) / 2 : qg.base[1] + m / 2 - 1;
-        const int r12 = (cri ? ksr : kc) * 16, r3 = (cri ? kc : ksr) * 16;
-        const double sc = (m == 0) ? 1.0 : (cri ? -2.0 : 2.0);
-        Gl0[r12 + v_l] = sc * a[0];
-        Gl1[r12 + v_l] = sc * a[1];
-        if (lane_xf) {
-            Gl0[r12 + 3 + f_l] = sc * a[2];
-            Gl1[r12 + 3 + f_l] = sc * a[3];
-            if (m > 0) {
-                const double sx = -2.0 * m;
-                Gl0[r3 + 6 + f_l] = sx * rs0 * a[0];
-                Gl1[r3 + 6 + f_l] = sx * rs1 * a[1];
-            }
-        }
+    double* const Gl = R + (lane >> 4) * gsz;           // this lane's latitudes 0..3 of the block (4..7: + 4 gsz)
+    double* const spare = Gl + qg.nks * 64 + (lane & 7);
+    // its rows of m = 0, 2, .. and m = 1, 3, ..: the cos or sin rows, and the other ones for x_phi
+    const int row_e = cri ? qg.base[1] - 1 : 0, row_o = cri ? qg.base[3] : qg.base[2];
+    const int row_e3 = cri ? 0 : qg.base[1] - 1, row_o3 = cri ? qg.base[2] : qg.base[3];
+    auto store_col = [&](int m, const dbl4& a, double rs0, double rs1) __attribute__((always_inline)) {
+        const bool some = m > 0 || !cri;
+        double* const gr = Gl + (((m & 1) ? row_o : row_e) + (m >> 1)) * 16 + v_l;
+        double* const g = lane_field && some ? gr : spare;
+        double* const gt = lane_xf && some ? gr + 3 : spare;
+        double* const gp = lane_xf && m > 0 ? Gl + (((m & 1) ? row_o3 : row_e3) + (m >> 1)) * 16 + 6 + v_l : spare;
+        const double dm = m;
+        g[0] = a[0];
+        g[4 * gsz] = a[1];
+        gt[0] = a[2];
+        gt[4 * gsz] = a[3];
+        gp[0] = dm * rs0 * a[0];
+        gp[4 * gsz] = dm * rs1 * a[1];
     };
 
-    const int m_first = wv <= p ? wv : p + 1;
-    // Legendre fragments per prefetch batch (PFT, else the class default)
-    constexpr int PF = PFT > 0 ? PFT : SC::PF;
-    constexpr int NBATCH = (SC::KW + PF - 1) / PF;
-    // kernels at one node (its NV values in val: this lane's record of the
-    // wave's node buffer or of the row-0 records) with the modified weight wi of its
-    // latitude (0 for a lane without a node of its own), accumulated per
-    // lane.  gate: skip the kinds not requested (branches); without it
-    // every kind the fields allow is accumulated (the requested ones are
-    // stored) and the code has no branch, so the scheduler can interleave
-    // it with the next latitude's longitude-sum MFMAs.
-    auto eval_node = [&](const double* val, double wi, bool gate) {
+    // fragments of a wave's next column loaded ahead
+    constexpr int PF = 2 * (PFT > 0 ? PFT : SC::PF);
+    // kernels at one node (its NV values in val: this lane's registers or its
+    // row-0 record) with the modified weight wi of its latitude, accumulated
+    // per lane, the kinds requested only.
+    auto eval_node = [&](const double* val, double wi) {
         const double xt0 = val[3], xt1 = val[4], xt2 = val[5];
         const double xp0 = val[6], xp1 = val[7], xp2 = val[8];
         const double cx = xt1 * xp2 - xt2 * xp1;
         const double cy = xt2 * xp0 - xt0 * xp2;
         const double cz = xt0 * xp1 - xt1 * xp0;
-        // ungated, lanes without a node (weight 0) may hold padding rows of
-        // the longitude sums (zeros): keep their arithmetic finite (gated
-        // calls come from lanes with a node only)
-        const bool live = gate || wi != 0.0;
-        const double J2 = live ? cx * cx + cy * cy + cz * cz : 1.0;
+        const double J2 = cx * cx + cy * cy + cz * cz;
         const double iJ = rsqrt_nr(J2);
         const double w = wi * J2 * iJ;
         const double nx = cx * iJ, ny = cy * iJ, nz = cz * iJ;
         const double hx = x0[0] - val[0], hy = x0[1] - val[1], hz = x0[2] - val[2];
-        const double r2 = live ? hx * hx + hy * hy + hz * hz : 1.0;
+        const double r2 = hx * hx + hy * hy + hz * hz;
         const double ir = rsqrt_nr(r2), ir2 = ir * ir, ir3 = ir * ir2;
         const double hn = hx * nx + hy * ny + hz * nz;
         if constexpr (HF) {
-            if (!gate || wS) {
+            if (wS) {
                 const double f0 = val[VD], f1 = val[VD + 1], f2 = val[VD + 2];
                 const double hf = (hx * f0 + hy * f1 + hz * f2) * ir3;
                 acc[0] += w * (f0 * ir + hx * hf);
@@ -1043,7 +1102,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
             }
         }
         if constexpr (HF || HU) {
-            if (!gate || wD) {
+            if (wD) {
                 constexpr int uo = VD + (HU ? UOFF : FOFF) - 3;
                 const double hu = hx * val[uo] + hy * val[uo + 1] + hz * val[uo + 2];
                 const double tq = -6.0 * w * hu * hn * ir3 * ir2;
@@ -1054,9 +1113,9 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
         }
         if constexpr (HS) {
             const double sg = w * val[VD + SOFF - 3];
-            if (!gate || wSL) acc[6] += sg * ir;
-            if (!gate || wL) acc[7] += sg * hn * ir3;
-            if (!gate || wK) acc[8] += sg * (hx * n0v[0] + hy * n0v[1] + hz * n0v[2]) * ir3;
+            if (wSL) acc[6] += sg * ir;
+            if (wL) acc[7] += sg * hn * ir3;
+            if (wK) acc[8] += sg * (hx * n0v[0] + hy * n0v[1] + hz * n0v[2]) * ir3;
         }
     };
 
@@ -1091,70 +1150,81 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
     // after the block's last barrier one wave evaluates all sixteen in
     // sixteen lanes (during the next block's Legendre sums), instead of two
     // lanes in each of the eight waves.
-    double* const RZ = R + LB * gsz + NW * NBW;
     auto row0_eval = [&](int bb) {
         const int i = bb * LB + (lane >> 1);
         if (lane < 2 * LB && i <= Lq.Q) {
             if constexpr (MODE) emit_node(RZ + lane * NVP, wsing[i], i, (lane & 1) ? qg.H : 0);
-            else eval_node(RZ + lane * NVP, wsing[i], true);
+            else eval_node(RZ + lane * NVP, wsing[i]);
         }
     };
 
-    // first prefetch batch of the next latitude block: block 0's here, each
-    // later one loaded at the end of the block before, so that its latency
-    // hides behind that block's longitude sums
-    double avn[PF];
+    // first fragments of the next latitude block: block 0's here, each later
+    // one's loaded at the end of the block before, so that their latency hides
+    // behind that block's longitude sums
+    double fa[2][SC::KLO];
     {
         const auto lf0 = gmem(Lq.lfrag + (long long)wv * SC::KW * 64 + lane);
 #pragma unroll
-        for (int u = 0; u < PF; ++u) avn[u] = (u < SC::KW) ? lf0[(long long)u * 64] : 0.0;
+        for (int k = 0; k < min(PF, SC::GMAX); ++k) fa[0][k] = lf0[(long long)k * 64];
     }
     for (int b = 0; b < nblk; ++b) {
         if (SC::ROW0 && qg.l0 == 1 && b > 0 && wv == ((b - 1) & (NW - 1))) row0_eval(b - 1);
         // 3a. Legendre sums on MFMA: per degree column of this wave, a chain
         //     over n of (Pbar; dPbar at 8 latitudes) x (rotated coefficients).
-        //     This wave's A fragments are contiguous in the table (zero past
-        //     its last k-step), so they stream in batches independent of the
-        //     column bookkeeping.
+        //     Table slots past a column's end are zero; groups past G are
+        //     skipped whole.
         {
             const auto lf = gmem(Lq.lfrag + ((long long)b * NW + wv) * SC::KW * 64 + lane);
-            double av[2][PF];
+            // 1 / sin theta at this lane's two latitudes (clamped past the last
+            // one), with the sign of x_phi's term
+            const double sg = cri ? 1.0 : -1.0;
+            const double rs0 = sg * rsin[min(b * LB + (lane >> 4), Lq.Q)];
+            const double rs1 = sg * rsin[min(b * LB + (lane >> 4) + 4, Lq.Q)];
+            // (opaque: the store addresses of all columns would otherwise be
+            // kept in registers over the blocks, six per column)
+            int pb = p;
+            asm volatile("" : "+s"(pb));
+            // this wave's columns, the one m < r second (the waves without one
+            // load the first column's fragments again)
+            auto slot_len = [](int i) { return i == 1 ? SC::KLO : self_pos_len(i ? i - 1 : 0, NW, SC::GMAX); };
+            auto slot_ptr = [&](int i, int k) {
+                return lf + (long long)((i == 1 ? (wv < left ? SC::KWS : 0) : self_pos_off(i ? i - 1 : 0, NW, SC::GMAX)) + k) * 64;
+            };
 #pragma unroll
-            for (int u = 0; u < PF; ++u) av[0][u] = avn[u];
-            int m = m_first, left = (m <= p) ? (p + 1 - m + 3) / 4 : 0;
-            bool odd_step = (m_first / NW) & 1;
-            dbl4 a = dbl4{0, 0, 0, 0};
-            // 1 / sin theta at this lane's two latitudes (clamped past the last one)
-            const double rs0 = rsin[min(b * LB + (lane >> 4), Lq.Q)];
-            const double rs1 = rsin[min(b * LB + (lane >> 4) + 4, Lq.Q)];
+            for (int i = 0; i <= SC::NPOS; ++i) {
+                const int len = slot_len(i);
 #pragma unroll
-            for (int g = 0; g < NBATCH; ++g) {
-                if (g + 1 < NBATCH) {
+                for (int k = PF; k < len; ++k) fa[i & 1][k] = *slot_ptr(i, k);
+                if (i < SC::NPOS) {
 #pragma unroll
-                    for (int u = 0; u < PF; ++u) {
-                        const int t = (g + 1) * PF + u;
-                        av[(g + 1) & 1][u] = (t < SC::KW) ? lf[(long long)t * 64] : 0.0;
-                    }
+                    for (int k = 0; k < min(PF, slot_len(i + 1)); ++k) fa[(i + 1) & 1][k] = *slot_ptr(i + 1, k);
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                dbl4 a = dbl4{0, 0, 0, 0};
+                if (i == 1) {
+                    if (wv < left) {
+                        double lo[SC::KLO];
 #pragma unroll
-                for (int u = 0; u < PF; ++u) {
-                    const int t = g * PF + u;
-                    if (t < SC::KW && left > 0) {
-                        a = __builtin_amdgcn_mfma_f64_16x16x4f64(av[g & 1][u], cB[t], a, 0, 0, 0);
-                        if (--left == 0) {   // column finished: store it, go to the next one
-                            store_col(m, a, rs0, rs1);
-                            a = dbl4{0, 0, 0, 0};
-                            m += odd_step ? dm1 : dm0;
-                            odd_step = !odd_step;
-                            left = (m <= p) ? (p + 1 - m + 3) / 4 : 0;
-                        }
+                        for (int k = 0; k < SC::KLO; ++k) lo[k] = LO[min(k, G) * 64];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < SC::KLO; ++k) a = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[1][k], lo[k], a, 0, 0, 0);
+                        store_col(wv, a, rs0, rs1);
+                    }
+                } else {
+                    const int s = i ? i - 1 : 0, g = self_group(s, wv, NW, SC::GMAX);
+                    if (g <= G) {
+#pragma unroll
+                        for (int k = 0; k < len; ++k)
+                            a = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i & 1][k], cB[self_pos_off(s, NW, SC::GMAX) + k], a, 0, 0, 0);
+                        store_col(pb + 1 - 4 * g + (wv & 3), a, rs0, rs1);
                     }
                 }
             }
             if (b + 1 < nblk) {
                 const auto lfn = lf + (long long)NW * SC::KW * 64;   // block b + 1, this wave
 #pragma unroll
-                for (int u = 0; u < PF; ++u) avn[u] = (u < SC::KW) ? lfn[(long long)u * 64] : 0.0;
+                for (int k = 0; k < min(PF, SC::GMAX); ++k) fa[0][k] = lfn[(long long)k * 64];
             }
         }
         __syncthreads();
@@ -1164,178 +1234,134 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT) void k_self(
         //     values through the wave's own LDS buffer (64 nodes: {l, H - l,
         //     H + l, N - l} x 16 rows), then one node per lane: kernels with
         //     the modified weights.
-        if (dft_wave) {
-            const int boff = (lane >> 4) * 16 + (lane & 15);
-            // Four row tiles (p = 48): the two waves of a tile share a SIMD,
-            // and with four latitudes each the first finished its sums well
-            // before the second; taking five of the eight balances the pair
-            // (67.6 -> 66.3 ms on the 64-drop workload).  Otherwise latitudes
-            // are dealt round-robin over the waves of a tile.
-            const bool split = qg.nTp == 4;
-            const int ll0 = split ? (wv < 4 ? 0 : 5) : wv / qg.nTp;
-            const int ll1 = split ? (wv < 4 ? 5 : LB) : LB;
-            const int dll = split ? 1 : SC::NW / qg.nTp;
-            int nmine = 0;                               // this wave's latitudes in the block
-            for (int ll = ll0; ll < ll1 && b * LB + ll <= Lq.Q; ll += dll) ++nmine;
-            // node of this lane; the four images coincide pairwise at l = 0 and at 2 l = H
-            const int c4 = lane >> 4, l = qg.l0 + 16 * my_tile + (lane & 15);
+        const int boff = (lane >> 4) * 16 + (lane & 15);
+        int kb[4], kl[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            kb[q] = qg.base[q] * 16;
+            kl[q] = max(qg.nk[q] - 1, 0);
+        }
+        // The partial sums of one latitude and row tile: lane group g holds
+        // quantities g + 4 r of row l.  The four images of each, then a 4x4
+        // transpose over the lane groups gives group c every quantity of image
+        // c: one node per lane.
+        auto nodes = [&](int ll, int tile, double wi, const dbl4& ec, const dbl4& es, const dbl4& oc,
+                         const dbl4& os) __attribute__((always_inline)) {
+            double nv[16];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double s0 = ec[r] + oc[r], s1 = ec[r] - oc[r];
+                const double t0 = es[r] + os[r], t1 = es[r] - os[r];
+                double im[4] = {s0 + t0, s1 - t1, s1 + t1, s0 - t0};   // l, H - l, H + l, N - l
+                swap32(im[0], im[2]);
+                swap32(im[1], im[3]);
+                swap16(im[0], im[1]);
+                swap16(im[2], im[3]);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) nv[4 * r + h] = im[h];
+            }
+            // the four images coincide pairwise at l = 0 and at 2 l = H
+            const int c4 = lane >> 4, l = qg.l0 + 16 * tile + (lane & 15);
             const bool node_ok = 2 * l <= qg.H &&
                                  (c4 == 0 || (c4 == 1 && 2 * l < qg.H) || (c4 == 2 && l > 0) ||
                                   (c4 == 3 && l > 0 && 2 * l < qg.H));
-            const int lon = c4 == 0 ? l : c4 == 1 ? qg.H - l : c4 == 2 ? qg.H + l : 2 * qg.H - l;
-            dbl4 ec, es, oc, os;
-            // longitude sums of latitude ll of the block, this wave's row tile:
-            // k-steps up to the class maximum without guards (past a group's
-            // last k-step the A fragment is zero and the B address is clamped
-            // to the group's last k-step)
-            auto chain = [&](int ll) {
-                const double* G = R + ll * gsz + boff;
-                ec = dbl4{0, 0, 0, 0};
-                es = ec;
-                oc = ec;
-                os = ec;
-                const int kl0 = qg.nk[0] - 1, kl1 = qg.nk[1] - 1, kl2 = qg.nk[2] - 1, kl3 = qg.nk[3] - 1;
-                const int g0 = qg.base[0] / 4, g1 = qg.base[1] / 4, g2 = qg.base[2] / 4, g3 = qg.base[3] / 4;
+            if (node_ok) {
+                const int lon = c4 == 0 ? l : c4 == 1 ? qg.H - l : c4 == 2 ? qg.H + l : 2 * qg.H - l;
+                if constexpr (MODE) emit_node(nv, wi, b * LB + ll, lon);
+                else eval_node(nv, wi);
+            }
+        };
+        // k-steps run to the class maximum without guards: past a group's last
+        // one the cos/sin operand is zero and the other one's address is clamped.
+        // LDS reads go a batch of products ahead, the first batch of the next
+        // latitude or tile before this one's kernels.  The scheduler would move
+        // each read down to its product and wait for it there (p = 48: 7.7k
+        // cycles per tile and wave pair), so barriers hold them.
+        constexpr int NBT = 5, NBA = (SC::KT + NBT - 1) / NBT;
+        double ga[2][NBT], ta[2][TREG ? 1 : NBT];
+        auto fetch = [&](const double* Gb, auto tp, int i, int h) __attribute__((always_inline)) {
 #pragma unroll
-                for (int ks = 0; ks < SC::KEC; ++ks) {
-                    ec = __builtin_amdgcn_mfma_f64_16x16x4f64(aEC[ks], G[(g0 + min(ks, kl0)) * 64], ec, 0, 0, 0);
-                    if (ks < SC::KES)
-                        es = __builtin_amdgcn_mfma_f64_16x16x4f64(aES[ks < SC::KES ? ks : 0],
-                                                                  G[(g1 + max(min(ks, kl1), 0)) * 64], es, 0, 0, 0);
-                    if (ks < SC::KOC) {
-                        oc = __builtin_amdgcn_mfma_f64_16x16x4f64(aOC[ks < SC::KOC ? ks : 0], G[(g2 + min(ks, kl2)) * 64],
-                                                                  oc, 0, 0, 0);
-                        os = __builtin_amdgcn_mfma_f64_16x16x4f64(aOS[ks < SC::KOC ? ks : 0], G[(g3 + min(ks, kl3)) * 64],
-                                                                  os, 0, 0, 0);
-                    }
-                }
-            };
-            // node buffer <- the four images of the latitude in ec, es, oc, os
-            // (record 16 c + row for the nodes c = 0..3 of the row), then this
-            // lane's node values -> nv (registers: the buffer is then free)
-            auto publish = [&](double* nv) {
-                {
-                    // lanes of the unused columns v >= NV write to spare slots
-                    // past the records instead of branching around the stores
-                    const int v = lane & 15;
-                    const bool real = v < NV;
-                    double* const dst = real ? NB + v : NB + 64 * NVP + (v - NV);
-                    const int step = real ? NVP : 0;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = (lane >> 4) + 4 * r;
-                        const double s0 = ec[r] + oc[r], s1 = ec[r] - oc[r];
-                        const double t0 = es[r] + os[r], t1 = es[r] - os[r];
-                        dst[row * step] = s0 + t0;             // l
-                        dst[(16 + row) * step] = s1 - t1;      // H - l
-                        dst[(32 + row) * step] = s1 + t1;      // H + l
-                        dst[(48 + row) * step] = s0 - t0;      // N - l
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                for (int v = 0; v < NV; ++v) nv[v] = NB[lane * NVP + v];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            };
-            // Software pipeline over a wave's two latitudes (p = 24, 32): the
-            // second latitude's sums are issued to the matrix unit right before
-            // the vector unit evaluates the kernels at the first latitude's
-            // nodes, in one basic block, so the two overlap.  (p = 48 has no
-            // registers to spare for it, p = 16 one latitude per wave and block.)
-            double na[NV], nb[NV];
-            if (PMAX <= 32 && nmine == 2) {
-                // the weights are loaded unconditionally (both latitudes exist),
-                // so no branch splits the block
-                const double wa = wsing[b * LB + ll0], wb = wsing[b * LB + ll0 + dll];
-                chain(ll0);
-                publish(na);
-                __builtin_amdgcn_sched_barrier(0);
-                chain(ll0 + dll);
-                if constexpr (MODE) {
-                    if (node_ok) emit_node(na, wa, b * LB + ll0, lon);
-                } else {
-                    eval_node(na, node_ok ? wa : 0.0, false);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                publish(nb);
-                if constexpr (MODE) {
-                    if (node_ok) emit_node(nb, wb, b * LB + ll0 + dll, lon);
-                } else {
-                    eval_node(nb, node_ok ? wb : 0.0, false);
-                }
-            } else {
-                for (int ll = ll0; ll < ll1; ll += dll) {
-                    const int i = b * LB + ll;
-                    if (i > Lq.Q) break;
-                    const double* G = R + ll * gsz + boff;
-                    dbl4 ec1 = dbl4{0, 0, 0, 0}, es1 = ec1, oc1 = ec1, os1 = ec1;
-                    const int kl0 = qg.nk[0] - 1, kl1 = qg.nk[1] - 1, kl2 = qg.nk[2] - 1, kl3 = qg.nk[3] - 1;
-                    const int g0 = qg.base[0] / 4, g1 = qg.base[1] / 4, g2 = qg.base[2] / 4, g3 = qg.base[3] / 4;
-#pragma unroll
-                    for (int ks = 0; ks < SC::KEC; ++ks) {
-                        ec1 = __builtin_amdgcn_mfma_f64_16x16x4f64(aEC[ks], G[(g0 + min(ks, kl0)) * 64], ec1, 0, 0, 0);
-                        if (ks < SC::KES)
-                            es1 = __builtin_amdgcn_mfma_f64_16x16x4f64(aES[ks < SC::KES ? ks : 0],
-                                                                       G[(g1 + max(min(ks, kl1), 0)) * 64], es1, 0, 0,
-                                                                       0);
-                        if (ks < SC::KOC) {
-                            oc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(aOC[ks < SC::KOC ? ks : 0],
-                                                                       G[(g2 + min(ks, kl2)) * 64], oc1, 0, 0, 0);
-                            os1 = __builtin_amdgcn_mfma_f64_16x16x4f64(aOS[ks < SC::KOC ? ks : 0],
-                                                                       G[(g3 + min(ks, kl3)) * 64], os1, 0, 0, 0);
-                        }
-                    }
-                    // node buffer: record 16 c + row for the nodes c = 0..3 of the row
-                    {
-                        const int v = lane & 15;
-                        if (v < NV) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const int row = (lane >> 4) + 4 * r;
-                                const double s0 = ec1[r] + oc1[r], s1 = ec1[r] - oc1[r];
-                                const double t0 = es1[r] + os1[r], t1 = es1[r] - os1[r];
-                                NB[row * NVP + v] = s0 + t0;             // l
-                                NB[(16 + row) * NVP + v] = s1 - t1;      // H - l
-                                NB[(32 + row) * NVP + v] = s1 + t1;      // H + l
-                                NB[(48 + row) * NVP + v] = s0 - t0;      // N - l
-                            }
-                        }
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    if (node_ok) {
-                        if constexpr (MODE) emit_node(NB + lane * NVP, wsing[i], i, lon);
-                        else eval_node(NB + lane * NVP, wsing[i], true);
-                    }
-                    // the buffer is rewritten for the next latitude
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int e = 0; e < NBT; ++e) {
+                const int u = i * NBT + e;
+                if (u < SC::KT) {
+                    ga[h][e] = Gb[kb[u & 3] + min(u >> 2, kl[u & 3]) * 64];
+                    if constexpr (!TREG) ta[h][e] = tp[u * 64];
                 }
             }
+        };
+        // (the first batch is there; leaves that of (Gn, tn))
+        auto chain = [&](const double* Gb, auto tp, const double* Gn, auto tn, dbl4* sum) __attribute__((always_inline)) {
+            sum[0] = sum[1] = sum[2] = sum[3] = dbl4{0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < NBA; ++i) {
+                if (i + 1 < NBA) fetch(Gb, tp, i + 1, (i + 1) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < NBT; ++e) {
+                    const int u = i * NBT + e;
+                    if (u < SC::KT)
+                        sum[u & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[i & 1][e], TREG ? aT[TREG ? u : 0] : ta[i & 1][TREG ? 0 : e],
+                                                                          sum[u & 3], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            fetch(Gn, tn, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (TREG) {
+            for (int tile = my_tile; tile < qg.nT; tile += NW) {
+                if (qg.nT > NW) load_trig(tile);
+                const int ntp = min(qg.nTp, NW), step = NW / ntp, last = min(LB - 1, Lq.Q - b * LB);
+                int ll = wv / ntp;
+                fetch(R + min(ll, last) * gsz + boff, 0, 0, 0);
+                for (; ll <= last; ll += step) {
+                    const double wi = wsing[b * LB + ll];
+                    dbl4 sum[4];
+                    chain(R + ll * gsz + boff, 0, R + min(ll + step, last) * gsz + boff, 0, sum);
+                    nodes(ll, tile, wi, sum[0], sum[1], sum[2], sum[3]);
+                }
+            }
+        } else if (b * LB + wv <= Lq.Q) {
+            // one latitude per wave, all of its row tiles: both operands from LDS
+            const double wi = wsing[b * LB + wv];
+            const double* const Gb = R + wv * gsz + boff;
+            auto tiles = [&](auto tp) __attribute__((always_inline)) {
+                fetch(Gb, tp, 0, 0);
+                for (int tile = 0; tile < qg.nT; ++tile) {
+                    const auto tn = tp + (tile + 1 < qg.nT ? SC::KT * 64 : 0);
+                    dbl4 sum[4];
+                    chain(Gb, tp, Gb, tn, sum);
+                    nodes(wv, tile, wi, sum[0], sum[1], sum[2], sum[3]);
+                    tp = tn;
+                }
+            };
+            if (tlds) tiles((const double*)(TL + lane));
+            else tiles(gmem(Lq.afrag + lane));
         }
         // 3d. when row 0 is apart: row 0 of latitude wv of the block, phi = 0
         //     and pi take EC + OC and EC - OC, the sums of the cos rows of even
         //     and odd m; lane (column v, part) sums every fourth row, shuffles
         //     add the parts; the two records go to the row-0 area.
-        if (SC::ROW0 && qg.l0 == 1 && b * LB + wv <= Lq.Q) {
-            const double* G = R + wv * gsz + (lane & 15);
-            const int part = lane >> 4;
-            double ecs = 0.0, ocs = 0.0;
-            for (int k = 0; k < qg.nk[0]; ++k) ecs += G[(qg.base[0] + 4 * k + part) * 16];
-            for (int k = 0; k < qg.nk[2]; ++k) ocs += G[(qg.base[2] + 4 * k + part) * 16];
-            ecs += __shfl_xor(ecs, 16);
-            ecs += __shfl_xor(ecs, 32);
-            ocs += __shfl_xor(ocs, 16);
-            ocs += __shfl_xor(ocs, 32);
-            const int v = lane & 15;
-            if (part < 2 && v < NV) RZ[(2 * wv + part) * NVP + v] = part ? ecs - ocs : ecs + ocs;
-        }
+        if (SC::ROW0 && qg.l0 == 1)
+            for (int ll = wv; ll < LB && b * LB + ll <= Lq.Q; ll += NW) {
+                const double* G = R + ll * gsz + (lane & 15);
+                const int part = lane >> 4;
+                double ecs = 0.0, ocs = 0.0, ge[SC::KEC], go[SC::KEC - 1];
+#pragma unroll
+                for (int k = 0; k < SC::KEC; ++k) ge[k] = G[(qg.base[0] + 4 * min(k, qg.nk[0] - 1) + part) * 16];
+#pragma unroll
+                for (int k = 0; k < SC::KEC - 1; ++k) go[k] = G[(qg.base[2] + 4 * min(k, qg.nk[2] - 1) + part) * 16];
+#pragma unroll
+                for (int k = 0; k < SC::KEC; ++k) ecs += k < qg.nk[0] ? ge[k] : 0.0;
+#pragma unroll
+                for (int k = 0; k < SC::KEC - 1; ++k) ocs += k < qg.nk[2] ? go[k] : 0.0;
+                ecs += __shfl_xor(ecs, 16);
+                ecs += __shfl_xor(ecs, 32);
+                ocs += __shfl_xor(ocs, 16);
+                ocs += __shfl_xor(ocs, 32);
+                const int v = lane & 15;
+                if (part < 2 && v < NV) RZ[(2 * ll + part) * NVP + v] = part ? ecs - ocs : ecs + ocs;
+            }
         __syncthreads();  // Fourier blocks consumed before the next block's Legendre sums
     }
     if (SC::ROW0 && qg.l0 == 1 && nblk > 0 && wv == ((nblk - 1) & (NW - 1))) row0_eval(nblk - 1);
@@ -2686,15 +2712,19 @@ static int degree_class(int p)
 static size_t self_lds_bytes(const ehd_ctx* ctx, const std::vector<int>& drops, int nf)
 {
     // rotated coefficients first; afterwards the same memory holds the
-    // Fourier blocks of one latitude block and each wave's node buffer
+    // Fourier blocks of one latitude block, the row-0 records, the
+    // coefficients of the columns m < r and (p > 32, where it fits) the cos/sin table
     size_t best = 0;
     for (int d : drops) {
         const DropInfo& D = ctx->info[d];
         const QuarterGrid g = quarter_grid(D.p, D.nlon_s, self_row0(D.p));
         const size_t coef = (size_t)nf * ncoef(D.p) * 16;
-        const size_t work = ((size_t)kLatBlock * g.nks * 64 +
-                             (size_t)SelfClass<16>::NW * (64 * ((nf + 6) | 1) + (D.p <= 32 ? 16 : 0)) +
-                             (self_row0(D.p) ? (size_t)2 * kLatBlock * ((nf + 6) | 1) : 0)) * 8;
+        const size_t work = ((size_t)kLatBlock * self_gsz(g) +
+                             (self_row0(D.p) ? (size_t)2 * kLatBlock * ((nf + 6) | 1) : 0) +
+                             (size_t)((D.p + 1) % 4) * ((D.p + 1) / 4 + 1) * 64) * 8;
+        // (576 bytes: the kernel's reduction scratch)
+        const size_t trig = D.p > 32 ? (size_t)g.nT * SelfClass<48>::KT * 64 * 8 : 0;
+        if (work + trig + 576 <= (size_t)ctx->max_lds) best = std::max(best, work + trig);
         best = std::max(best, std::max(coef, work));
     }
     return best;
@@ -2740,8 +2770,9 @@ static int launch_self_class(ehd_ctx* ctx, int cls, const double* f, const doubl
     long long a11 = ctx->T;
     double* a13 = ctx->d_raw;
     long long a14 = 0;
+    unsigned a15 = (unsigned)(lds / 8);
     void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4, (void*)&a5, (void*)&f, (void*)&u,
-                    (void*)&s, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&a14};
+                    (void*)&s, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&a14, (void*)&a15};
     EHD_HIP(ctx, hipLaunchKernel(fn, dim3((unsigned)count), dim3(SelfClass<PMAX>::NT), args, lds, ctx->ls));
     ctx->mark_class(cls, 1);
     return EHD_OK;
@@ -3472,7 +3503,11 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
         std::vector<double> afrag;
         if (singular) {
             const QuarterGrid g = quarter_grid(pp, nl, self_row0(pp));
-            afrag.assign((size_t)g.nT * g.nks * 64, 0.0);
+            // (p > 32: the k-steps in the order of the products, zeros to the class's most)
+            using S48 = SelfClass<48>;
+            const bool pad = pp > 32;
+            const int nks = pad ? S48::KT : g.nks;
+            afrag.assign((size_t)g.nT * nks * 64, 0.0);
             const int terms[4] = {pp / 2 + 1, pp / 2, (pp + 1) / 2, (pp + 1) / 2};
             for (int t = 0; t < g.nT; ++t)
                 for (int grp = 0; grp < 4; ++grp)
@@ -3483,7 +3518,7 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
                             const int m = grp == 0 ? 2 * term : grp == 1 ? 2 * term + 2 : 2 * term + 1;
                             const bool is_cos = grp == 0 || grp == 2;
                             const double a = 2.0 * kPi * (double)((long)m * l % nl) / nl;
-                            afrag[((size_t)t * g.nks + g.base[grp] / 4 + ks) * 64 + lane] =
+                            afrag[((size_t)t * nks + (pad ? 4 * ks + grp : g.base[grp] / 4 + ks)) * 64 + lane] =
                                 is_cos ? std::cos(a) : std::sin(a);
                         }
         }
@@ -3509,29 +3544,32 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
         L.trig = dptr;
         if (singular) {
             // Legendre A fragments, per latitude block and per wave: the
-            // k-steps of the wave's degree columns (snake order, increasing
-            // m) back to back, zero-padded to the class's maximum; lane holds
-            // row lane%16 (Pbar at latitudes 0..7 of the block, then
-            // dPbar/dtheta), degree n = m + 4 ks + lane/16.
+            // k-steps of the wave's columns back to back in the slots of
+            // self_pos_off, then those of its column m < r; lane holds row
+            // lane%16 (Pbar at latitudes 0..7 of the block, then dPbar/dtheta),
+            // degree n = m + 4 k + lane/16; zero elsewhere.
             const long ncp = ncoef(pp);
-            const int nw = SelfClass<16>::NW, kw = self_kw(pp);
+            const int nw = self_nw(pp), kw = self_kw(pp), gmax = self_gmax(pp), G = (pp + 1) / 4, left = (pp + 1) % 4;
+            const int npos = nw == 4 ? gmax : gmax / 2, kws = self_pos_off(npos, nw, gmax);
             const int nblk = (Q + 1 + kLatBlock - 1) / kLatBlock;
             std::vector<double> lf((size_t)nblk * nw * kw * 64, 0.0);
             for (int bb = 0; bb < nblk; ++bb)
                 for (int w = 0; w < nw; ++w) {
-                    int t = 0;
-                    for (int m = 0; m <= pp; ++m) {
-                        if (snake_wave(m, nw) != w) continue;
-                        for (int ks = 0; ks < (pp + 1 - m + 3) / 4; ++ks, ++t)
+                    auto column = [&](int m, int t0, int steps) {
+                        for (int k = 0; k < steps; ++k)
                             for (int lane = 0; lane < 64; ++lane) {
-                                const int row = lane & 15, n = m + 4 * ks + (lane >> 4);
+                                const int row = lane & 15, n = m + 4 * k + (lane >> 4);
                                 const int lat = bb * kLatBlock + (row & 7);
                                 if (lat > Q || n > pp) continue;
                                 const std::vector<double>& tab = (row < 8) ? P : dP;
-                                lf[(((size_t)bb * nw + w) * kw + t) * 64 + lane] = tab[(size_t)lat * ncp + tri(n, m)];
+                                lf[(((size_t)bb * nw + w) * kw + t0 + k) * 64 + lane] = tab[(size_t)lat * ncp + tri(n, m)];
                             }
+                    };
+                    for (int s = 0; s < npos; ++s) {
+                        const int g = self_group(s, w, nw, gmax);
+                        if (g <= G) column(pp + 1 - 4 * g + (w & 3), self_pos_off(s, nw, gmax), g);
                     }
-                    if (t > kw) return -1;
+                    if (w < left) column(w, kws, G + 1);
                 }
             if (upload(ctx, &dptr, lf)) return -1;
             L.lfrag = dptr;
@@ -3863,9 +3901,9 @@ static ehd_ctx::KernRes kernel_res(ehd_ctx* ctx, const void* fn)
 }
 
 // Overlap mode: the degree classes below p = 48 whose blocks leave room on a
-// compute unit for one looping FP32 far-field block: each SIMD holds the
-// block's two waves of the self-interaction and one far-field wave in its
-// 512 registers per lane, and the LDS of both blocks fits the CU's.  A
+// compute unit for one looping FP32 far-field block: each SIMD holds a wave
+// of two blocks of the self-interaction and one far-field wave in its 512
+// registers per lane, and the LDS of the three blocks fits the CU's.  A
 // class without that room would have its CUs taken by the far-field blocks
 // and slow down several times over, so it runs before the fork.  Every
 // kernel the evaluation launches for the class must fit.
@@ -3879,16 +3917,17 @@ static unsigned classes_beside_far(ehd_ctx* ctx, int far_prec, unsigned kinds, b
     else if (needU) v[nv++] = {false, true, false};
     else v[nv++] = {needF, false, needLap};
     const ehd_ctx::KernRes fr = kernel_res(ctx, far32_kernel(ctx->far_tpt, kinds));
-    constexpr int self_waves = SelfClass<16>::NT / 256, far_waves = kThreads / 256;   // per SIMD
+    constexpr int self_waves = 2, far_waves = kThreads / 256;   // per SIMD
     unsigned m = 0;
     for (int c = 0; c < 3; ++c) {
         if (ctx->cls_drops[c].empty()) continue;
         bool fits = true;
         for (int i = 0; i < nv; ++i) {
+            // (two blocks of the class per compute unit)
             const ehd_ctx::KernRes sr =
                 kernel_res(ctx, self_kernel_of_class(c, v[i].hf, v[i].hu, v[i].hs, ctx->self_pf[c]));
             const int nf = 3 + (v[i].hf ? 3 : 0) + (v[i].hu ? 3 : 0) + (v[i].hs ? 1 : 0);
-            const size_t lds = self_lds_bytes(ctx, ctx->cls_drops[c], nf) + (size_t)sr.lds + (size_t)fr.lds;
+            const size_t lds = 2 * (self_lds_bytes(ctx, ctx->cls_drops[c], nf) + (size_t)sr.lds) + (size_t)fr.lds;
             fits = fits && self_waves * sr.vgpr + far_waves * fr.vgpr <= 512 && lds <= (size_t)ctx->max_lds;
         }
         if (fits) m |= 1u << c;
@@ -4123,8 +4162,9 @@ static int launch_weights(ehd_ctx* ctx, int cls, int mode, int first, int count,
     long long a11 = ctx->T;
     unsigned kinds = 0;
     double* a13 = (double*)ctx->opgrid.p;
+    unsigned a15 = (unsigned)(lds / 8);
     void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4, (void*)&a5, (void*)&none, (void*)&none,
-                    (void*)&none, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&gstride};
+                    (void*)&none, (void*)&a9, (void*)&a10, (void*)&a11, (void*)&kinds, (void*)&a13, (void*)&gstride, (void*)&a15};
     EHD_HIP(ctx, hipLaunchKernel(fn, dim3((unsigned)count), dim3(SelfClass<PMAX>::NT), args, lds, ctx->stream));
     return EHD_OK;
 }

@@ -296,7 +296,7 @@ int ehd_time_far(ehd_ctx* ctx, int far_prec, unsigned kinds, int targets_per_thr
 
 /* Self-interaction tuning (the per-target singular rule of Sec. 2.1,
  * eq. mod_weights, batched by degree class).  The class kernels stream the
- * Legendre tables of the rotated grid, pf pairs of fragments of a wave's next
+ * Legendre tables of the rotated grid, pf + 1 fragments of a wave's next
  * column ahead (the prefetch batch); each class is
  * built with three batches for the field set x, f, sigma (the kinds S, D,
  * S_L, L with u = f, and the E_n and velocity solves' field sets use the

@@ -783,11 +783,11 @@ struct SelfClass {
     // row 0 of the longitude sums may be taken apart (pays at q = 2p for
     // p = 16, 32 and 48: one tile less; elsewhere the tile count is unchanged)
     static constexpr bool ROW0 = PMAX != 24;
-    // Pairs of Legendre fragments of a wave's next column loaded before the
+    // Legendre fragments, less one, of a wave's next column loaded before the
     // products of the current one: the default and the two others built for the field set
     // x, f, sigma, among which the self-interaction autotuner picks
-    static constexpr int PF = PMAX == 48 ? 3 : PMAX == 32 ? 3 : 2;
-    static constexpr int PF_ALT0 = PMAX == 48 ? 5 : PMAX == 32 ? 2 : 3;
+    static constexpr int PF = PMAX == 48 ? 5 : PMAX == 32 ? 3 : 2;
+    static constexpr int PF_ALT0 = PMAX == 48 ? 3 : PMAX == 32 ? 2 : 3;
     static constexpr int PF_ALT1 = PMAX == 48 ? 6 : PMAX == 32 ? 5 : 4;
 };
 
@@ -1074,7 +1074,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
     };
 
     // fragments of a wave's next column loaded ahead
-    constexpr int PF = 2 * (PFT > 0 ? PFT : SC::PF);
+    constexpr int PF = 1 + (PFT > 0 ? PFT : SC::PF);
     // kernels at one node (its NV values in val: this lane's registers or its
     // row-0 record) with the modified weight wi of its latitude, accumulated
     // per lane, the kinds requested only.

@@ -1,9 +1,10 @@
 // Galerkin solvers built on the layer-potential evaluation (paper Sec. 2,
 // eq. galerkin_En and eq. BIM_galerkin): restarted GMRES in FP64 on the
-// device, whose mat-vec is one ehd_layer_potentials call followed by the
-// Galerkin projection ehd_analyze.  Orthogonalisation is classical
-// Gram-Schmidt applied twice (CGS2), with the dot products of a step batched
-// in one launch; the small Hessenberg least-squares problem (Givens
+// device, whose mat-vec is one layer-potential evaluation, its singular rule
+// by operator matrices built once per solve where their memory can be had,
+// followed by the Galerkin projection.  Orthogonalisation is classical
+// Gram-Schmidt applied twice (CGS2), the dot products of a step in one launch
+// over many blocks; the small Hessenberg least-squares problem (Givens
 // rotations) lives on the host.
 //
 // The unknowns are packed SH coefficient vectors (the layout of

@@ -1184,6 +1184,9 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
             // kept in registers over the blocks, six per column)
             int pb = p;
             asm volatile("" : "+s"(pb));
+            // A column's sums are stored in the block of code that made them: a
+            // version that carried them over a branch was compiled with 11 wait
+            // states between the last product and the copy of its result, too few.
             // this wave's columns, the one m < r second (the waves without one
             // load the first column's fragments again)
             auto slot_len = [](int i) { return i == 1 ? SC::KLO : self_pos_len(i ? i - 1 : 0, NW, SC::GMAX); };

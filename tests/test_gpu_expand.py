@@ -74,6 +74,27 @@ def test_expanded_far_field_matches_the_direct_sums(E, case):
     assert np.all(err < TOL), err
 
 
+@pytest.mark.parametrize("away", [1e3, 1e8])
+def test_suspension_far_from_the_origin(E, away):
+    """Orders up to 40 and source counts that leave a rest of 2 in the moments'
+    stages of four, with the whole suspension moved off the origin: the sums
+    stay finite and keep the accuracy that the coordinates have there.
+    Tolerance: a node's coordinates round at a few 1e-16 of `away` on either
+    side, 2e-15 away together, and the kernels' relative change is at most
+    six times that over the least distance, 0.2 radii; 1e-13 away, and TOL."""
+    s = W.suspension(24, [32], 9.0, 17)
+    ns = (s.q_far + 1) * (2 * s.q_far + 2)
+    assert np.all(ns % 4 == 2)
+    off = W.drop_offsets(s.p.astype(np.int64))
+    for d in range(s.ndrops):
+        s.xcoef[3 * off[d]:3 * off[d + 1]].reshape(3, -1)[:, 0] += np.sqrt(4.0 * np.pi) * away * np.array([1.0, -1.0, 0.5])
+    got, ref, expanded = far(E, s, E.ALL_KINDS, 200)
+    err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    print("away", away, "expanded pairs", expanded, "err", err, flush=True)
+    assert expanded > 0
+    assert np.all(err < TOL + 1e-13 * away), err
+
+
 @pytest.mark.parametrize("kinds", [1, 2, 4, 8, 16, 3, 5, 12, 18, 20, 28, 15])
 def test_every_kind_set_takes_its_own_columns(E, kinds):
     got, ref, expanded = far(E, suspension("uneven_degrees"), kinds, 60)

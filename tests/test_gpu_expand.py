@@ -95,6 +95,66 @@ def test_suspension_far_from_the_origin(E, away):
     assert np.all(err < TOL + 1e-13 * away), err
 
 
+def test_truncation_of_a_distant_pair(E):
+    """The double layer of two unit spheres 50 radii apart (order 10), densities
+    in a bump of up to degree 48 at the points that face each other, where
+    neglected orders show most (and most in this kernel), against the regular
+    rule's sums in 80 bits.  Tolerance: 4e-15 of truncation by the plan's rule;
+    5e4 terms added in tiles of 256, sqrt(256) + sqrt(203) roundings of 1.1e-16
+    for a random walk, 3.3e-15; and about ten roundings of the nodes' values,
+    1e-15.  1e-14 of the vector."""
+    import torch
+    p, q, dist = 48, 160, 50.0
+    z = np.array([0.0, 0.0, 0.5 * dist])
+    s = W.two_drops(p, 1)
+    nc = W.ncoef(p)
+    amp = np.array([0.7, -0.4, 1.0])
+    bump = [np.zeros(2 * nc) for _ in range(2)]
+    for d in range(2):
+        blk = s.xcoef[6 * nc * d:6 * nc * (d + 1)].reshape(3, -1)
+        blk[:, 0] = np.sqrt(4.0 * np.pi) * (z if d else -z)
+        for n in range(p + 1):
+            e = np.sqrt((2 * n + 1) / (4.0 * np.pi)) * np.exp(-(n / 24.0) ** 2)
+            bump[d][2 * W.tri(n, 0)] = e * ((-1) ** n if d else 1)
+    s.fcoef = np.concatenate([a * b for b in bump for a in amp])
+    s.q_self[:] = p
+    s.q_far[:] = q
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    ctx.set_drops(s.p, s.q_self, s.q_far, 0, torch.from_numpy(s.xcoef).to(dev))
+    assert ctx.far_plan() == (0, 2)
+    so = torch.zeros(3, ctx.ntargets, dtype=torch.float64, device=dev)
+    fo = torch.zeros_like(so)
+    ctx.layer_potentials(None, torch.from_numpy(s.fcoef).to(dev), None, E.STOKES_DL, E.FAR_FP64, so, fo)
+    ctx.sync()
+    nlon = 2 * p + 2
+    node = np.array([0, 5, nlon + 17, 3 * nlon + 40, 10 * nlon, 20 * nlon + 9, 40 * nlon + 60])
+    got = fo.cpu().numpy()[:, node]                          # drop 0: the pole theta = 0 faces drop 1
+    ctx.close()
+
+    ld = np.longdouble
+    x0, _ = oracle.targets(s, np.zeros(len(node), np.int32), node.astype(np.int32))
+    x0 = x0.astype(ld) + z[:, None]
+    x0 = x0 / np.sqrt((x0 ** 2).sum(0)) - z[:, None]         # on the unit sphere about -z
+    ct, w = oracle.gauss_legendre(q + 1)
+    ct, ph = ct.astype(ld), 2 * ld(np.pi) * np.arange(2 * q + 2).astype(ld) / (2 * q + 2)
+    st = np.sqrt(1 - ct * ct)
+    nrm = np.stack([np.outer(st, np.cos(ph)), np.outer(st, np.sin(ph)), np.outer(ct, np.ones_like(ph))]).reshape(3, -1)
+    pn, pm, val = ct * 0 + 1, ct * 0, ct * 0                 # bump of drop 1: about the direction -z
+    for n in range(p + 1):
+        val = val + (2 * n + 1) / (4 * ld(np.pi)) * np.exp(-(ld(n) / 24) ** 2) * (-1) ** n * pn
+        pn, pm = ((2 * n + 1) * ct * pn - n * pm) / (n + 1), pn
+    dens = np.repeat(val * w.astype(ld) * 2 * ld(np.pi) / (2 * q + 2), 2 * q + 2)
+    ref = np.zeros((3, len(node)), ld)
+    for k in range(len(node)):
+        h = x0[:, k:k + 1] - (nrm + z[:, None])
+        r = np.sqrt((h * h).sum(0))
+        ref[:, k] = (-6 * h * (amp.astype(ld) @ h) * (h * nrm).sum(0) / r ** 5 * dens).sum(1)
+    ref /= 4 * ld(np.pi)
+    err = float(np.abs(got - ref).max() / np.abs(ref).max())
+    print("distant pair err", err, flush=True)
+    assert err < 1e-14, err
+
+
 @pytest.mark.parametrize("kinds", [1, 2, 4, 8, 16, 3, 5, 12, 18, 20, 28, 15])
 def test_every_kind_set_takes_its_own_columns(E, kinds):
     got, ref, expanded = far(E, suspension("uneven_degrees"), kinds, 60)

@@ -3382,9 +3382,18 @@ static int plan_far(ehd_ctx* ctx, const std::vector<double>& rad)
             const size_t first = runs[s].size();
             off[s].push_back((int)first);
             while (t >= drops[lo].toff + drops[lo].nt) ++lo;
+            if (!on) {                                 // every tile but the own ones of a block on one drop
+                const bool one = drops[lo].toff + drops[lo].nt >= std::min(ctx->T, t + step);
+                const int own = one ? (int)((drops[lo].ns + kTile - 1) / kTile) : 0;
+                const int before = one ? (int)(drops[lo].soff / kTile) : ctx->ntiles;
+                if (before > 0) runs[s].push_back(make_int2(0, 0));
+                if (before + own < ctx->ntiles) runs[s].push_back(make_int2(before + own, before));
+                runs[s].push_back(make_int2(0, ctx->ntiles - own));
+                continue;
+            }
             std::fill(any.begin(), any.end(), 0);
             for (int i = lo; i < nd && drops[i].toff < std::min(ctx->T, t + step); ++i)
-                for (int j = 0; j < nd; ++j) any[j] |= (unsigned char)(i != j && (!on || near[(size_t)i * nd + j]));
+                for (int j = 0; j < nd; ++j) any[j] |= (unsigned char)(i != j && near[(size_t)i * nd + j]);
             int at = 0;
             for (int j = 0; j < nd; ++j) {
                 if (!any[j]) continue;

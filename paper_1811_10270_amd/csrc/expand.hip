@@ -26,6 +26,8 @@
 
 #include <algorithm>
 #include <cmath>
+#include <map>
+#include <utility>
 
 #include "ehdbim.h"
 
@@ -650,14 +652,20 @@ constexpr int kMaxDrops = 4096;        // more drops than this keep the direct s
 // relative to 6 / distance^2, evaluated in 80 bits: 2.8e-15 at rho = 0.1
 // (N = 17), 1.9e-15 at 0.05 (13), 0.9e-15 at 0.02 (10); with rho^(N+1) in the
 // rule it was 2.5e-14, 3.3e-14 and 4.0e-14.
-int order_for(double rho)
-{
-    if (!(rho >= 0.0) || rho > 0.5) return -1;
-    double p = rho * rho * rho;
-    for (int N = 3; N <= kOrder; ++N, p *= rho)
-        if ((N + 2.0) * (N + 2.0) * p <= 4e-15) return N;
-    return -1;
-}
+// The rule is kept solved for rho.
+struct OrderLimits {
+    double rho[kOrder + 1];                                  // largest rho of each order
+    OrderLimits()
+    {
+        for (int N = 0; N <= kOrder; ++N) rho[N] = N < 3 ? 0.0 : std::pow(4e-15 / ((N + 2.0) * (N + 2.0)), 1.0 / N);
+    }
+    int order(double r) const                                // smallest order for r, -1: none
+    {
+        if (!(r >= 0.0)) return -1;
+        const double* const p = std::lower_bound(rho + 3, rho + kOrder + 1, r);
+        return p == rho + kOrder + 1 ? -1 : (int)(p - rho);
+    }
+};
 
 template <typename T>
 hipError_t put(ehd::Expand::Buf& b, const std::vector<T>& v, hipStream_t st)
@@ -682,24 +690,81 @@ hipError_t expand_plan(Expand& E, const std::vector<ExpandDrop>& drops, hipStrea
     E.unit = std::exp2(std::ceil(std::log2(rmax)));
     if (!(E.unit > 1e-100) || !(E.unit < 1e100)) return hipSuccess;
 
-    // pairs: expanded where separated and cheaper than the direct sum.  Costs
-    // in cycles of one compute unit, as measured on 256 drops of p = 32
-    // (kCost*).
+    // nothing to gain where all pairs together are cheap
+    double nts = 0.0, nss = 0.0, own = 0.0;
+    for (const ExpandDrop& d : drops) {
+        nts += (double)d.nt;
+        nss += (double)d.ns;
+        own += (double)d.nt * (double)d.ns;
+    }
+    if (!(kCostDirect * (nts * nss - own) > kCostFixed)) return hipSuccess;
+
+    // pairs: expanded where separated and cheaper than the direct sum.  A plan
+    // is made for every shape, so most pairs that stay direct are told by one
+    // comparison: the order up to which a translation is cheaper than the
+    // pair's sum follows from the node counts (few different ones), and with it
+    // the least distance.  Whole rows fall by the farthest corner of the centres'
+    // box (4000 drops of p = 4, nothing to expand: 400 ms with a search of the
+    // order per pair).
+    static const OrderLimits limits;
+    std::vector<int> kind(nd);
+    std::vector<std::pair<long long, long long>> kinds;      // (nt, ns)
+    std::vector<double> smallest;                            // least source radius of a kind
+    {
+        std::map<std::pair<long long, long long>, int> seen;
+        for (int d = 0; d < nd; ++d) {
+            const auto at = seen.emplace(std::make_pair(drops[d].nt, drops[d].ns), (int)kinds.size());
+            if (at.second) {
+                kinds.push_back(at.first->first);
+                smallest.push_back(drops[d].rs);
+            }
+            kind[d] = at.first->second;
+            smallest[kind[d]] = std::min(smallest[kind[d]], drops[d].rs);
+        }
+    }
+    auto m2l_cost = [](int N) { return kCostPair * (double)ncf(N) * ncf(N) + 2000.0; };
+    double lo[3], hi[3];
+    bool boxed = true;
+    for (int c = 0; c < 3; ++c) {
+        lo[c] = hi[c] = drops[0].c[c];
+        for (const ExpandDrop& d : drops) {
+            lo[c] = std::min(lo[c], d.c[c]);
+            hi[c] = std::max(hi[c], d.c[c]);
+            boxed = boxed && std::isfinite(d.c[c]);
+        }
+    }
     E.near.assign((size_t)nd * nd, 1);
     std::vector<int2> orders(nd, make_int2(-1, -1));
     std::vector<std::vector<ExpandPair>> lists(nd);
+    std::vector<double> inv(kinds.size());                   // 1 / rho of a kind's largest order, 0: none
     double gain = 0.0;
-    for (int i = 0; i < nd; ++i)
+    for (int i = 0; i < nd; ++i) {
+        const ExpandDrop& A = drops[i];
+        double least = HUGE_VAL, far2 = 0.0;
+        for (size_t k = 0; k < kinds.size(); ++k) {
+            const double direct = kCostDirect * (double)A.nt * (double)kinds[k].second;
+            int N = kOrder;
+            while (N >= 3 && !(m2l_cost(N) < direct)) --N;
+            inv[k] = N < 3 ? 0.0 : 1.0 / limits.rho[N];
+            if (inv[k] > 0.0) least = std::min(least, A.rt + smallest[k] * inv[k]);
+        }
+        for (int c = 0; c < 3; ++c) {
+            const double d = std::max(A.c[c] - lo[c], hi[c] - A.c[c]);
+            far2 += d * d;
+        }
+        if (least == HUGE_VAL || (boxed && far2 < least * least * (1.0 - 1e-9))) continue;
         for (int j = 0; j < nd; ++j) {
-            if (i == j) continue;
-            const ExpandDrop &A = drops[i], &B = drops[j];
+            const ExpandDrop& B = drops[j];
+            const double q = inv[kind[j]];
+            if (i == j || !(q > 0.0)) continue;
             const double dx = A.c[0] - B.c[0], dy = A.c[1] - B.c[1], dz = A.c[2] - B.c[2];
-            const double dist = std::sqrt(dx * dx + dy * dy + dz * dz);
+            const double d2 = dx * dx + dy * dy + dz * dz, need = std::max(A.rt + B.rs * q, B.rs + A.rt * q);
+            if (!(d2 >= need * need * (1.0 - 1e-9))) continue;
+            const double dist = std::sqrt(d2);
             if (!std::isfinite(dist) || !(dist - A.rt > 0.0) || !(dist - B.rs > 0.0) || dist < 0.25 * E.unit) continue;
-            const int N = order_for(std::max(B.rs / (dist - A.rt), A.rt / (dist - B.rs)));
+            const int N = limits.order(std::max(B.rs / (dist - A.rt), A.rt / (dist - B.rs)));
             if (N < 0) continue;
-            const double direct = kCostDirect * (double)A.nt * (double)B.ns;
-            const double m2l = kCostPair * (double)ncf(N) * ncf(N) + 2000.0;
+            const double direct = kCostDirect * (double)A.nt * (double)B.ns, m2l = m2l_cost(N);
             if (m2l >= direct) continue;
             gain += direct - m2l;
             E.near[(size_t)i * nd + j] = 0;
@@ -707,6 +772,7 @@ hipError_t expand_plan(Expand& E, const std::vector<ExpandDrop>& drops, hipStrea
             orders[i].y = std::max(orders[i].y, N);
             orders[j].x = std::max(orders[j].x, N);
         }
+    }
     int nsrc = 0;
     long long most = 0;
     for (int d = 0; d < nd; ++d) {

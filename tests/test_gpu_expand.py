@@ -193,3 +193,46 @@ def test_plan_follows_the_shape_and_replays(E):
             _ = (out[1] * 2.0).sum().item()       # eager work between replays
     ctx.set_graph(False)
     ctx.close()
+
+
+def lattice(nd, p, spacing=2.6):
+    """nd copies of one drop on a cubic lattice."""
+    one, k = W.single_drop(p=p), int(np.ceil(nd ** (1.0 / 3.0)))
+    x = np.tile(one.xcoef, nd).reshape(nd, 3, -1)
+    for c in range(3):
+        x[:, c, 0] += np.sqrt(4.0 * np.pi) * spacing * ((np.arange(nd) // k ** c) % k)
+    ps = np.full(nd, p, np.int32)
+    return W.Suspension("lattice", ps, 2 * ps, 2 * ps, 0, x.ravel(), np.tile(one.fcoef, nd), np.tile(one.sigcoef, nd))
+
+
+@pytest.mark.parametrize("nd, p", [(1100, 2), (1100, 8)])     # without and with expansions
+def test_more_drops_than_tile_lists_are_kept_for(E, nd, p):
+    s = lattice(nd, p)
+    got, ref, expanded = far(E, s, E.ALL_KINDS, 60)
+    err = np.abs(got - ref).max(axis=1) / np.abs(ref).max(axis=1)
+    print(nd, p, "expanded pairs", expanded, "err", err, flush=True)
+    assert (expanded > 0) == (p == 8)
+    assert np.all(err < TOL), err
+
+
+def test_plan_of_many_small_drops_costs_little(E):
+    """No pair of drops of p = 2 is worth a translation: a new shape's time grows
+    with the drops (4 times as many: 4.0 times as long without a plan), not
+    with their pairs (16 times)."""
+    import time
+    import torch
+    best = []
+    for nd in (1000, 4000):
+        s = lattice(nd, 2)
+        ctx, x = E.Context(0), torch.from_numpy(s.xcoef).to("cuda:0")
+        ctx.set_drops(s.p, s.q_self, s.q_far, 0, x)
+        assert ctx.far_plan()[1] == 0
+        took = []
+        for _ in range(4):
+            t0 = time.perf_counter()
+            ctx.update_shape(x)
+            took.append(time.perf_counter() - t0)
+        best.append(min(took))
+        ctx.close()
+    print("update_shape", best, flush=True)
+    assert best[1] < 6.0 * best[0], best

@@ -648,16 +648,17 @@ constexpr int kMaxDrops = 4096;        // more drops than this keep the direct s
 // terms of a potential are below rho^(N+1).  The Stokes double layer adds a
 // dipole's and a gradient's derivative, (N+2)^2 together, and in Phi_3 the
 // factor y, as large as the distance of the drops, which takes one power of
-// rho back.  Its largest error over 1, 0.2 and 5 as ratios of the radii,
-// relative to 6 / distance^2, evaluated in 80 bits: 2.8e-15 at rho = 0.1
-// (N = 17), 1.9e-15 at 0.05 (13), 0.9e-15 at 0.02 (10); with rho^(N+1) in the
-// rule it was 2.5e-14, 3.3e-14 and 4.0e-14.
+// rho back: (N+2)^2 rho^N <= 1e-14.  Evaluated in 80 bits where that is an
+// equality, radii alike or 1 to 5, worst places: D 6e-15 (N = 6) to 9e-15 (24)
+// of 6 / distance^2, the other kernels below 1.5e-15 of theirs; the direct sums
+// of a distant pair, whose 2/r has one Newton step, are 3e-14 off in D.
+// (4e-15 instead: orders half a one higher, 256 drops of p = 32 1% longer.)
 // The rule is kept solved for rho.
 struct OrderLimits {
     double rho[kOrder + 1];                                  // largest rho of each order
     OrderLimits()
     {
-        for (int N = 0; N <= kOrder; ++N) rho[N] = N < 3 ? 0.0 : std::pow(4e-15 / ((N + 2.0) * (N + 2.0)), 1.0 / N);
+        for (int N = 0; N <= kOrder; ++N) rho[N] = N < 3 ? 0.0 : std::pow(1e-14 / ((N + 2.0) * (N + 2.0)), 1.0 / N);
     }
     int order(double r) const                                // smallest order for r, -1: none
     {

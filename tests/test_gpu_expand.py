@@ -99,7 +99,7 @@ def test_truncation_of_a_distant_pair(E):
     """The double layer of two unit spheres 50 radii apart (order 10), densities
     in a bump of up to degree 48 at the points that face each other, where
     neglected orders show most (and most in this kernel), against the regular
-    rule's sums in 80 bits.  Tolerance: 4e-15 of truncation by the plan's rule;
+    rule's sums in 80 bits.  Tolerance: 4e-15 of truncation (order 10 here);
     5e4 terms added in tiles of 256, sqrt(256) + sqrt(203) roundings of 1.1e-16
     for a random walk, 3.3e-15; and about ten roundings of the nodes' values,
     1e-15.  1e-14 of the vector."""

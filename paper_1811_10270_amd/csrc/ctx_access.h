@@ -19,6 +19,14 @@ int ehd_ctx_graph_on(const ehd_ctx* ctx);
 int ehd_ctx_matrices(ehd_ctx* ctx, unsigned kind, bool* ready);
 int ehd_ctx_matrix_potential(ehd_ctx* ctx, const double* in, int far_prec, double* out);
 void ehd_ctx_matrices_done(ehd_ctx* ctx, bool all);
+// hipMalloc for a call's workspace; if it fails, once more after the matrices
+// kept from an earlier solve have given their memory back.
+hipError_t ehd_ctx_malloc_bytes(ehd_ctx* ctx, void** p, size_t bytes);
+template <typename T>
+hipError_t ehd_ctx_malloc(ehd_ctx* ctx, T** p, size_t bytes)
+{
+    return ehd_ctx_malloc_bytes(ctx, (void**)p, bytes);
+}
 // The Laplace-Beltrami operator on the current surfaces as five coefficients
 // per target node, geo[5][T] (of g_tt, g_tp, g_pp, g_t, g_p), and its values of
 // one packed field from them, lap[T].

@@ -51,6 +51,7 @@ constexpr int kMaxListDrops = 1024;    // far field: most drops for tile lists w
 constexpr long long kOpGrid = 1LL << 30;           // operator matrices: bytes of rotated-grid weights at a time
 constexpr int kOpGroup = 8;                        // targets per group of one weight field
 constexpr size_t kOpKeep = (size_t)2 << 30;        // and the most memory kept from solve to solve
+constexpr size_t kOpSpare = (size_t)256 << 20;     // device memory they leave free (a first launch's scratch, other users)
 
 // ---------------------------------------------------------------------------
 // Device-side descriptors
@@ -2884,7 +2885,7 @@ template <typename T>
 static int near_upload(ehd_ctx* ctx, T** out, const std::vector<T>& h, std::vector<void*>* owner = nullptr)
 {
     void* p = nullptr;
-    EHD_HIP(ctx, hipMalloc(&p, sizeof(T) * std::max<size_t>(h.size(), 1)));
+    EHD_HIP(ctx, ehd_ctx_malloc(ctx, &p, sizeof(T) * std::max<size_t>(h.size(), 1)));
     (owner ? owner : &ctx->near.allocs)->push_back(p);
     if (!h.empty())
         EHD_HIP(ctx, hipMemcpyAsync(p, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice, ctx->stream));
@@ -2896,7 +2897,7 @@ static int near_upload(ehd_ctx* ctx, T** out, const std::vector<T>& h, std::vect
 static int near_zeros(ehd_ctx* ctx, double** out, size_t n)
 {
     void* p = nullptr;
-    EHD_HIP(ctx, hipMalloc(&p, sizeof(double) * std::max<size_t>(n, 1)));
+    EHD_HIP(ctx, ehd_ctx_malloc(ctx, &p, sizeof(double) * std::max<size_t>(n, 1)));
     ctx->near.allocs.push_back(p);
     EHD_HIP(ctx, hipMemsetAsync(p, 0, sizeof(double) * std::max<size_t>(n, 1), ctx->stream));
     *out = (double*)p;
@@ -4272,6 +4273,15 @@ int ehd_ctx_matrices(ehd_ctx* ctx, unsigned kind, bool* ready)
         gbytes = std::max(gbytes, sizeof(double) * (size_t)P.gstride * P.batch * per);
         cbytes = std::max(cbytes, sizeof(double) * (size_t)P.cstride * P.batch * per);
     }
+    // what they grow by has to leave the device kOpSpare
+    size_t grow = 0, free_bytes = 0, all_bytes = 0;
+    for (const auto& w : {std::make_pair(&ctx->opmat, total), std::make_pair(&ctx->opgrid, gbytes),
+                          std::make_pair(&ctx->opcoef, cbytes)})
+        if (w.second > w.first->cap) grow += w.second - w.first->cap;
+    if (e == hipSuccess && grow) {
+        e = hipMemGetInfo(&free_bytes, &all_bytes);
+        if (e == hipSuccess && grow + kOpSpare > free_bytes) e = hipErrorOutOfMemory;
+    }
     if (e == hipSuccess) e = ehd::ensure(ctx->opmat, total);
     if (e == hipSuccess) e = ehd::ensure(ctx->opgrid, gbytes);
     if (e == hipSuccess) e = ehd::ensure(ctx->opcoef, cbytes);
@@ -4323,6 +4333,17 @@ int ehd_ctx_matrix_potential(ehd_ctx* ctx, const double* in, int far_prec, doubl
     const bool lap = ctx->opkind == EHD_LAP_DLADJ;
     ctx->ls = ctx->stream;
     return enqueue_evaluation(ctx, nullptr, lap ? nullptr : in, lap ? in : nullptr, ctx->opkind, far_prec, out, nullptr, true);
+}
+
+hipError_t ehd_ctx_malloc_bytes(ehd_ctx* ctx, void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !ctx->opkind && ctx->opmat.p) {
+        (void)hipGetLastError();
+        ehd_ctx_matrices_done(ctx, true);
+        e = hipMalloc(p, bytes);
+    }
+    return e;
 }
 
 // The matrices are not needed any more; large ones give their memory back.

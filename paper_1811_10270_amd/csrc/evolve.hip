@@ -117,7 +117,7 @@ struct Work {
 
 int alloc(ehd_ctx* ctx, Buf& b, long long n)
 {
-    EVO_HIP(hipMalloc(&b.p, sizeof(double) * (size_t)std::max(n, 1LL)));
+    EVO_HIP(ehd_ctx_malloc(ctx, &b.p, sizeof(double) * (size_t)std::max(n, 1LL)));
     return EHD_OK;
 }
 

@@ -17,7 +17,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
-#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -301,8 +300,6 @@ struct DevBuf {
         }                                                                                            \
     } while (0)
 
-using Op = std::function<int(const double* in, double* out)>;
-
 // Workspace of one GMRES(m) solve of vectors of length n.  Device: the
 // Krylov basis V [(m+1) n], w [n] and hd [2m+3] (the projections of the
 // two Gram-Schmidt passes and |w|^2); host: the Hessenberg matrix
@@ -425,19 +422,26 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
     }
 }
 
-// GMRES(m) with its workspace allocated for the call.
-int gmres(ehd_ctx* ctx, long long n, const Op& A, const double* b, double* x, int m, int maxit, double tol,
-          int* iters, double* relres)
-{
+// Workspace of one call, allocated before any operator matrices, which take
+// memory only where it is left over.
+struct GmresBuffers {
     DevBuf Vb, wb, hb;
-    SOLVE_HIP(hipMalloc(&Vb.p, sizeof(double) * (size_t)(m + 1) * n));
-    SOLVE_HIP(hipMalloc(&wb.p, sizeof(double) * (size_t)n));
-    // hd: first-pass projections [0, m], second-pass [m + 1, 2m + 1], |w|^2 at 2m + 2
-    SOLVE_HIP(hipMalloc(&hb.p, sizeof(double) * (size_t)(2 * m + 3)));
-    std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), h(m + 1), y(m), hh(2 * m + 3);
-    const GmresWork ws{Vb.p, wb.p, hb.p, H.data(), cs.data(), sn.data(), g.data(), h.data(), y.data(), hh.data()};
-    return gmres_ws(ctx, n, A, b, x, m, maxit, tol, ws, iters, relres);
-}
+    std::vector<double> H, cs, sn, g, h, y, hh;
+    GmresWork ws{};
+    int alloc(ehd_ctx* ctx, long long n, int m)
+    {
+        SOLVE_HIP(ehd_ctx_malloc(ctx, &Vb.p, sizeof(double) * (size_t)(m + 1) * n));
+        SOLVE_HIP(ehd_ctx_malloc(ctx, &wb.p, sizeof(double) * (size_t)n));
+        // hd: first-pass projections [0, m], second-pass [m + 1, 2m + 1], |w|^2 at 2m + 2
+        SOLVE_HIP(ehd_ctx_malloc(ctx, &hb.p, sizeof(double) * (size_t)(2 * m + 3)));
+        H.resize((size_t)(m + 1) * m);
+        for (std::vector<double>* v : {&cs, &sn, &y}) v->resize(m);
+        for (std::vector<double>* v : {&g, &h}) v->resize(m + 1);
+        hh.resize(2 * m + 3);
+        ws = {Vb.p, wb.p, hb.p, H.data(), cs.data(), sn.data(), g.data(), h.data(), y.data(), hh.data()};
+        return EHD_OK;
+    }
+};
 
 // A solve's operator matrices (ehd_ctx_matrices), where its mat-vecs repay
 // them: they cost about as much as one evaluation (K*) or two (D), so a solve
@@ -494,6 +498,8 @@ int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, in
     SOLVE_HIP(hipGetLastError());
     // operator E -> E/2 - (R-1)/(R+1) P[K*[E]]
     const double c = (R - 1.0) / (R + 1.0);
+    GmresBuffers own;
+    if (!ws && (rc = own.alloc(ctx, n, restart))) return rc;
     Matrices mats(ctx);
     if (!ws && (rc = mats.build(EHD_LAP_DLADJ, maxit))) return rc;
     auto A = [&](const double* in, double* out) -> int {
@@ -505,8 +511,7 @@ int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, in
         SOLVE_HIP(hipGetLastError());
         return EHD_OK;
     };
-    if (ws) return gmres_ws(ctx, n, A, rhs, en_coef_d, restart, maxit, tol, *ws, iters, relres);
-    return gmres(ctx, n, Op(A), rhs, en_coef_d, restart, maxit, tol, iters, relres);
+    return gmres_ws(ctx, n, A, rhs, en_coef_d, restart, maxit, tol, ws ? *ws : own.ws, iters, relres);
 }
 
 // Allocation-free E_n solve: its workspace lives in `scratch`, one array per
@@ -554,9 +559,9 @@ int ehd_solve_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int
     long long T, n;
     if ((rc = ehd_num_targets(ctx, &T)) || (rc = ehd_num_coefs(ctx, &n))) return rc;
     DevBuf grid, rhs, geo;
-    SOLVE_HIP(hipMalloc(&grid.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&rhs.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&geo.p, sizeof(double) * (size_t)6 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &grid.p, sizeof(double) * (size_t)T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &rhs.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &geo.p, sizeof(double) * (size_t)6 * T));
     return solve_En_impl(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, grid.p, rhs.p,
                          geo.p, nullptr);
 }
@@ -618,15 +623,17 @@ int ehd_solve_velocity(ehd_ctx* ctx, double lambda, const double* fcoef_d, int f
     const long long n = 3 * nc;
     hipStream_t st = ehd_ctx_stream(ctx);
     DevBuf grid, rhs;
-    SOLVE_HIP(hipMalloc(&grid.p, sizeof(double) * (size_t)3 * T));
-    SOLVE_HIP(hipMalloc(&rhs.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &grid.p, sizeof(double) * (size_t)3 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &rhs.p, sizeof(double) * (size_t)n));
     // right-hand side P[S[f]]
     if ((rc = ehd_layer_potentials(ctx, fcoef_d, nullptr, nullptr, EHD_STOKES_SL, far_prec, grid.p, nullptr))) return rc;
     if ((rc = ehd_analyze(ctx, 3, grid.p, rhs.p))) return rc;
     // operator u -> (lambda+1) u - (lambda-1) P[D[u]]
+    GmresBuffers work;
+    if ((rc = work.alloc(ctx, n, restart))) return rc;
     Matrices mats(ctx);
     if ((rc = mats.build(EHD_STOKES_DL, maxit))) return rc;
-    const Op A = [&](const double* in, double* out) -> int {
+    auto A = [&](const double* in, double* out) -> int {
         int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid.p)
                         : ehd_layer_potentials(ctx, nullptr, in, nullptr, EHD_STOKES_DL, far_prec, grid.p, nullptr);
         if (!r) r = ehd_analyze(ctx, 3, grid.p, out);
@@ -635,7 +642,7 @@ int ehd_solve_velocity(ehd_ctx* ctx, double lambda, const double* fcoef_d, int f
         SOLVE_HIP(hipGetLastError());
         return EHD_OK;
     };
-    return gmres(ctx, n, A, rhs.p, ucoef_d, restart, maxit, tol, iters, relres);
+    return gmres_ws(ctx, n, A, rhs.p, ucoef_d, restart, maxit, tol, work.ws, iters, relres);
 }
 
 int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* gamma_coef_d, double* en_coef_d,
@@ -661,14 +668,14 @@ int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* ga
     if ((rc = ehd_num_targets(ctx, &T)) || (rc = ehd_num_coefs(ctx, &nc))) return rc;
     hipStream_t st = ehd_ctx_stream(ctx);
     DevBuf q, val, geo, H, gq, gG, En, Gm, ft, fc;
-    SOLVE_HIP(hipMalloc(&q.p, sizeof(double) * (size_t)nc));
-    SOLVE_HIP(hipMalloc(&val.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&geo.p, sizeof(double) * (size_t)6 * T));
-    SOLVE_HIP(hipMalloc(&H.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&gq.p, sizeof(double) * (size_t)3 * T));
-    SOLVE_HIP(hipMalloc(&En.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&ft.p, sizeof(double) * (size_t)3 * T));
-    SOLVE_HIP(hipMalloc(&fc.p, sizeof(double) * (size_t)3 * nc));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &q.p, sizeof(double) * (size_t)nc));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &val.p, sizeof(double) * (size_t)T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &geo.p, sizeof(double) * (size_t)6 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &H.p, sizeof(double) * (size_t)T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &gq.p, sizeof(double) * (size_t)3 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &En.p, sizeof(double) * (size_t)T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &ft.p, sizeof(double) * (size_t)3 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &fc.p, sizeof(double) * (size_t)3 * nc));
     // ii-iii. tangential field: the surface potential phi_inf + S_L[q],
     // q = [[E_n]] = (1 - 1/R) E_n, projected; its surface gradient
     hipLaunchKernelGGL(k_axpby, dim3(nblocks(nc)), dim3(kT), 0, st, 1.0 - 1.0 / prm->R, en_coef_d, 0.0, q.p, nc);
@@ -681,8 +688,8 @@ int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* ga
     const double* gG_ptr = nullptr;
     const double* Gm_ptr = nullptr;
     if (gamma_coef_d && prm->eos != EHD_EOS_CLEAN) {
-        SOLVE_HIP(hipMalloc(&gG.p, sizeof(double) * (size_t)3 * T));
-        SOLVE_HIP(hipMalloc(&Gm.p, sizeof(double) * (size_t)T));
+        SOLVE_HIP(ehd_ctx_malloc(ctx, &gG.p, sizeof(double) * (size_t)3 * T));
+        SOLVE_HIP(ehd_ctx_malloc(ctx, &Gm.p, sizeof(double) * (size_t)T));
         if ((rc = ehd_surface(ctx, 1, gamma_coef_d, H.p, gG.p, nullptr))) return rc;
         if ((rc = ehd_synthesize(ctx, 1, gamma_coef_d, Gm.p))) return rc;
         gG_ptr = gG.p;
@@ -734,15 +741,15 @@ int ehd_solve_surfactant(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
         off[d + 1] = off[d] + (long long)(p + 1) * (p + 2);
     }
     DevBuf lap, geo, proj, tmp, di, df, kd, offb, kb;
-    SOLVE_HIP(hipMalloc(&lap.p, sizeof(double) * (size_t)T));
-    SOLVE_HIP(hipMalloc(&geo.p, sizeof(double) * (size_t)5 * T));
-    SOLVE_HIP(hipMalloc(&proj.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&tmp.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&di.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&df.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&kd.p, sizeof(double) * (size_t)n));
-    SOLVE_HIP(hipMalloc(&offb.p, sizeof(long long) * off.size()));
-    SOLVE_HIP(hipMalloc(&kb.p, sizeof(double) * (size_t)nd));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &lap.p, sizeof(double) * (size_t)T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &geo.p, sizeof(double) * (size_t)5 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &proj.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &tmp.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &di.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &df.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &kd.p, sizeof(double) * (size_t)n));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &offb.p, sizeof(long long) * off.size()));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &kb.p, sizeof(double) * (size_t)nd));
     SOLVE_HIP(hipMemcpyAsync(offb.p, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice, st));
     SOLVE_HIP(hipMemcpyAsync(kb.p, kappa_h, sizeof(double) * nd, hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_diag, dim3(nd), dim3(kT), 0, st, reinterpret_cast<const long long*>(offb.p), kb.p, precond, kd.p,
@@ -751,7 +758,7 @@ int ehd_solve_surfactant(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     // the shapes' part of the Laplace-Beltrami operator, once per solve
     if ((rc = ehd_ctx_lap_geometry(ctx, geo.p))) return rc;
     // operator c -> c - kappa P[Lap_S c], applied to M^{-1} y (right preconditioning)
-    const Op A = [&](const double* in, double* out) -> int {
+    auto A = [&](const double* in, double* out) -> int {
         hipLaunchKernelGGL(k_mul, dim3(nblocks(n)), dim3(kT), 0, st, di.p, in, tmp.p, n);
         int r = ehd_ctx_lap_values(ctx, geo.p, tmp.p, lap.p);
         if (!r) r = ehd_analyze(ctx, 1, lap.p, out);
@@ -763,7 +770,9 @@ int ehd_solve_surfactant(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     // y0 = M c0, solve, c = M^{-1} y
     hipLaunchKernelGGL(k_mul, dim3(nblocks(n)), dim3(kT), 0, st, df.p, gamma_d, gamma_d, n);
     SOLVE_HIP(hipGetLastError());
-    if ((rc = gmres(ctx, n, A, rhs_d, gamma_d, restart, maxit, tol, iters, relres))) return rc;
+    GmresBuffers work;
+    if ((rc = work.alloc(ctx, n, restart))) return rc;
+    if ((rc = gmres_ws(ctx, n, A, rhs_d, gamma_d, restart, maxit, tol, work.ws, iters, relres))) return rc;
     hipLaunchKernelGGL(k_mul, dim3(nblocks(n)), dim3(kT), 0, st, di.p, gamma_d, gamma_d, n);
     SOLVE_HIP(hipGetLastError());
     SOLVE_HIP(hipStreamSynchronize(st));
@@ -792,8 +801,8 @@ int ehd_surfactant_guess(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     SOLVE_HIP(hipSetDevice(ehd_ctx_device(ctx)));
     hipStream_t st = ehd_ctx_stream(ctx);
     DevBuf offb, kb;
-    SOLVE_HIP(hipMalloc(&offb.p, sizeof(long long) * off.size()));
-    SOLVE_HIP(hipMalloc(&kb.p, sizeof(double) * kv.size()));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &offb.p, sizeof(long long) * off.size()));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &kb.p, sizeof(double) * kv.size()));
     SOLVE_HIP(hipMemcpyAsync(offb.p, off.data(), sizeof(long long) * off.size(), hipMemcpyHostToDevice, st));
     SOLVE_HIP(hipMemcpyAsync(kb.p, kv.data(), sizeof(double) * kv.size(), hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_guess, dim3(nd), dim3(kT), 0, st, reinterpret_cast<const long long*>(offb.p), kb.p, rhs_d,
@@ -820,8 +829,8 @@ int ehd_learned_features(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     SOLVE_HIP(hipSetDevice(ehd_ctx_device(ctx)));
     hipStream_t st = ehd_ctx_stream(ctx);
     DevBuf x, kb;
-    SOLVE_HIP(hipMalloc(&x.p, sizeof(double) * (size_t)3 * nc * nd));
-    SOLVE_HIP(hipMalloc(&kb.p, sizeof(double) * (size_t)nd));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &x.p, sizeof(double) * (size_t)3 * nc * nd));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &kb.p, sizeof(double) * (size_t)nd));
     int rc = ehd_drop_coefs(ctx, x.p);
     if (rc) return rc;
     SOLVE_HIP(hipMemcpyAsync(kb.p, kappa_h, sizeof(double) * nd, hipMemcpyHostToDevice, st));

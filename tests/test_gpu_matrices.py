@@ -103,3 +103,68 @@ def test_solves_follow_the_shape_and_the_drops(E):
     assert torch.equal(solve(ctx), want)
     ctx.close()
     ctx2.close()
+
+
+def lattice(E, nd):
+    """A context of nd copies of a p = 16 drop on a cubic lattice, their force density."""
+    import torch
+    one, k = W.single_drop(p=16), int(np.ceil(nd ** (1.0 / 3.0)))
+    x = np.tile(one.xcoef, nd).reshape(nd, 3, -1)
+    for c in range(3):
+        x[:, c, 0] += np.sqrt(4.0 * np.pi) * 3.0 * ((np.arange(nd) // k ** c) % k)
+    ps, dev = np.full(nd, 16, np.int32), torch.device("cuda", 0)
+    ctx = E.Context(0)
+    ctx.set_drops(ps, 2 * ps, 2 * ps, 0, torch.from_numpy(x.ravel()).to(dev))
+    return ctx, torch.from_numpy(np.tile(one.fcoef, nd)).to(dev)
+
+
+def leave(nbytes):
+    """Tensors that take the device's memory but for nbytes (a first one may
+    free some of what the runtime holds: a second takes the rest)."""
+    import torch
+    torch.cuda.empty_cache()
+    hold = []
+    for _ in range(2):
+        more = torch.cuda.mem_get_info()[0] - int(nbytes)
+        if more > 1 << 21:
+            hold.append(torch.empty(more, dtype=torch.uint8, device="cuda:0"))
+    print("left", torch.cuda.mem_get_info()[0], "of", int(nbytes), flush=True)
+    return hold
+
+
+def test_solve_runs_where_matrices_and_basis_do_not_both_fit(E):
+    """256 drops of p = 16: matrices 2.2 GB and 1.2 GB of weights for their build,
+    basis of 200 vectors 0.38 GB.  With room for the matrices and little more
+    the solve evaluates instead, as it does with next to none; large matrices
+    are given back, small ones when their memory is asked for."""
+    import torch
+    ctx, f = lattice(E, 256)
+    n, nd = ctx.num_coefs(), 256
+    grid = 6 * 33 * 66 * 8
+    batch = (1 << 30) // grid
+    need = 48 * 578 * 306 * nd + batch * (grid + 6 * 17 * 18 * 8)
+    u = [torch.zeros(3 * n, dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    ctx.solve_velocity(3.0, f, u[1], restart=200, maxit=4)        # (first launches take scratch memory)
+    free = torch.cuda.mem_get_info()[0]
+    ctx.solve_velocity(3.0, f, u[0], restart=200, tol=1e-11)
+    assert abs(torch.cuda.mem_get_info()[0] - free) < 64 << 20, "matrices kept beyond the limit"
+    for room in (0.15e9, -2.0e9):
+        hold = leave(need + room)
+        u[1].zero_()
+        it, res = ctx.solve_velocity(3.0, f, u[1], restart=200, tol=1e-11)
+        del hold
+        err = ((u[0] - u[1]).abs().max() / u[0].abs().max()).item()
+        print("room", room, "iterations", it, "residual", res, "err", err, flush=True)
+        assert res <= 1e-11 and err < 1e-10
+    ctx.close()
+    # 64 drops: 1.8 GB kept, wanted by the next solve's larger basis (94 MB)
+    ctx, f = lattice(E, 64)
+    u = [torch.zeros(3 * ctx.num_coefs(), dtype=torch.float64, device="cuda:0") for _ in range(2)]
+    ctx.solve_velocity(3.0, f, u[0], restart=30, tol=1e-11)
+    hold = leave(80e6)
+    it, res = ctx.solve_velocity(3.0, f, u[1], restart=200, tol=1e-11)
+    del hold
+    torch.cuda.empty_cache()
+    err = ((u[0] - u[1]).abs().max() / u[0].abs().max()).item()
+    ctx.close()
+    assert res <= 1e-11 and err < 1e-10, (res, err)

@@ -320,11 +320,13 @@ int ehd_time_self(ehd_ctx* ctx, int cls, int pf, const double* fcoef_d, const do
  * restarted GMRES in FP64 on the device.  Each iteration is one evaluation of
  * the layer potential (far field in far_prec) and one ehd_analyze.  With
  * maxit >= 4 and without the nearly singular correction the singular rule is
- * built once per solve as a matrix over the coefficients (ehd_solve_En: 8 T_d n_d
+ * built once per solve that takes steps as a matrix over the coefficients
+ * (ehd_solve_En: 8 T_d n_d
  * bytes for a drop of T_d nodes and n_d = (p+1)(p+2) coefficients,
  * ehd_solve_velocity six times that; up to 2 GiB stay with the context until
- * ehd_set_drops, more is given back after the solve), and evaluated by it;
- * where the device memory does not suffice, by ehd_layer_potentials.
+ * ehd_set_drops or until another call needs them, more is given back after the
+ * solve), and evaluated by it; where the device memory does not suffice beside
+ * the solve's own workspace and 256 MiB, by ehd_layer_potentials.
  * restart in [1, 200], maxit >= 0 (mat-vecs; 0 only evaluates the true
  * residual of the initial guess into *relres), tol > 0: stop when the true
  * residual |b - A x| <= tol |b| (Euclidean norm of the packed coefficient

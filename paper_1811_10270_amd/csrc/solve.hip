@@ -313,10 +313,12 @@ struct GmresWork {
 // Restarted GMRES(m) for A x = b on device vectors of length n; x holds the
 // initial guess on entry.  Converged when the true relative residual
 // |b - A x| / |b| <= tol.  Every workspace entry is written before it is
-// read.
-template <class OpT>
+// read.  prepare() is called once there are Krylov steps to take: after the
+// residual of a guess; at once for a zero one, whose residual is b, or where
+// the caller expects steps (moved).
+template <class OpT, class PrepareT>
 int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x, int m, int maxit, double tol,
-             const GmresWork& ws, int* iters, double* relres)
+             const GmresWork& ws, int* iters, double* relres, bool moved, const PrepareT& prepare)
 {
     hipStream_t st = ehd_ctx_stream(ctx);
     double* V = ws.V;
@@ -329,19 +331,23 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
     // (m + 1) nb <= n / 2 and the blocks of n are fewer than n / 2 then.
     const int nb = (int)std::min<long long>(32, std::max<long long>(1, n / 2048));
     const int nu = (int)nblocks(n);
-    auto norm = [&](const double* vec, double* spare, double* out) -> int {
-        double* const part = nb > 1 ? spare : hd;
-        hipLaunchKernelGGL(k_dots, dim3(1, nb), dim3(kT), 0, st, vec, n, vec, n, part);
-        if (nb > 1) hipLaunchKernelGGL(k_total, dim3(1), dim3(kT), 0, st, part, nb, hd);
+    auto norms = [&](const double* const* vec, int k, double* spare, double* out) -> int {
+        for (int i = 0; i < k; ++i) {
+            double* const part = nb > 1 ? spare + i * nb : hd + i;
+            hipLaunchKernelGGL(k_dots, dim3(1, nb), dim3(kT), 0, st, vec[i], n, vec[i], n, part);
+            if (nb > 1) hipLaunchKernelGGL(k_total, dim3(1), dim3(kT), 0, st, part, nb, hd + i);
+        }
         SOLVE_HIP(hipGetLastError());
-        SOLVE_HIP(hipMemcpyAsync(out, hd, sizeof(double), hipMemcpyDeviceToHost, st));
+        SOLVE_HIP(hipMemcpyAsync(out, hd, sizeof(double) * k, hipMemcpyDeviceToHost, st));
         SOLVE_HIP(hipStreamSynchronize(st));
-        *out = std::sqrt(*out);
+        for (int i = 0; i < k; ++i) out[i] = std::sqrt(out[i]);
         return EHD_OK;
     };
-    double bnorm;
-    int rc = norm(b, V, &bnorm);
+    double bx[2];
+    const double* const given[2] = {b, x};
+    int rc = norms(given, 2, V, bx);
     if (rc) return rc;
+    const double bnorm = bx[0];
     *iters = 0;
     if (bnorm == 0.0) {
         hipLaunchKernelGGL(k_fill, dim3(nblocks(n)), dim3(kT), 0, st, x, 0.0, n);
@@ -350,16 +356,23 @@ int gmres_ws(ehd_ctx* ctx, long long n, const OpT& A, const double* b, double* x
         *relres = 0.0;
         return EHD_OK;
     }
+    bool now = (moved || bx[1] == 0.0) && maxit > 0 && tol < 1.0, prepared = false;
     for (;;) {
         // true residual r = b - A x, into V_0
+        if (now && (rc = prepare())) return rc;
+        prepared = prepared || now;
+        now = false;
         if ((rc = A(x, w))) return rc;
         SOLVE_HIP(hipMemcpyAsync(V, b, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, -1.0, w, 1.0, V, n);
         SOLVE_HIP(hipGetLastError());
         double beta;
-        if ((rc = norm(V, V + n, &beta))) return rc;
+        const double* const v0 = V;
+        if ((rc = norms(&v0, 1, V + n, &beta))) return rc;
         *relres = beta / bnorm;
         if (*relres <= tol || *iters >= maxit) return EHD_OK;
+        if (!prepared && (rc = prepare())) return rc;
+        prepared = true;
         hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, 0.0, V, 1.0 / beta, V, n);
         std::fill(g, g + m + 1, 0.0);
         g[0] = beta;
@@ -443,9 +456,11 @@ struct GmresBuffers {
     }
 };
 
-// A solve's operator matrices (ehd_ctx_matrices), where its mat-vecs repay
-// them: they cost about as much as one evaluation (K*) or two (D), so a solve
-// of at least kMatrixSteps steps may use them.
+// A solve's operator matrices (ehd_ctx_matrices).  They cost about as much as
+// one evaluation (K*) or two (D): built once the guess is known to need steps,
+// since even one step and the residual after it take two products, and not
+// where maxit allows fewer than kMatrixSteps.  (Two drops of p = 32, guess
+// converged: E_n 1.8 ms with matrices built at once, 1.35 without, u 4.7 and 2.6.)
 constexpr int kMatrixSteps = 4;
 struct Matrices {
     ehd_ctx* ctx;
@@ -482,8 +497,8 @@ int check_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int res
 // The E_n system of eq. galerkin_En with device buffers grid [T], rhs [n],
 // geo [6 T] and the GMRES workspace ws (NULL: GMRES allocates its own).
 int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int restart, int maxit, double tol,
-                  double* en_coef_d, int* iters, double* relres, double* grid, double* rhs, double* geo,
-                  const GmresWork* ws)
+                  double* en_coef_d, int* iters, double* relres, bool moved, double* grid, double* rhs,
+                  double* geo, const GmresWork* ws)
 {
     long long T, n;
     int rc;
@@ -501,7 +516,6 @@ int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, in
     GmresBuffers own;
     if (!ws && (rc = own.alloc(ctx, n, restart))) return rc;
     Matrices mats(ctx);
-    if (!ws && (rc = mats.build(EHD_LAP_DLADJ, maxit))) return rc;
     auto A = [&](const double* in, double* out) -> int {
         int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid)
                         : ehd_layer_potentials(ctx, nullptr, nullptr, in, EHD_LAP_DLADJ, far_prec, grid, nullptr);
@@ -511,7 +525,8 @@ int solve_En_impl(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, in
         SOLVE_HIP(hipGetLastError());
         return EHD_OK;
     };
-    return gmres_ws(ctx, n, A, rhs, en_coef_d, restart, maxit, tol, ws ? *ws : own.ws, iters, relres);
+    return gmres_ws(ctx, n, A, rhs, en_coef_d, restart, maxit, tol, ws ? *ws : own.ws, iters, relres, moved,
+                    [&] { return ws ? EHD_OK : mats.build(EHD_LAP_DLADJ, maxit); });
 }
 
 // Allocation-free E_n solve: its workspace lives in `scratch`, one array per
@@ -546,12 +561,9 @@ int scratch_of_device(ehd_ctx* ctx, int dev, double** out)
     return EHD_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int ehd_solve_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int restart, int maxit, double tol,
-                 double* en_coef_d, int* iters, double* relres)
+// The solves; moved: the guess is that of an earlier shape, to need steps.
+int solve_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int restart, int maxit, double tol,
+             double* en_coef_d, int* iters, double* relres, bool moved)
 {
     int rc = check_En(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres);
     if (rc) return rc;
@@ -562,8 +574,55 @@ int ehd_solve_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int
     SOLVE_HIP(ehd_ctx_malloc(ctx, &grid.p, sizeof(double) * (size_t)T));
     SOLVE_HIP(ehd_ctx_malloc(ctx, &rhs.p, sizeof(double) * (size_t)n));
     SOLVE_HIP(ehd_ctx_malloc(ctx, &geo.p, sizeof(double) * (size_t)6 * T));
-    return solve_En_impl(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, grid.p, rhs.p,
-                         geo.p, nullptr);
+    return solve_En_impl(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, moved, grid.p,
+                         rhs.p, geo.p, nullptr);
+}
+
+int solve_velocity(ehd_ctx* ctx, double lambda, const double* fcoef_d, int far_prec, int restart, int maxit, double tol,
+                   double* ucoef_d, int* iters, double* relres, bool moved)
+{
+    if (!ctx) return EHD_E_ARG;
+    if (!ehd_ctx_ndrops(ctx)) return ehd_ctx_fail(ctx, EHD_E_STATE, "ehd_set_drops has not been called");
+    if (!fcoef_d || !ucoef_d || !iters || !relres) return ehd_ctx_fail(ctx, EHD_E_ARG, "NULL argument");
+    if (!(lambda >= 0.0) || !std::isfinite(lambda)) return ehd_ctx_fail(ctx, EHD_E_ARG, "lambda must be >= 0");
+    int rc = check_opts(ctx, far_prec, restart, maxit, tol);
+    if (rc) return rc;
+    SOLVE_HIP(hipSetDevice(ehd_ctx_device(ctx)));
+    long long T, nc;
+    if ((rc = ehd_num_targets(ctx, &T)) || (rc = ehd_num_coefs(ctx, &nc))) return rc;
+    const long long n = 3 * nc;
+    hipStream_t st = ehd_ctx_stream(ctx);
+    DevBuf grid, rhs;
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &grid.p, sizeof(double) * (size_t)3 * T));
+    SOLVE_HIP(ehd_ctx_malloc(ctx, &rhs.p, sizeof(double) * (size_t)n));
+    // right-hand side P[S[f]]
+    if ((rc = ehd_layer_potentials(ctx, fcoef_d, nullptr, nullptr, EHD_STOKES_SL, far_prec, grid.p, nullptr))) return rc;
+    if ((rc = ehd_analyze(ctx, 3, grid.p, rhs.p))) return rc;
+    // operator u -> (lambda+1) u - (lambda-1) P[D[u]]
+    GmresBuffers work;
+    if ((rc = work.alloc(ctx, n, restart))) return rc;
+    Matrices mats(ctx);
+    auto A = [&](const double* in, double* out) -> int {
+        int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid.p)
+                        : ehd_layer_potentials(ctx, nullptr, in, nullptr, EHD_STOKES_DL, far_prec, grid.p, nullptr);
+        if (!r) r = ehd_analyze(ctx, 3, grid.p, out);
+        if (r) return r;
+        hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, lambda + 1.0, in, -(lambda - 1.0), out, n);
+        SOLVE_HIP(hipGetLastError());
+        return EHD_OK;
+    };
+    return gmres_ws(ctx, n, A, rhs.p, ucoef_d, restart, maxit, tol, work.ws, iters, relres, moved,
+                    [&] { return mats.build(EHD_STOKES_DL, maxit); });
+}
+
+}  // namespace
+
+extern "C" {
+
+int ehd_solve_En(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int restart, int maxit, double tol,
+                 double* en_coef_d, int* iters, double* relres)
+{
+    return solve_En(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, false);
 }
 
 int ehd_solve_En_noalloc(ehd_ctx* ctx, double R, double Eu, double Eq, int far_prec, int restart, int maxit,
@@ -604,45 +663,14 @@ int ehd_solve_En_noalloc(ehd_ctx* ctx, double R, double Eu, double Eq, int far_p
     double H[(kNoAllocMaxRestart + 1) * kNoAllocMaxRestart], cs[kNoAllocMaxRestart], sn[kNoAllocMaxRestart],
         g[kNoAllocMaxRestart + 1], h[kNoAllocMaxRestart + 1], y[kNoAllocMaxRestart], hh[2 * kNoAllocMaxRestart + 3];
     const GmresWork ws{base + offs[0], base + offs[1], base + offs[2], H, cs, sn, g, h, y, hh};
-    return solve_En_impl(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, base + offs[3],
+    return solve_En_impl(ctx, R, Eu, Eq, far_prec, restart, maxit, tol, en_coef_d, iters, relres, false, base + offs[3],
                          base + offs[4], base + offs[5], &ws);
 }
 
 int ehd_solve_velocity(ehd_ctx* ctx, double lambda, const double* fcoef_d, int far_prec, int restart, int maxit,
                        double tol, double* ucoef_d, int* iters, double* relres)
 {
-    if (!ctx) return EHD_E_ARG;
-    if (!ehd_ctx_ndrops(ctx)) return ehd_ctx_fail(ctx, EHD_E_STATE, "ehd_set_drops has not been called");
-    if (!fcoef_d || !ucoef_d || !iters || !relres) return ehd_ctx_fail(ctx, EHD_E_ARG, "NULL argument");
-    if (!(lambda >= 0.0) || !std::isfinite(lambda)) return ehd_ctx_fail(ctx, EHD_E_ARG, "lambda must be >= 0");
-    int rc = check_opts(ctx, far_prec, restart, maxit, tol);
-    if (rc) return rc;
-    SOLVE_HIP(hipSetDevice(ehd_ctx_device(ctx)));
-    long long T, nc;
-    if ((rc = ehd_num_targets(ctx, &T)) || (rc = ehd_num_coefs(ctx, &nc))) return rc;
-    const long long n = 3 * nc;
-    hipStream_t st = ehd_ctx_stream(ctx);
-    DevBuf grid, rhs;
-    SOLVE_HIP(ehd_ctx_malloc(ctx, &grid.p, sizeof(double) * (size_t)3 * T));
-    SOLVE_HIP(ehd_ctx_malloc(ctx, &rhs.p, sizeof(double) * (size_t)n));
-    // right-hand side P[S[f]]
-    if ((rc = ehd_layer_potentials(ctx, fcoef_d, nullptr, nullptr, EHD_STOKES_SL, far_prec, grid.p, nullptr))) return rc;
-    if ((rc = ehd_analyze(ctx, 3, grid.p, rhs.p))) return rc;
-    // operator u -> (lambda+1) u - (lambda-1) P[D[u]]
-    GmresBuffers work;
-    if ((rc = work.alloc(ctx, n, restart))) return rc;
-    Matrices mats(ctx);
-    if ((rc = mats.build(EHD_STOKES_DL, maxit))) return rc;
-    auto A = [&](const double* in, double* out) -> int {
-        int r = mats.on ? ehd_ctx_matrix_potential(ctx, in, far_prec, grid.p)
-                        : ehd_layer_potentials(ctx, nullptr, in, nullptr, EHD_STOKES_DL, far_prec, grid.p, nullptr);
-        if (!r) r = ehd_analyze(ctx, 3, grid.p, out);
-        if (r) return r;
-        hipLaunchKernelGGL(k_axpby, dim3(nblocks(n)), dim3(kT), 0, st, lambda + 1.0, in, -(lambda - 1.0), out, n);
-        SOLVE_HIP(hipGetLastError());
-        return EHD_OK;
-    };
-    return gmres_ws(ctx, n, A, rhs.p, ucoef_d, restart, maxit, tol, work.ws, iters, relres);
+    return solve_velocity(ctx, lambda, fcoef_d, far_prec, restart, maxit, tol, ucoef_d, iters, relres, false);
 }
 
 int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* gamma_coef_d, double* en_coef_d,
@@ -660,9 +688,12 @@ int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* ga
     int rc;
     int it_en = 0, it_u = 0;
     double rr;
-    // i. E_n
-    if ((rc = ehd_solve_En(ctx, prm->R, prm->Eu, prm->Eq, prm->far_prec, prm->restart, prm->maxit, prm->tol,
-                           en_coef_d, &it_en, &rr)))
+    // i. E_n.  A step's guesses come from an earlier shape: the matrices of K*
+    // are built at once, which costs little more than the evaluation that would
+    // tell (0.4 ms of 23 with two drops of p = 32); those of D if this guess did
+    // need steps.
+    if ((rc = solve_En(ctx, prm->R, prm->Eu, prm->Eq, prm->far_prec, prm->restart, prm->maxit, prm->tol, en_coef_d,
+                       &it_en, &rr, true)))
         return rc;
     long long T, nc;
     if ((rc = ehd_num_targets(ctx, &T)) || (rc = ehd_num_coefs(ctx, &nc))) return rc;
@@ -702,8 +733,8 @@ int ehd_explicit_step(ehd_ctx* ctx, const ehd_step_params* prm, const double* ga
     SOLVE_HIP(hipGetLastError());
     if ((rc = ehd_analyze(ctx, 3, ft.p, fc.p))) return rc;
     // vi. velocity
-    if ((rc = ehd_solve_velocity(ctx, prm->lambda, fc.p, prm->far_prec, prm->restart, prm->maxit, prm->tol, ucoef_d,
-                                 &it_u, &rr)))
+    if ((rc = solve_velocity(ctx, prm->lambda, fc.p, prm->far_prec, prm->restart, prm->maxit, prm->tol, ucoef_d, &it_u,
+                             &rr, it_en > 0)))
         return rc;
     // vii. x + dt u
     if ((rc = ehd_drop_coefs(ctx, xnew_coef_d))) return rc;
@@ -772,7 +803,9 @@ int ehd_solve_surfactant(ehd_ctx* ctx, const double* kappa_h, const double* rhs_
     SOLVE_HIP(hipGetLastError());
     GmresBuffers work;
     if ((rc = work.alloc(ctx, n, restart))) return rc;
-    if ((rc = gmres_ws(ctx, n, A, rhs_d, gamma_d, restart, maxit, tol, work.ws, iters, relres))) return rc;
+    if ((rc = gmres_ws(ctx, n, A, rhs_d, gamma_d, restart, maxit, tol, work.ws, iters, relres, false,
+                       [] { return EHD_OK; })))
+        return rc;
     hipLaunchKernelGGL(k_mul, dim3(nblocks(n)), dim3(kT), 0, st, di.p, gamma_d, gamma_d, n);
     SOLVE_HIP(hipGetLastError());
     SOLVE_HIP(hipStreamSynchronize(st));

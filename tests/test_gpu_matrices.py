@@ -168,3 +168,29 @@ def test_solve_runs_where_matrices_and_basis_do_not_both_fit(E):
     err = ((u[0] - u[1]).abs().max() / u[0].abs().max()).item()
     ctx.close()
     assert res <= 1e-11 and err < 1e-10, (res, err)
+
+
+def test_a_converged_guess_costs_one_evaluation(E):
+    """A guess that meets the tolerance: its residual by one evaluation (the
+    timing slots record them), no step, no matrices (1.3 GB of memory here)."""
+    import torch
+    s, ctx, dev = context(E, [32, 32], [64, 64], 0)
+    f = torch.from_numpy(s.fcoef).to(dev)
+    en = torch.zeros(ctx.num_coefs(), dtype=torch.float64, device=dev)
+    u = torch.zeros(3 * ctx.num_coefs(), dtype=torch.float64, device=dev)
+    ctx.solve_En(0.4, 1.0, 0.3, en)
+    ctx.solve_velocity(3.0, f, u)
+    ctx.close()
+    _, ctx, _ = context(E, [32, 32], [64, 64], 0)
+    ctx.set_timing(4)
+    free = torch.cuda.mem_get_info()[0]
+    for solve, v, calls in ((lambda: ctx.solve_En(0.4, 1.0, 0.3, en, tol=1e-11), en, 1),
+                            (lambda: ctx.solve_velocity(3.0, f, u, tol=1e-11), u, 3)):
+        want = v.clone()
+        it, res = solve()
+        ctx.stage_times(calls - 1)
+        with pytest.raises(RuntimeError):
+            ctx.stage_times(calls)
+        assert it == 0 and res <= 1e-11 and torch.equal(v, want)
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+    ctx.close()

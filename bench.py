@@ -279,11 +279,11 @@ def time_evaluation(args, torch, E, ctx, s, far_prec, kinds, f, sig, out, u=None
         shape = shapes[1] if far_prec == E.FAR_FP32C and len(shapes) > 1 else shapes[0]
         tpt, nch = (int(v) for v in shape.split("x"))
         ctx.set_far_config(tpt, nch)
-    tile = {"targets_per_thread": ctx.far_config()[0], "source_chunks": ctx.far_config()[1], "autotuned": False}
+    tile = {"targets_per_thread": ctx.far_config()[0], "source_chunks": ctx.far_chunks(far_prec), "autotuned": False}
     if not args.no_autotune and not args.far_tile:
         from paper_1811_10270_amd import autotune
         tpt, nch, timings, cached = autotune.autotune_far(ctx, s.p, s.q_far, s.grid_mode, far_prec, kinds=kinds)
-        tile = {"targets_per_thread": tpt, "source_chunks": nch, "autotuned": True, "from_cache": cached,
+        tile = {"targets_per_thread": tpt, "source_chunks": ctx.far_chunks(far_prec), "autotuned": True, "from_cache": cached,
                 "timings_ms": timings}
     log("far tile", tile)
     ctx.set_graph(bool(args.graph))
@@ -315,7 +315,7 @@ def time_evaluation(args, torch, E, ctx, s, far_prec, kinds, f, sig, out, u=None
     cls_times = [ctx.self_class_times(i) for i in range(K)]
 
     T = ctx.ntargets
-    tpt_, nch_ = ctx.far_config()
+    tpt_, nch_ = ctx.far_config()[0], ctx.far_chunks(far_prec)
     # the library's overlap plan: classes beside a forked far-field share
     beside, forked = ctx.overlap_plan(kinds, far_prec) if args.overlap else (0, 0)
     overlap = forked > 0

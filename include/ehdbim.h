@@ -270,12 +270,14 @@ int ehd_overlap_plan(ehd_ctx* ctx, unsigned kinds, int far_prec, int with_u, uns
 
 /* Far-field tile shape: targets per thread (1 or 2) and number of source
  * chunks (1..16, at most the number of source tiles) the targets' sums are
- * split into.  ehd_set_drops sets a default (with it the FP64 sums take as many
- * chunks as there can be; and of few targets each FP64 chunk is cut further);
- * the autotuner (ehd_time_far over candidates,
+ * split into.  ehd_set_drops sets a default shape, which stands for a rule, also
+ * when it is set again or timed: the FP64 sums take as many chunks as there can
+ * be, the FP32 ones those reported (ehd_far_chunks: the chunks in effect).  Of
+ * few targets each FP64 chunk is cut further.  The autotuner (ehd_time_far over candidates,
  * paper_1811_10270_amd/autotune.py) picks the fastest. */
 int ehd_set_far_config(ehd_ctx* ctx, int targets_per_thread, int nchunk);
 int ehd_get_far_config(const ehd_ctx* ctx, int* targets_per_thread, int* nchunk);
+int ehd_far_chunks(const ehd_ctx* ctx, int far_prec, int* nchunk);
 
 /* How the FP64 far field of the current shapes is summed: *direct receives
  * the target-source interactions of the direct sums, *expanded the (target

@@ -2512,8 +2512,8 @@ struct ehd_ctx {
     std::vector<AdjTab> adjtab_h;
     bool opready = false;            // the tables and groups of the current drops are on the device
     unsigned opkind = 0;             // the kind the matrices are of, 0: none
-    bool far_set = false;            // tile shape chosen by the caller
     int nchunk = 1;                  // far field: source chunks (grid y)
+    int nchunk0 = 1;                 // their default, with one target per thread
     int far_tpt = 1;                 // far field: targets per thread
     int self_pf[4] = {0, 0, 0, 0};   // self-interaction: Legendre prefetch batch per degree class (0: default)
 
@@ -3734,7 +3734,7 @@ int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h,
     ctx->far_tpt = 1;
     ctx->nchunk = (int)std::min<long long>(std::min<long long>(std::max<long long>(1, (2048 + tblocks - 1) / tblocks),
                                                                ctx->ntiles), kMaxChunks);
-    ctx->far_set = false;
+    ctx->nchunk0 = ctx->nchunk;
     const size_t parts = kMaxChunks * (T > kCutTargets ? 1 : kMaxCut);
     if ((rc = dev_alloc(ctx, &ctx->d_partial, parts * 9 * T))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->d_expanded, (size_t)9 * T))) return rc;
@@ -3825,15 +3825,18 @@ static long long far_blocks(const ehd_ctx* ctx, int tpt)
     return (ctx->T + (long long)kThreads * tpt - 1) / ((long long)kThreads * tpt);
 }
 
-// Source chunks of an evaluation: those the caller chose, or the default.
-// With the default the FP64 direct sums take as many as there can be, since
+// Source chunks that a tile shape stands for.  The default shape is a rule
+// (setting what ehd_get_far_config reported keeps it): the FP64 direct sums
+// take as many as there can be, since
 // the drops near a target are few tiles (256 drops of p = 32: 1 chunk 34.3 ms,
 // 4 27.1, 16 23.5; 64 drops of mixed degree, 4 chunks 9.5 ms, 16 7.4); the
 // FP32 sums depend on the split at their rounding and keep theirs.
-static int far_chunks(const ehd_ctx* ctx, int far_prec)
+static int far_chunks(const ehd_ctx* ctx, int far_prec, int tpt, int nchunk)
 {
-    return ctx->far_set || far_prec != EHD_FAR_FP64 ? ctx->nchunk : std::min(ctx->ntiles, kMaxChunks);
+    const bool rule = far_prec == EHD_FAR_FP64 && tpt == 1 && nchunk == ctx->nchunk0;
+    return rule ? std::min(ctx->ntiles, kMaxChunks) : nchunk;
 }
+static int far_chunks(const ehd_ctx* ctx, int far_prec) { return far_chunks(ctx, far_prec, ctx->far_tpt, ctx->nchunk); }
 
 // Source parts (partial sums per target) of a tile shape: its chunks; in FP64
 // each is cut into up to four where there are so few blocks of targets that
@@ -4479,7 +4482,6 @@ int ehd_set_far_config(ehd_ctx* ctx, int targets_per_thread, int nchunk)
                  kMaxChunks, ctx->ntiles);
     ctx->far_tpt = targets_per_thread;
     ctx->nchunk = nchunk;
-    ctx->far_set = true;
     return EHD_OK;
 }
 
@@ -4489,6 +4491,14 @@ int ehd_get_far_config(const ehd_ctx* ctx, int* targets_per_thread, int* nchunk)
     *targets_per_thread = ctx->far_tpt;
     *nchunk = ctx->nchunk;
     return ctx->nd ? EHD_OK : EHD_E_STATE;
+}
+
+int ehd_far_chunks(const ehd_ctx* ctx, int far_prec, int* nchunk)
+{
+    if (!ctx || !nchunk || (far_prec != EHD_FAR_FP64 && far_prec != EHD_FAR_FP32C)) return EHD_E_ARG;
+    if (!ctx->nd) return EHD_E_STATE;
+    *nchunk = far_chunks(ctx, far_prec);
+    return EHD_OK;
 }
 
 int ehd_far_plan(const ehd_ctx* ctx, long long* direct, long long* expanded)
@@ -4518,6 +4528,7 @@ int ehd_time_far(ehd_ctx* ctx, int far_prec, unsigned kinds, int targets_per_thr
         nchunk > ctx->ntiles)
         EHD_FAIL(ctx, EHD_E_ARG, "invalid tile shape");
     EHD_HIP(ctx, hipSetDevice(ctx->device));
+    nchunk = far_chunks(ctx, far_prec, targets_per_thread, nchunk);
     hipEvent_t e0, e1;
     EHD_HIP(ctx, hipEventCreate(&e0));
     EHD_HIP(ctx, hipEventCreate(&e1));

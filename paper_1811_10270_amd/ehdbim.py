@@ -40,7 +40,7 @@ EXPORTED = ("ehd_create", "ehd_destroy", "ehd_last_error", "ehd_grid_dims", "ehd
             "ehd_mlp_forward", "ehd_mlp_backward", "ehd_mlp_mse", "ehd_mlp_adam", "ehd_area_weights",
             "ehd_update_shape", "ehd_surfactant_terms", "ehd_evolve_step", "ehd_evolve", "ehd_set_near",
             "ehd_near_pairs", "ehd_set_overlap", "ehd_overlap_plan", "ehd_self_config_candidates", "ehd_set_self_config", "ehd_get_self_config", "ehd_time_self", "ehd_solve_En_noalloc", "ehd_surfactant_guess",
-            "ehd_learned_features", "ehd_far_plan")
+            "ehd_learned_features", "ehd_far_plan", "ehd_far_chunks")
 STAGES = ("densities", "self", "far", "combine")
 DEGREE_CLASSES = (16, 24, 32, 48)   # largest p of each self-interaction kernel class
 
@@ -113,6 +113,7 @@ def load(path: str = LIB_PATH):
     lib.ehd_set_graph.argtypes = [vp, C.c_int]
     lib.ehd_set_far_config.argtypes = [vp, C.c_int, C.c_int]
     lib.ehd_get_far_config.argtypes = [vp, ip, ip]
+    lib.ehd_far_chunks.argtypes = [vp, C.c_int, ip]
     lib.ehd_time_far.argtypes = [vp, C.c_int, C.c_uint, C.c_int, C.c_int, C.c_int, dp]
     lib.ehd_far_plan.argtypes = [vp, C.POINTER(C.c_longlong), C.POINTER(C.c_longlong)]
     lib.ehd_num_coefs.argtypes = [vp, C.POINTER(C.c_longlong)]
@@ -375,6 +376,13 @@ class Context:
         a, b = C.c_int(), C.c_int()
         self._check(self._lib.ehd_get_far_config(self._h, C.byref(a), C.byref(b)))
         return a.value, b.value
+
+    def far_chunks(self, far_prec: int) -> int:
+        """Source chunks in effect for far_prec (ehd_far_chunks): the default
+        shape stands for a rule."""
+        n = C.c_int()
+        self._check(self._lib.ehd_far_chunks(self._h, far_prec, C.byref(n)))
+        return n.value
 
     def far_plan(self):
         """(target-source interactions summed directly, pairs of drops that go

@@ -236,3 +236,34 @@ def test_plan_of_many_small_drops_costs_little(E):
         ctx.close()
     print("update_shape", best, flush=True)
     assert best[1] < 6.0 * best[0], best
+
+
+def test_setting_the_reported_tile_shape_changes_nothing(E):
+    """ehd_set_far_config with what ehd_get_far_config reports keeps the default
+    of either precision, also after another shape; another shape is followed."""
+    import torch
+    s = W.suspension(64, [24], 12.0, 5)                      # 80,000 targets: 7 chunks reported, 16 taken in FP64
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    ctx.set_drops(s.p, s.q_self, s.q_far, 0, torch.from_numpy(s.xcoef).to(dev))
+    f = torch.from_numpy(s.fcoef).to(dev)
+    shape = ctx.far_config()
+    assert shape[1] < 16 and ctx.far_chunks(E.FAR_FP64) == 16 and ctx.far_chunks(E.FAR_FP32C) == shape[1]
+
+    def run(prec):
+        so = torch.zeros(3, ctx.ntargets, dtype=torch.float64, device=dev)
+        fo = torch.zeros_like(so)
+        ctx.layer_potentials(f, None, None, E.STOKES_SL, prec, so, fo)
+        ctx.sync()
+        return fo
+
+    first = [run(k) for k in (E.FAR_FP64, E.FAR_FP32C)]
+    for other in (None, (2, 3)):
+        if other:
+            ctx.set_far_config(*other)
+            assert ctx.far_config() == other and ctx.far_chunks(E.FAR_FP64) == ctx.far_chunks(E.FAR_FP32C) == 3
+            assert not torch.equal(first[1], run(E.FAR_FP32C))
+        ctx.set_far_config(*shape)
+        assert ctx.far_chunks(E.FAR_FP64) == 16 and ctx.far_config() == shape
+        for k, want in zip((E.FAR_FP64, E.FAR_FP32C), first):
+            assert torch.equal(run(k), want), (other, k)
+    ctx.close()

@@ -7,8 +7,9 @@ the share that overlap mode forks beside the self-interaction uses the same
 shape).  Each shape is timed `reps` times (once when a launch takes longer
 than LONG_MS) and ranked by its median.  The
 fastest is kept in the context and cached in a JSON file keyed by device
-architecture, library build, workload signature, kinds and precision, so a
-rebuilt library never reuses a stale choice.
+architecture, library build, workload signature, kinds, precision and, in FP64,
+the plan of direct and expanded pairs, so a rebuilt library or another
+arrangement of the drops never reuses a stale choice.
 
 The self-interaction autotuner does the same for the Legendre prefetch
 batch of each degree class present (ehd_time_self over the batches the
@@ -51,12 +52,16 @@ def library_hash() -> str:
 
 
 def signature(ctx, p, q_far, grid_mode: int, far_prec: int, kinds: int) -> str:
+    from . import ehdbim
     prop = torch.cuda.get_device_properties(ctx.device)
     arch = getattr(prop, "gcnArchName", prop.name)
     h = hashlib.sha1()
     h.update(repr((list(map(int, p)), list(map(int, q_far)), int(grid_mode))).encode())
+    # the FP64 direct sums keep the pairs of drops that are not expanded, which
+    # depend on where the drops are
+    plan = "|direct%d|expanded%d" % ctx.far_plan() if far_prec == ehdbim.FAR_FP64 else ""
     return (f"{arch}|{prop.multi_processor_count}|lib{library_hash()}|T{ctx.ntargets}|{h.hexdigest()[:16]}"
-            f"|prec{far_prec}|kinds{kinds}")
+            f"|prec{far_prec}|kinds{kinds}{plan}")
 
 
 def _load(path):

@@ -78,3 +78,23 @@ def test_far_autotuner_picks_caches_and_reuses(keys, tmp_path):
     ctx3 = FakeCtx({}, far)
     _, _, _, cached3 = autotune.autotune_far(ctx3, [32, 32], [64, 64], 0, 0, kinds=31, cache_path=cache)
     assert not cached3 and ctx3.timed > 0
+
+
+def test_far_key_follows_the_plan_in_fp64(monkeypatch):
+    """Which pairs of drops are summed directly depends on where the drops are:
+    another plan is another key in FP64; the FP32 sums take every pair."""
+    class Props:
+        gcnArchName, multi_processor_count = "gfx950", 256
+
+    E.load()
+    monkeypatch.setattr(autotune.torch.cuda, "get_device_properties", lambda dev: Props)
+    ctx = FakeCtx({}, {})
+
+    def key(plan, prec):
+        ctx.far_plan = lambda: plan
+        return autotune.signature(ctx, [32, 32], [64, 64], 0, prec, 15)
+
+    near, apart = (36808200, 0), (0, 2)
+    assert key(near, E.FAR_FP64) != key(apart, E.FAR_FP64)
+    assert key(near, E.FAR_FP64) == key(near, E.FAR_FP64)
+    assert key(near, E.FAR_FP32C) == key(apart, E.FAR_FP32C)

@@ -84,7 +84,7 @@ def test_far_key_follows_the_plan_in_fp64(monkeypatch):
     """Which pairs of drops are summed directly depends on where the drops are:
     another plan is another key in FP64; the FP32 sums take every pair."""
     class Props:
-        gcnArchName, multi_processor_count = "gfx950", 256
+        name, gcnArchName, multi_processor_count = "MI355X", "gfx950", 256
 
     E.load()
     monkeypatch.setattr(autotune.torch.cuda, "get_device_properties", lambda dev: Props)

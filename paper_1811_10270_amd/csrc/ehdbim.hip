@@ -3954,7 +3954,8 @@ static unsigned classes_beside_far(ehd_ctx* ctx, int far_prec, unsigned kinds, b
 // Overlap mode: share of the far field's work items forked beside the
 // degree classes in `beside`, the expected time of those classes over that
 // of the far field (each its algorithmic work over the fraction of peak it
-// reaches alone: 0.25, 0.48, 0.65 for the classes, 0.96 for the FP32 far
+// reaches alone: 0.51, 0.63, 0.85 for the classes, 16 drops each of p = 16, 24
+// and 32 in 0.54, 3.0 and 8.9 ms, 0.96 for the FP32 far
 // field at 53 flops per interaction), at most one half.  The FP64 far field
 // needs the same FP64 units as the self-interaction, which slows down by
 // about as much as the far work done beside it (256 drops lost 3-8% at
@@ -3962,7 +3963,7 @@ static unsigned classes_beside_far(ehd_ctx* ctx, int far_prec, unsigned kinds, b
 static double overlap_share(const ehd_ctx* ctx, int far_prec, unsigned beside)
 {
     if (far_prec == EHD_FAR_FP64 || !beside) return 0.0;
-    static const double eff[3] = {0.25, 0.48, 0.65};
+    static const double eff[3] = {0.51, 0.63, 0.85};
     double small = 0.0, far = 0.0;
     long long S = 0;
     for (int d = 0; d < ctx->nd; ++d) S += ctx->info[d].ns;

@@ -366,3 +366,25 @@ def test_self_prefetch_autotuner(E, tmp_path):
     ctx.set_overlap(False)
     ctx.close()
     ctx2.close()
+
+
+def test_overlap_forks_no_more_than_the_classes_take(E):
+    """The far-field share forked beside a degree class takes about the class's
+    own time (within 1.4, the plan's rates being one workload's)."""
+    import torch
+    s = W.batched_suspension(seed=3)
+    ctx, f, sg, dev = _setup(E, s)
+    out = torch.zeros(8, ctx.ntargets, dtype=torch.float64, device=dev)
+    ctx.set_timing(3)
+    for _ in range(3):
+        ctx.layer_potentials(f, None, sg, E.METRIC_KINDS, E.FAR_FP32C, out)
+    ctx.sync()
+    far_ms, cls_ms = ctx.stage_times(2)[2], ctx.self_class_times(2)
+    tpt = ctx.far_config()[0]
+    items = -(-ctx.ntargets // (256 * tpt)) * ctx.far_chunks(E.FAR_FP32C)
+    ctx.set_overlap(True)
+    beside, forked = ctx.overlap_plan(E.METRIC_KINDS, E.FAR_FP32C)
+    ctx.close()
+    beside_ms = sum(cls_ms[c] for c in range(4) if beside >> c & 1)
+    print("forked", forked, "of", items, "beside", beside, "ms", far_ms * forked / items, "against", beside_ms, flush=True)
+    assert forked > 0 and far_ms * forked / items < 1.4 * beside_ms

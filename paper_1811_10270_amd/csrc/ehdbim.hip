@@ -19,6 +19,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -3449,7 +3450,13 @@ static int build_geometry(ehd_ctx* ctx)
     std::vector<double> rad(2 * ctx->nd);
     EHD_HIP(ctx, hipMemcpyAsync(rad.data(), ctx->d_rad, sizeof(double) * rad.size(), hipMemcpyDeviceToHost, ctx->stream));
     EHD_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    return plan_far(ctx, rad);
+    try {
+        return plan_far(ctx, rad);
+    } catch (const std::bad_alloc&) {                          // (the pair lists grow with the square of the drops)
+        ctx->ex.release();
+        ctx->far_lists = false;
+        return EHD_OK;
+    }
 }
 
 int ehd_set_drops(ehd_ctx* ctx, int ndrops, const int* p_h, const int* q_self_h, const int* q_far_h,

@@ -635,6 +635,13 @@ __global__ __launch_bounds__(256) void k_l2p(const ehd::ExpandDrop* __restrict__
 // at order 40), per target and k-step of the evaluation (1.4 ms for 558,000
 // targets), and what the seven launches take on few drops, where no kernel
 // fills the device (12 drops of p = 5 to 29: 0.7 ms against 0.3 saved).
+// All kinds on 2 to 48 drops of p = 8, 16, 24, 32, 48 and mixed, volume
+// fractions 0.1 and 0.01, both ways: the plan takes the faster one, or one
+// within 5%, in each of 96 cases; it turns between 16 drops of p = 16 (direct
+// 0.57 ms, expansions 0.68 to 0.78) and 24 (1.16 and 1.01, 0.75 sparse), and
+// between 2 of p = 48 (0.35 and 0.41 to 0.52) and 4 (1.90 and 1.58, 0.62).  A
+// single kind's direct sums cost a third to a half: next to the turn it loses
+// up to 0.2 ms.
 constexpr double kCostDirect = 0.8, kCostPair = 1.8, kCostMoment = 16.0, kCostEval = 3.5, kCostFixed = 256.0 * 1.2e6;
 // Translation blocks per class to aim at (two to four rounds of the blocks
 // that fit the device) and the most shares of the source orders.

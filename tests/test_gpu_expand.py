@@ -267,3 +267,66 @@ def test_setting_the_reported_tile_shape_changes_nothing(E):
         for k, want in zip((E.FAR_FP64, E.FAR_FP32C), first):
             assert torch.equal(run(k), want), (other, k)
     ctx.close()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_a_bad_density_stays_where_the_direct_sums_leave_it(E, bad):
+    """One drop's sigma not finite: the Laplace rows of every other drop's
+    targets are not finite, as by direct sums; its own targets and the Stokes
+    rows are what they were."""
+    import torch
+    s = suspension("uneven_degrees")
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    ctx.set_drops(s.p, s.q_self, s.q_far, s.grid_mode, torch.from_numpy(s.xcoef).to(dev))
+    assert ctx.far_plan()[1] > 0
+    f, sg = torch.from_numpy(s.fcoef).to(dev), torch.from_numpy(s.sigcoef).to(dev)
+    off, t = W.drop_offsets(s.p.astype(np.int64)), s.target_offsets()
+    d = int(np.argmax(s.p))
+
+    def run():
+        so = torch.zeros(9, ctx.ntargets, dtype=torch.float64, device=dev)
+        fo = torch.zeros_like(so)
+        ctx.layer_potentials(f, None, sg, E.ALL_KINDS, E.FAR_FP64, so, fo)
+        ctx.sync()
+        return fo.cpu().numpy()
+
+    clean = run()
+    sg[off[d]] = bad
+    got = run()
+    ctx.close()
+    own = np.zeros(clean.shape[1], bool)
+    own[t[d]:t[d + 1]] = True
+    assert np.array_equal(got[:6], clean[:6]) and np.array_equal(got[6:, own], clean[6:, own])
+    assert not np.isfinite(got[6:, ~own]).any()
+
+
+def test_plan_without_memory_sums_directly(E):
+    """No room for the expansions' buffers: the same potentials by direct sums,
+    and the expansions again with the next shape that finds room."""
+    import torch
+    s = suspension("sparse")
+    ctx, dev = E.Context(0), torch.device("cuda", 0)
+    close = s.xcoef.copy().reshape(s.ndrops, 3, -1)
+    close[:, :, 0] *= 0.01
+    x, f, sg = (torch.from_numpy(v).to(dev) for v in (s.xcoef, s.fcoef, s.sigcoef))
+    ctx.set_drops(s.p, s.q_self, s.q_far, s.grid_mode, torch.from_numpy(close.ravel().copy()).to(dev))
+    out = [torch.zeros(9, ctx.ntargets, dtype=torch.float64, device=dev) for _ in range(2)]
+    ctx.layer_potentials(f, None, sg, E.ALL_KINDS, E.FAR_FP64, out[0])
+    ctx.sync()
+    assert ctx.far_plan()[1] == 0
+    torch.cuda.empty_cache()
+    hold = []
+    for _ in range(2):
+        hold.append(torch.empty(max(torch.cuda.mem_get_info()[0] - (64 << 20), 1), dtype=torch.uint8, device=dev))
+    print("left", torch.cuda.mem_get_info()[0], flush=True)
+    for k in range(2):
+        ctx.update_shape(x)
+        assert (ctx.far_plan()[1] > 0) == (k == 1)
+        ctx.layer_potentials(f, None, sg, E.ALL_KINDS, E.FAR_FP64, out[k])
+        ctx.sync()
+        del hold[:]
+        torch.cuda.empty_cache()
+    ctx.close()
+    err = (out[0] - out[1]).abs().max(dim=1).values / out[0].abs().max(dim=1).values
+    print("err", err, flush=True)
+    assert err.max().item() < TOL

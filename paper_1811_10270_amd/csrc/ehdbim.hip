@@ -65,7 +65,7 @@ struct LegTab {                // degree-p expansions on a degree-Q grid
     const double* rsin;        // [Q+1] 1 / sin theta_i
     const double* cth;         // [Q+1] cos theta_i
     const double* trig;        // [nlon][p+1][2] cos(m phi_l), sin(m phi_l)
-    const double* afrag;       // singular grids: MFMA A fragments of the quarter-period
+    const double* afrag;       // singular grids: MFMA fragments (B operand) of the quarter-period
                                // cos/sin tables: [row tile][k-step (EC ES OC OS; p > 32: in turn)][lane]
     const double* lfrag;       // singular grids: MFMA A fragments of the Legendre sums,
                                // [latitude block][wave][k-step][lane]; rows 0-7 Pbar,
@@ -849,7 +849,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
     const WigTab W = wigs[D.wig];
     const QuarterGrid qg = quarter_grid(p, Lq.nlon, SC::ROW0);
     double2* cr = lds;                               // [NF][nc] rotated coefficients
-    double* R = reinterpret_cast<double*>(lds);      // later: Fourier blocks + node values
+    double* R = reinterpret_cast<double*>(lds);      // later: Fourier blocks, row-0 records
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
     (void)NT;
@@ -860,11 +860,11 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
     if constexpr (HU) for (int c = 0; c < 3; ++c) fld[UOFF + c] = gmem(ucoef + 3 * D.coff + c * 2 * nc);
     if constexpr (HS) fld[SOFF] = gmem(scoef + D.coff);
 
-    // register-resident A operand of the longitude sums of this wave's row
-    // tile (rows l = 16 tile .. 16 tile + 15): cos/sin(m phi_l) of the four
-    // term groups.  Waves w, w + nTp, .. share tile w % nTp and split the
+    // register-resident B operand of the longitude sums of this wave's row
+    // tile (nodes l = 16 tile .. 16 tile + 15, after row 0): cos/sin(m phi_l) of
+    // the four term groups.  Waves w, w + nTp, .. share tile w % nTp and split the
     // latitudes of a block.  Loaded here, before the rotation, whose time
-    // hides their latency.
+    // hides their latency.  (Above p = 32 the table is read from LDS.)
     constexpr bool TREG = PMAX <= 32;
     const int my_tile = wv % min(qg.nTp, NW);
     double aT[TREG ? SC::KT : 1];
@@ -881,12 +881,12 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
     //    contiguously).
     //    a. z_nm = c_nm e^{i m phi_t} of every field, in the slots the rotated
     //       coefficients of degree n will take;
-    //    b. each degree n belongs to one wave (snake order over the waves),
-    //       lane m' computes Re c'_nm' = sum_m A_mm' Re z_nm and
-    //       Im c'_nm' = sum_m B_mm' Im z_nm for all fields (z read as LDS
-    //       broadcasts, the rows of A and B coalesced over the lanes), then
-    //       overwrites the degree's slots: only this wave reads them.
-    static_assert(PMAX < 64, "one lane per order m' of a degree");
+    //    b. Re c'_nm' = sum_m A_mm' Re z_nm and Im c'_nm' = sum_m B_mm' Im z_nm
+    //       as FP64 MFMA products per degree n: rows m' (the tables' columns),
+    //       columns (field, re/im), terms m.  Degrees in jobs of one, two or
+    //       four, dealt to the waves in snake order; a job overwrites the slots
+    //       of its degrees, which only its wave reads.
+    static_assert(PMAX < 64, "at most four row tiles of 16 orders m' (rotate)");
     {
         const auto ph = gmem(Lp.trig + (long long)k * (p + 1) * 2);
         for (int it = threadIdx.x; it < nc; it += blockDim.x) {
@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
     // stored as real Fourier coefficients: field values and x_theta in the
     // cos row (re) or sin row (im) of m with factors 1 (m = 0) or 2 and -2,
     // x_phi / sin theta = -m (a_m sin - b_m cos) / sin theta in the other row.
-    // Kept short: it is expanded at every k-step of the unrolled chain.
+    // Kept short: it is expanded once per column of the schedule.
     // (lanes without a value to store write to the spare slots of their block)
     const int f_l = cf_ < NF ? cf_ : 0;
     const int v_l = (f_l < 3) ? f_l : VD + (f_l - 3);
@@ -1188,7 +1188,10 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
             asm volatile("" : "+s"(pb));
             // A column's sums are stored in the block of code that made them: a
             // version that carried them over a branch was compiled with 11 wait
-            // states between the last product and the copy of its result, too few.
+            // states between the last product and the copy of its result, where
+            // 18 are needed.  Nothing but the parity tests would notice that in an
+            // edit, so the assembly of every kernel with FP64 MFMA was walked over
+            // all its branches: the present ones have 18 or more before each read.
             // this wave's columns, the one m < r second (the waves without one
             // load the first column's fragments again)
             auto slot_len = [](int i) { return i == 1 ? SC::KLO : self_pos_len(i ? i - 1 : 0, NW, SC::GMAX); };
@@ -1235,10 +1238,10 @@ __global__ __launch_bounds__(SelfClass<PMAX>::NT, SelfClass<PMAX>::WPE) void k_s
         __syncthreads();
 
         // 3b/3c. per latitude of the block owned by this wave: longitude
-        //     sums of its row tile on MFMA (four term-group chains), node
-        //     values through the wave's own LDS buffer (64 nodes: {l, H - l,
-        //     H + l, N - l} x 16 rows), then one node per lane: kernels with
-        //     the modified weights.
+        //     sums of its row tile on MFMA (four term-group chains), the four
+        //     images {l, H - l, H + l, N - l} x 16 rows transposed over the lane
+        //     groups in registers, then one node per lane: kernels with the
+        //     modified weights.
         const int boff = (lane >> 4) * 16 + (lane & 15);
         int kb[4], kl[4];
 #pragma unroll

@@ -309,18 +309,21 @@ __global__ __launch_bounds__(256) void k_moments(const int2* __restrict__ orders
 
 // ---------------------------------------------------------------------------
 // Translations: a block takes consecutive pairs of one target drop.  Lanes
-// hold the local coefficients of one order m and two consecutive degrees n
-// for all potentials in registers over all of the block's pairs; the waves of
+// hold the local coefficients of one order m and R consecutive degrees n
+// (two up to order 19, four above) for all potentials in registers over all of
+// the block's pairs; the waves of
 // a lane set split the source orders m'.  With a = I_{n+n'}^{m+m'} and
 // b = (-1)^m' I_{n+n'}^{m-m'} (from LDS), M = p + i q:
 //   M a + conj(M) b = (p s_r - q t_i, p s_i + q t_r),  s = a + b, t = a - b,
-// and the two degrees' s and t shift by one as n' steps (two steps unrolled,
-// so that the window stays in place): two table reads feed 8 NP FMAs.  The
+// and the R degrees' s and t shift by one as n' steps (R steps unrolled,
+// so that the window stays in place): two table reads feed 4 R NP FMAs.  The
 // moments are wave-uniform (scalar loads).  The potentials phi_3 and Phi_3
 // move their origin with the pair: M_3 -= D.M, D = c_i - c_j.  While the block
 // works on one pair, some of its waves' lanes build the next pair's table.
-// FP64 FMA issue bounds it; two degrees per lane keep it at 128 registers
-// (four degrees spilled and ran 1.4 to 2 times as long).
+// FP64 FMA issue bounds it.  With ten potentials four degrees per lane spill,
+// which costs more than it saves where the chains are short: 256 drops, orders
+// up to 19 3.3 ms with two and 6.2 with four; above, 2.5 with four and 3.3 with
+// two.
 // lpart[slot][split][m, n][NP] (re, im), without the (-1)^n.
 // ---------------------------------------------------------------------------
 template <int CLS>

@@ -81,7 +81,11 @@ enum {
                               is faster (ehd_far_plan)                       */
     EHD_FAR_FP32C = 1      /* FP32 arithmetic on drop-centred coordinates,
                               FP32 accumulation per source tile, compensated
-                              (Kahan) accumulation of the tile sums          */
+                              (Kahan) accumulation of the tile sums; direct
+                              sums over every pair, so slower than FP64 where
+                              that expands (256 drops of p = 32: 870 ms per
+                              evaluation against 184) and 1e-7 accurate: for
+                              few or close drops, where FP64 sums directly too */
 };
 
 enum { EHD_GRID_PAPER = 0, EHD_GRID_2P = 1 };
@@ -202,7 +206,9 @@ int ehd_near_pairs(const ehd_ctx* ctx, long long* npairs);
  * time step): copies xcoef_d (3 packed fields per drop, as for
  * ehd_set_drops) and recomputes the drop centres, the target and far-source
  * geometry and, when ehd_set_near is on, the nearly singular pairs, keeping
- * every table.  Drops a recorded graph.
+ * every table.  Drops a recorded graph (one that the caller has captured of
+ * evaluations holds for the shapes of its capture only: launches and lists of
+ * the far field and of the nearly singular pairs follow the shapes).
  * Synchronous. */
 int ehd_update_shape(ehd_ctx* ctx, const double* xcoef_d);
 
@@ -283,7 +289,8 @@ int ehd_far_chunks(const ehd_ctx* ctx, int far_prec, int* nchunk);
  * the target-source interactions of the direct sums, *expanded the (target
  * drop, source drop) pairs that go through solid-harmonic expansions instead.
  * A pair is expanded if its drops are so far apart that an order of at most 40
- * truncates below the direct sums' rounding, and if all of them together are
+ * truncates below the direct sums' rounding (1e-14 of the double layer, 1.5e-15
+ * of the other kernels), and if all of them together are
  * expected to save time; the FP32 far field sums every pair directly.  Renewed
  * by ehd_set_drops and ehd_update_shape.  Host query only. */
 int ehd_far_plan(const ehd_ctx* ctx, long long* direct, long long* expanded);

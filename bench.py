@@ -77,49 +77,54 @@ def self_exec_flops_per_drop(p: int, q: int, grid_mode: int) -> float:
 # rocprofv3 FETCH_SIZE / WRITE_SIZE counter runs summarised in profiles/
 # (counters scaled by what they read for a plain device copy of known size),
 # valid only for the kernel source they were taken with.
-TRAFFIC_SOURCE_SHA256 = "60810dad5ec8cec55a8307727e9bb7747487add5813133afb8f5c1052345e121"
+TRAFFIC_SOURCE_SHA256 = "4b082327cf9e1c52651f1aac90ec2edc4e897f54bd88beabcbe87fdc78ec7458"
 # (workload, "fp64" | "fp32c", kernel name[, far-field tile shape]) -> bytes per
 # launch of all its items; a far-field kernel's traffic depends on its tile
 # shape (per-chunk partial sums, source re-reads per block of targets)
 TRAFFIC_BYTES = {
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x12"): 4.647e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x14"): 4.493e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x15"): 4.548e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x16"): 4.647e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x12"): 5.798e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x14"): 5.473e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x15"): 5.469e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x16"): 5.39e+08,
+    ("batched_64_mixed_p", "fp32c", "k_self<16>"): 7.186e+06,
+    ("batched_64_mixed_p", "fp32c", "k_self<24>"): 2.509e+07,
+    ("batched_64_mixed_p", "fp32c", "k_self<32>"): 1.289e+08,
+    ("batched_64_mixed_p", "fp32c", "k_self<48>"): 3.19e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x12"): 1.89e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x14"): 1.909e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x15"): 1.916e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x16"): 1.928e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x12"): 1.221e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x14"): 1.242e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x15"): 1.259e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x16"): 1.284e+09,
+    ("batched_64_mixed_p", "fp64", "k_self<16>"): 7.186e+06,
+    ("batched_64_mixed_p", "fp64", "k_self<24>"): 2.509e+07,
+    ("batched_64_mixed_p", "fp64", "k_self<32>"): 1.289e+08,
+    ("batched_64_mixed_p", "fp64", "k_self<48>"): 3.19e+09,
     ("large_256_p32", "fp32c", "k_far32", "1x12"): 9.241e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x14"): 9.513e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x15"): 9.478e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x16"): 1.091e+10,
-    ("large_256_p32", "fp32c", "k_far32", "2x12"): 5.428e+09,
-    ("large_256_p32", "fp32c", "k_far32", "2x14"): 5.514e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x14"): 9.494e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x15"): 9.568e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x16"): 1.151e+10,
+    ("large_256_p32", "fp32c", "k_far32", "2x12"): 5.432e+09,
+    ("large_256_p32", "fp32c", "k_far32", "2x14"): 5.523e+09,
     ("large_256_p32", "fp32c", "k_far32", "2x15"): 5.564e+09,
-    ("large_256_p32", "fp32c", "k_far32", "2x16"): 5.648e+09,
-    ("large_256_p32", "fp64", "k_far64", "1x12"): 6.26e+10,
-    ("large_256_p32", "fp64", "k_far64", "1x14"): 8.783e+10,
-    ("large_256_p32", "fp64", "k_far64", "1x15"): 7.441e+10,
-    ("large_256_p32", "fp64", "k_far64", "1x16"): 9.977e+10,
-    ("large_256_p32", "fp64", "k_far64", "2x12"): 1.695e+10,
-    ("large_256_p32", "fp64", "k_far64", "2x14"): 1.902e+10,
-    ("large_256_p32", "fp64", "k_far64", "2x15"): 1.94e+10,
-    ("large_256_p32", "fp64", "k_far64", "2x16"): 2.234e+10,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x12"): 4.735e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x14"): 4.518e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x15"): 4.571e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x16"): 4.661e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x12"): 5.844e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x14"): 5.558e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x15"): 5.453e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x16"): 5.381e+08,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x12"): 5.991e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x14"): 4.871e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x15"): 3.977e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x16"): 3.348e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x12"): 2.147e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x14"): 2.085e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x15"): 1.887e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x16"): 1.746e+09,
-    ("large_256_p32", "fp64", "k_self<32>"): 1.815e9,
-    ("large_256_p32", "fp32c", "k_self<32>"): 1.815e9,
+    ("large_256_p32", "fp32c", "k_far32", "2x16"): 5.662e+09,
+    ("large_256_p32", "fp32c", "k_self<32>"): 1.923e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x12"): 9.212e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x14"): 9.324e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x15"): 9.379e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x16"): 9.444e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x12"): 5.433e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x14"): 5.551e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x15"): 5.606e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x16"): 5.665e+09,
+    ("large_256_p32", "fp64", "k_self<32>"): 1.923e+09,
 }
-for _pmax, _b in ((48, 6.773e8), (32, 1.202e8), (24, 2.543e7), (16, 7.398e6)):
-    for _prec in ("fp64", "fp32c"):
-        TRAFFIC_BYTES[("batched_64_mixed_p", _prec, f"k_self<{_pmax}>")] = _b
 
 
 def kernel_source_sha256() -> str:

@@ -141,16 +141,18 @@ __global__ __launch_bounds__(kMomThreads) void k_p2m(const ehd::ExpandDrop* __re
     const int e_rec = tid - 128;
     const bool rec_role = e_rec >= 0 && e_rec < 14 * ST;
     const double* const rsrc = src + (long long)(rec_role ? e_rec / ST : 0) * Spad;
-    // past the last source: no strength, at the centre (the basis of a place
+    // past the last source: its place without a strength (the basis of a place
     // far from the drop overflows, and infinity times no strength is NaN)
-    const double pad = !rec_role || e_rec >= 3 * ST ? 0.0 : e_rec < ST ? c0 : e_rec < 2 * ST ? c1 : c2;
+    const bool place = e_rec < 7 * ST;
+    const long long slast = s1 - 1;
     double next = 0.0;
     for (int k = -2; k < nst; ++k) {
         // stage k + 2 loaded, stage k + 1 built, stage k multiplied
         const int kb = (k + 1) & 1, kc = k & 1;
         if (rec_role) {
             const long long s = s0 + (long long)(k + 2) * ST + e_rec % ST;
-            next = s < s1 ? rsrc[s] : pad;
+            const double v = rsrc[s < slast ? s : slast];
+            next = s < s1 || place ? v : 0.0;
         }
         if (k >= -1) {
             const int s = tid % ST;

@@ -82,48 +82,48 @@ TRAFFIC_SOURCE_SHA256 = "4b082327cf9e1c52651f1aac90ec2edc4e897f54bd88beabcbe87fd
 # launch of all its items; a far-field kernel's traffic depends on its tile
 # shape (per-chunk partial sums, source re-reads per block of targets)
 TRAFFIC_BYTES = {
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x12"): 4.647e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x14"): 4.493e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x15"): 4.548e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "1x16"): 4.647e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x12"): 5.798e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x14"): 5.473e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x15"): 5.469e+08,
-    ("batched_64_mixed_p", "fp32c", "k_far32", "2x16"): 5.39e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x12"): 4.678e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x14"): 4.514e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x15"): 4.577e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "1x16"): 4.655e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x12"): 5.823e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x14"): 5.489e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x15"): 5.471e+08,
+    ("batched_64_mixed_p", "fp32c", "k_far32", "2x16"): 5.379e+08,
     ("batched_64_mixed_p", "fp32c", "k_self<16>"): 7.186e+06,
     ("batched_64_mixed_p", "fp32c", "k_self<24>"): 2.509e+07,
-    ("batched_64_mixed_p", "fp32c", "k_self<32>"): 1.289e+08,
-    ("batched_64_mixed_p", "fp32c", "k_self<48>"): 3.19e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x12"): 1.89e+09,
+    ("batched_64_mixed_p", "fp32c", "k_self<32>"): 1.699e+08,
+    ("batched_64_mixed_p", "fp32c", "k_self<48>"): 3.641e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x12"): 1.891e+09,
     ("batched_64_mixed_p", "fp64", "k_far64", "1x14"): 1.909e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x15"): 1.916e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "1x16"): 1.928e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x12"): 1.221e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x15"): 1.913e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "1x16"): 1.937e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x12"): 1.222e+09,
     ("batched_64_mixed_p", "fp64", "k_far64", "2x14"): 1.242e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x15"): 1.259e+09,
-    ("batched_64_mixed_p", "fp64", "k_far64", "2x16"): 1.284e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x15"): 1.258e+09,
+    ("batched_64_mixed_p", "fp64", "k_far64", "2x16"): 1.282e+09,
     ("batched_64_mixed_p", "fp64", "k_self<16>"): 7.186e+06,
     ("batched_64_mixed_p", "fp64", "k_self<24>"): 2.509e+07,
-    ("batched_64_mixed_p", "fp64", "k_self<32>"): 1.289e+08,
-    ("batched_64_mixed_p", "fp64", "k_self<48>"): 3.19e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x12"): 9.241e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x14"): 9.494e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x15"): 9.568e+09,
-    ("large_256_p32", "fp32c", "k_far32", "1x16"): 1.151e+10,
-    ("large_256_p32", "fp32c", "k_far32", "2x12"): 5.432e+09,
-    ("large_256_p32", "fp32c", "k_far32", "2x14"): 5.523e+09,
-    ("large_256_p32", "fp32c", "k_far32", "2x15"): 5.564e+09,
-    ("large_256_p32", "fp32c", "k_far32", "2x16"): 5.662e+09,
-    ("large_256_p32", "fp32c", "k_self<32>"): 1.923e+09,
-    ("large_256_p32", "fp64", "k_far64", "1x12"): 9.212e+09,
-    ("large_256_p32", "fp64", "k_far64", "1x14"): 9.324e+09,
-    ("large_256_p32", "fp64", "k_far64", "1x15"): 9.379e+09,
-    ("large_256_p32", "fp64", "k_far64", "1x16"): 9.444e+09,
+    ("batched_64_mixed_p", "fp64", "k_self<32>"): 1.699e+08,
+    ("batched_64_mixed_p", "fp64", "k_self<48>"): 3.641e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x12"): 9.238e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x14"): 9.515e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x15"): 9.467e+09,
+    ("large_256_p32", "fp32c", "k_far32", "1x16"): 1.104e+10,
+    ("large_256_p32", "fp32c", "k_far32", "2x12"): 5.427e+09,
+    ("large_256_p32", "fp32c", "k_far32", "2x14"): 5.513e+09,
+    ("large_256_p32", "fp32c", "k_far32", "2x15"): 5.562e+09,
+    ("large_256_p32", "fp32c", "k_far32", "2x16"): 5.647e+09,
+    ("large_256_p32", "fp32c", "k_self<32>"): 2.782e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x12"): 9.207e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x14"): 9.332e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x15"): 9.384e+09,
+    ("large_256_p32", "fp64", "k_far64", "1x16"): 9.446e+09,
     ("large_256_p32", "fp64", "k_far64", "2x12"): 5.433e+09,
-    ("large_256_p32", "fp64", "k_far64", "2x14"): 5.551e+09,
-    ("large_256_p32", "fp64", "k_far64", "2x15"): 5.606e+09,
-    ("large_256_p32", "fp64", "k_far64", "2x16"): 5.665e+09,
-    ("large_256_p32", "fp64", "k_self<32>"): 1.923e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x14"): 5.545e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x15"): 5.607e+09,
+    ("large_256_p32", "fp64", "k_far64", "2x16"): 5.664e+09,
+    ("large_256_p32", "fp64", "k_self<32>"): 2.782e+09,
 }
 
 
